@@ -22,10 +22,13 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 
 # The sources each measured kernel is built from (the rollout kernels live in a
 # header of their own, which these kernels do not use).
-_CORE_SOURCES = ["include/saki.h", "paper_2609_36601_amd/csrc/saki.hip", "paper_2609_36601_amd/csrc/row_engine.hpp",
-                 "paper_2609_36601_amd/csrc/device_util.hpp"]
-KERNEL_SOURCES = {"couple": _CORE_SOURCES, "route": _CORE_SOURCES, "verify": _CORE_SOURCES, "stream": _CORE_SOURCES,
-                  "probe": _CORE_SOURCES + ["paper_2609_36601_amd/csrc/probe.hpp"]}
+_CSRC = "paper_2609_36601_amd/csrc/"
+_CORE_SOURCES = ["include/saki.h"] + [_CSRC + f for f in ("common.hpp", "row_engine.hpp", "device_util.hpp")]
+KERNEL_SOURCES = {"couple": _CORE_SOURCES + [_CSRC + "couple.hpp", _CSRC + "couple.hip"],
+                  "verify": _CORE_SOURCES + [_CSRC + "verify.hpp", _CSRC + "verify.hip"],
+                  "route": _CORE_SOURCES + [_CSRC + "saki.hip"],
+                  "probe": _CORE_SOURCES + [_CSRC + "probe.hpp", _CSRC + "saki.hip"]}
+KERNEL_SOURCES["stream"] = KERNEL_SOURCES["couple"]
 
 # HBM traffic of one step of the dominant kernel, from two rocprofv3 --pmc runs
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch): the couple kernel on the large

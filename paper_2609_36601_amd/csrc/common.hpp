@@ -1,0 +1,38 @@
+// What the row kernels share: workgroup shape, row cache sizes, the work counter.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <math.h>
+#include <stdint.h>
+
+#include "../../include/saki.h"
+#include "row_engine.hpp"
+
+namespace saki {
+
+constexpr int NT = 256;
+constexpr int WG_PER_CU = 2;
+// bf16 rows of up to CACHED_MAXC chunks (262,144 entries) use the variant with
+// a row cache of CACHE_KC chunks per wave: 4 KiB of chunk masses and 64 KiB of
+// cached chunks per workgroup, two workgroups in the 160 KiB of LDS of a CU.
+// The cached chunks are read once per row instead of three times.
+constexpr int CACHED_MAXC = 256;
+constexpr int CACHE_KC = 4;
+template <int KC>
+using RowSharedK = RowShared<NT, (KC > 0 ? CACHED_MAXC : MAX_CHUNKS), KC>;
+
+__device__ __forceinline__ float nanf_() { return __builtin_nanf(""); }
+
+// Takes the next work item (row or block) for the whole workgroup: thread 0
+// takes it from the counter with a device atomic and posts it in LDS, and
+// readfirstlane makes the index, and so the caller's loop exit, uniform in
+// every wave, so all threads reach the same barriers.
+__device__ __forceinline__ unsigned int take_next(unsigned int* counter, unsigned int* slot) {
+  if (threadIdx.x == 0) *slot = atomicAdd(counter, 1u);
+  __syncthreads();
+  const unsigned int v = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(*slot)));
+  __syncthreads();
+  return v;
+}
+
+}  // namespace saki
