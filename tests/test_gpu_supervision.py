@@ -112,3 +112,32 @@ def test_selection_routes_through_route_loss(saki_lib):
     assert abs(float(r["loss_sum"].item()) - ls) <= 1e-5 * abs(ls) + 1e-9
     assert np.max(np.abs(r["grad"].cpu().numpy() * 256 - g * 256)) < 2e-3
     assert int(sel.sum()) == int(out["corrected"].sum())
+
+
+@pytest.mark.parametrize("lengths, special", [
+    ([255, 256, 257, 1, 63, 64, 65, 1500], "none"),        # mean below 512: 256-thread workgroups, one long trajectory
+    ([1023, 1024, 1025, 2048, 600], "none"),               # 1,024-thread workgroups, edges of their passes
+    ([40000, 700], "range"),                               # a bin of more rows than LDS ranks: the second level
+    ([5000, 900, 4000], "inf"),                            # infinite keys: all in one bin, ties to the lower row
+])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_selection_sizes_and_key_ranges(saki_lib, lengths, special, mode):
+    """Selections are exact for every size and key range, whichever of the
+    histogram levels or the bisection resolves the trajectory."""
+    rng = np.random.default_rng(len(lengths) + mode)
+    off = np.concatenate([[0], np.cumsum(lengths)])
+    n = int(off[-1])
+    tv = (rng.random(n) ** 3).astype(np.float32)
+    if special == "range":
+        tv[:] = 1.0
+        tv[[3, 17]] = 1e-38, 3e38
+    elif special == "inf":
+        tv[rng.random(n) < 0.6] = np.inf
+    C = (rng.random(n) < 0.3).astype(np.uint8)
+    valid = (rng.random(n) < 0.9).astype(np.uint8)
+    say(f"select lengths={lengths} special={special} mode={mode}")
+    sel = saki_lib.select_positions(mode, torch.as_tensor(off, device=DEV), torch.as_tensor(tv, device=DEV),
+                                    torch.as_tensor(C, device=DEV), 99, torch.as_tensor(valid, device=DEV), 1000)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        _compare_selection(sel.cpu().numpy(), tv.astype(np.float64), C, valid, off, 99, 1000, mode)
