@@ -35,4 +35,9 @@ __device__ __forceinline__ unsigned int take_next(unsigned int* counter, unsigne
   return v;
 }
 
+// A condition that every lane of a wave computes alike (from LDS or uniform
+// data), as one the compiler knows to be uniform: a branch on it that leaves or
+// restarts a loop with barriers is then a scalar branch, never a masked one.
+__device__ __forceinline__ bool uniform(bool c) { return __builtin_amdgcn_readfirstlane(c ? 1 : 0) != 0; }
+
 }  // namespace saki

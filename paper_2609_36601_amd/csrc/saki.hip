@@ -27,6 +27,32 @@ __global__ void clear_counter_kernel(unsigned int* c) {
   if (threadIdx.x < 4) c[threadIdx.x] = 0u;
 }
 
+// Verification, before: no block has stopped, no item is taken.
+__global__ __launch_bounds__(256) void verify_begin_kernel(unsigned long long* next_item, int64_t n_blocks, int k,
+                                                           int32_t* accepted_len) {
+  const int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (b == 0) *next_item = 0ull;
+  if (b < n_blocks) accepted_len[b] = stop_word(k, false, -1);
+}
+
+// Verification, after: each block's word (its first stopping position) becomes
+// its accepted length and correction; the positions behind it are skipped
+// ones, also those evaluated ahead.
+__global__ __launch_bounds__(256) void verify_end_kernel(VerifyParams P) {
+  const int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (b >= P.n_blocks) return;
+  const int32_t w = P.accepted_len[b];
+  const int j = stop_pos(w);
+  P.accepted_len[b] = j + ((w >> 22) & 1);
+  P.correction[b] = (w & ((1 << 22) - 1)) - 1;
+  if (P.has_pp) {
+    for (int jj = j + 1; jj < P.k; ++jj) {
+      const int64_t r = b * P.k + jj;
+      write_skipped(P.pp, r, P.draft[r], SAKI_ROW_SKIPPED);
+    }
+  }
+}
+
 #include "rollout.hpp"
 
 // ---------------------------------------------------------------------------
@@ -505,15 +531,21 @@ saki_status saki_spec_verify(const saki_rows* in, int32_t k, const int32_t* draf
     P.pp = *per_pos;
     P.has_pp = 1;
   }
-  P.next_block = static_cast<unsigned int*>(ws);
+  // the 64-bit counter at the first 8-byte boundary of the 256 bytes
+  P.next_item = reinterpret_cast<unsigned long long*>((reinterpret_cast<uintptr_t>(ws) + 7u) & ~static_cast<uintptr_t>(7u));
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(saki::clear_counter_kernel, dim3(1), dim3(64), 0, hs, P.next_block);
-  st = launched("clear_counter_kernel");
+  const dim3 per_block(static_cast<unsigned>((P.n_blocks + 255) / 256));
+  hipLaunchKernelGGL(saki::verify_begin_kernel, per_block, dim3(256), 0, hs, P.next_item, P.n_blocks, P.k,
+                     P.accepted_len);
+  st = launched("verify_begin_kernel");
   if (st != SAKI_OK) return st;
   const bool bf16 = in->dtype == SAKI_BF16;
   const hipError_t e = saki::use_k34(P.eps) ? saki::launch_verify_part<1>(P, cus, bf16, hs)
                                             : saki::launch_verify_part<0>(P, cus, bf16, hs);
   if (e != hipSuccess) return fail(SAKI_E_LAUNCH, std::string("verify_kernel: ") + hipGetErrorString(e));
+  hipLaunchKernelGGL(saki::verify_end_kernel, per_block, dim3(256), 0, hs, P);
+  st = launched("verify_end_kernel");
+  if (st != SAKI_OK) return st;
   return ok();
 }
 

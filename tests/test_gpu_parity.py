@@ -288,6 +288,43 @@ def test_verify_edge_cases(saki_lib):
         assert st[9] == 2
 
 
+@pytest.mark.parametrize("nb, k", [(1, 1), (1, 64), (32, 8), (33, 8), (64, 8), (150, 7), (600, 1)])
+def test_verify_positions_evaluated_ahead(saki_lib, nb, k):
+    """Batches on both sides of one and two workgroups per CU: positions behind
+    a block's stop (a rejection, an accepted EOS, bad logits, a draft outside
+    the vocabulary) are evaluated ahead or skipped, and leave no trace."""
+    V, eos, eps, seed = 600, 7, 0.1, 21
+    g = torch.Generator(device=DEV).manual_seed(100 * nb + k)
+    n = nb * k
+    s = torch.randn(n, V, generator=g, device=DEV)
+    t = s + 0.5 * torch.randn(n, V, generator=g, device=DEV)
+    draft = torch.multinomial(s.softmax(1), 1, generator=g).squeeze(1).to(torch.int32)
+    draft[torch.rand(n, generator=g, device=DEV) < 0.05] = eos
+    draft[torch.rand(n, generator=g, device=DEV) < 0.02] = V + 3
+    s[torch.rand(n, generator=g, device=DEV) < 0.02, 5] = float("nan")
+    say(f"verify ahead nb={nb} k={k}")
+    out = saki_lib.spec_verify(s, t, k, draft, eps, seed, eos_id=eos)
+    lean = saki_lib.spec_verify(s, t, k, draft, eps, seed, eos_id=eos, per_pos=False)
+    torch.cuda.synchronize()
+    pp = np_out(out["per_pos"])
+    gpu = dict(accepted_len=out["accepted_len"].cpu().numpy(), correction=out["correction"].cpu().numpy(), per_pos=pp)
+    R = parity.compare_verify(gpu, f64(s), f64(t), k, draft.cpu().numpy(), eps, seed, 0, np.arange(nb), eos_id=eos)
+    say(R.summary())
+    R.check()
+    assert torch.equal(out["accepted_len"], lean["accepted_len"]) and torch.equal(out["correction"], lean["correction"])
+    # the position a block stops at: its correction, its EOS draft, or a bad position
+    al, st = gpu["accepted_len"], pp["row_status"].reshape(nb, k)
+    d = draft.cpu().numpy().reshape(nb, k)
+    for b in range(nb):
+        stop = int(al[b])
+        if stop > 0 and d[b, stop - 1] == eos:
+            stop -= 1
+        assert np.all(st[b, :stop] == 0) and np.all(st[b, stop + 1:] == 3), (b, stop, st[b])
+    skipped = (st == 3).reshape(-1)
+    assert np.all(pp["token"][skipped] == -1) and np.all(np.isnan(pp["lambda"][skipped]))
+    assert np.array_equal(pp["proposal"], draft.cpu().numpy()) and np.all(pp["corrected"][skipped] == 0)
+
+
 def padded(x):
     """Copy of a [n, V] tensor in storage whose row pitch is a multiple of 16 bytes."""
     n, V = x.shape
