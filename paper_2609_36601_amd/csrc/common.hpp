@@ -23,12 +23,20 @@ using RowSharedK = RowShared<NT, (KC > 0 ? CACHED_MAXC : MAX_CHUNKS), KC>;
 
 __device__ __forceinline__ float nanf_() { return __builtin_nanf(""); }
 
+// The next index from a work counter in device memory (a global atomic: the
+// pointer's address space spares the check that a flat one needs).
+template <typename C>
+__device__ __forceinline__ C take_index(C* counter) {
+  return __hip_atomic_fetch_add((__attribute__((address_space(1))) C*)counter, C{1}, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Takes the next work item (row or block) for the whole workgroup: thread 0
 // takes it from the counter with a device atomic and posts it in LDS, and
 // readfirstlane makes the index, and so the caller's loop exit, uniform in
 // every wave, so all threads reach the same barriers.
 __device__ __forceinline__ unsigned int take_next(unsigned int* counter, unsigned int* slot) {
-  if (threadIdx.x == 0) *slot = atomicAdd(counter, 1u);
+  if (threadIdx.x == 0) *slot = take_index(counter);
   __syncthreads();
   const unsigned int v = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(*slot)));
   __syncthreads();

@@ -13,6 +13,7 @@ struct CoupleParams {
   int64_t row_offset;
   int V;
   double eps;
+  float lam_mid;  // mid_lambda(eps)
   uint64_t seed;
   saki_couple_out out;
   // routing
@@ -23,38 +24,51 @@ struct CoupleParams {
   void* grad;
   int64_t grad_stride;
   int target_mode;      // SAKI_TARGET_MODE or SAKI_TARGET_SAMPLE
-  unsigned int* next_row;  // work counter in the caller's workspace, zero at launch
-  // Rows resolved in the plain forms whose TV turns out too small for their
-  // rounding are listed (redo_list, redo_count, in the workspace) and processed
-  // again by a second launch with every sweep in the expm1 form (redo_pass).
-  unsigned int* redo_list;
-  unsigned int* redo_count;
-  int redo_pass;
+  unsigned int* next_row;  // work counter in the caller's workspace, zero at launch; NULL: one row per workgroup
 };
 
 // K34: the stats sweep sums k3, k4 (radii below K34_EPS).
 template <typename T, typename G, bool ROUTE, bool GRAD, int KC, bool K34>
 __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
-  __shared__ RowSharedK<KC> sh;
+  using SH = RowSharedK<KC>;
+  __shared__ SH sh;
   __shared__ RowPlan plan;
-  Block<NT, RowSharedK<KC>> B(sh);
+  Block<NT, SH> B(sh);
   const int V = P.V;
   const int nch = (V + CHUNK - 1) / CHUNK;
   // Workgroups take rows from a counter: their speeds differ (the two
   // workgroups of a CU, and CUs, get unequal shares of the memory system), so
   // a fixed stride left the slowest ones finishing ~15% after the median.
-  // Each iteration takes a new row or ends the loop: at most n_rows + 1.
-  __shared__ unsigned int next_r;
-  // the second launch takes its rows from the list the first one made
-  const unsigned int n_work = P.redo_pass
-      ? static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(*P.redo_count)))
-      : static_cast<unsigned int>(P.n_rows);
-  const bool force_acc = P.redo_pass != 0;
-  for (int64_t it = 0; it <= P.n_rows; ++it) {
-    const unsigned int ru = take_next(P.next_row, &next_r);
-    // unsigned: n_rows < 2^31 and the counter stays below n_rows + grid
-    if (ru >= n_work) break;
-    const int64_t r = static_cast<int64_t>(P.redo_pass ? P.redo_list[ru] : ru);
+  // Workgroup b starts with row b.  Far from the end of the launch a lane of an
+  // idle wave takes the next index while wave 0 combines a row's sums, and
+  // posts it in LDS, so that a wave that is done with a row goes on to the next
+  // one without a barrier (the next row's first LDS writes are the chunk
+  // masses, read last before the barriers of the races, and each wave's own
+  // cache and reduction slots; plan and rs are written behind its first
+  // barrier).  The last two rows per workgroup are taken when it is free for
+  // them: a row taken ahead waits for the current one, and the launch ends
+  // later for it (4,096 long-rollout rows, eight per workgroup: +3%).
+  // readfirstlane makes the index, and so the loop's exit, uniform in every
+  // wave: all threads reach the same barriers.  The indices only grow, so
+  // every workgroup ends.
+  unsigned int ru = blockIdx.x;
+  bool taken = true;
+  // a row resolved in a plain form whose TV turns out too small for that
+  // form's rounding is processed again with every sweep in the expm1 form (rare)
+  bool force_acc = false;
+  // unsigned: n_rows < 2^31 and the counter stays below n_rows + grid
+  const unsigned int n_rows = static_cast<unsigned int>(P.n_rows);
+  for (;;) {
+    if (!taken) {
+      if (B.tid == 0) sh.next = gridDim.x + take_index(P.next_row);
+      __syncthreads();
+      ru = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)));
+    }
+    if (ru >= n_rows) break;
+    const bool ahead = P.next_row == nullptr || ru + 2 * gridDim.x < n_rows;
+    const bool take_now = ahead && !force_acc;
+    taken = ahead;
+    const int64_t r = static_cast<int64_t>(ru);
     const T* srow = static_cast<const T*>(P.s) + r * P.stride;
     const T* trow = static_cast<const T*>(P.t) + r * P.stride;
     G* grow = GRAD ? static_cast<G*>(P.grad) + r * P.grad_stride : nullptr;
@@ -62,8 +76,31 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     const float M = (ROUTE && P.valid) ? (P.valid[r] ? 1.0f : 0.0f) : 1.0f;
 
     const bool sample_target = ROUTE && P.target_mode == SAKI_TARGET_SAMPLE;
-    const RowStats& R = stats_sweep<T, NT, true, K34>(B, srow, trow, V, mid_lambda(P.eps), true, sample_target);
-    if (!R.finite) {
+    // while wave 0 combines the sums: the proposal's chunk race on the other
+    // waves, the accept uniform and the next index on a lane of the last one
+    auto idle = [&]() {
+      constexpr int NW = SH::NW;
+      const bool last = B.tid == NT - WAVE;
+      const bool take = last && take_now;
+      unsigned int nx = n_rows;
+      if (take && P.next_row) nx = gridDim.x + take_index(P.next_row);
+      double key;
+      int idx;
+      wave_chunk_race(nch, (B.wave - 1) * WAVE + B.lane, (NW - 1) * WAVE, P.seed, PROP_CHUNK, g, [&](int c) {
+        return static_cast<double>(sh.chunk_a[c]) * LN2_D + log(static_cast<double>(sh.chunk_b[c]));
+      }, &key, &idx);
+      if (B.lane == 0) {
+        sh.race_key[B.wave] = key;
+        sh.race_idx[B.wave] = idx;
+      }
+      if (last) {
+        if (take) sh.next = nx;
+        sh.u = philox_uniform(P.seed, ACCEPT, g, 0);
+      }
+    };
+    const RowStats& R = stats_sweep<T, NT, true, K34>(B, srow, trow, V, P.lam_mid, true, sample_target, idle);
+    if (ahead) ru = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)));
+    if (uniform(!R.finite)) {
       if (GRAD) fill_row<G, NT>(B.wave, B.lane, grow, V, M != 0.0f ? nanf_() : 0.0f);
       if (B.tid == 0) {
         const saki_couple_out& o = P.out;
@@ -87,6 +124,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
           if (P.scaled_loss) P.scaled_loss[r] = static_cast<double>(l);
         }
       }
+      force_acc = false;
       continue;
     }
 
@@ -100,9 +138,8 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     // exactly); the others, and fused rows whose checks fail, the lambda
     // search and the final sweep.
     // The serial steps between sweeps run on one wave at a time: wave 0 the
-    // start point while wave 1 draws the proposal z ~ p (the two-level race on
-    // the stats sweep's chunk masses, then the entry race in the winning
-    // chunk), which leaves the other waves' issue slots to the other
+    // start point while wave 1 draws the proposal z ~ p in the chunk that won
+    // the chunk race, which leaves the other waves' issue slots to the other
     // workgroup of the CU; the results go through LDS (plan).
     const bool end_first = R.kl1_est <= 1.05 * P.eps + 1e-5;
     if (B.wave == 0) {
@@ -120,12 +157,9 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       }
     } else if (B.wave == 1) {
       float ws, wt;
-      const int zz = wave_proposal<T>(srow, trow, nch, V, B.lane, P.seed, PROP_CHUNK, PROP_ELEM, g,
-                                      [&](int c) {
-                                        return static_cast<double>(sh.chunk_a[c]) * LN2_D +
-                                               log(static_cast<double>(sh.chunk_b[c]));
-                                      },
-                                      [](float sv, float, int) { return sv; }, &ws, &wt);
+      const int pc = race_winner(sh);
+      const int zz = wave_elem_race<T>(srow, trow, pc < nch ? pc : 0, V, B.lane, P.seed, PROP_ELEM, g,
+                                       [](float sv, float, int) { return sv; }, &ws, &wt);
       if (B.lane == 0) {
         plan.z = zz;
         plan.sz = ws;
@@ -133,7 +167,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       }
     }
     __syncthreads();
-    const bool fused = plan.fused != 0;
+    const bool fused = uniform(plan.fused != 0);
 
     float sz = plan.sz, tz = plan.tz;
     int z = plan.z;
@@ -142,7 +176,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       sz = s_vstar;
       tz = Loader<T>::load1(trow + z);
     }
-    const double u = static_cast<double>(philox_uniform(P.seed, ACCEPT, g, 0));
+    const double u = static_cast<double>(sh.u);
     const double logp_z = static_cast<double>(sz) - R.lse_s;
     const double logt_z = static_cast<double>(tz) - R.lse_t;
     const double adv = logt_z - logp_z;
@@ -171,87 +205,97 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
         s_hot_c = sv;
       }
     };
-    auto sweep1 = [&](float lam, bool acc) { return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc); };
 
     LamResult L;
     FinalConst F;
-    bool C;
-    double TV = 0.0;
+    bool C = false;
+    bool search = true;    // lambda* by lambda sweeps
+    double TV = 0.0, alpha = 0.0;
     bool tv_acc = false;   // the fused sweep's form (the final sweep's is F.acc)
     bool settled = false;  // TV, the residual chunk and the gradient row come from the fused sweep
+    bool redo = false;     // the row again in the expm1 forms
     int res_chunk = nch;
     if (fused) {
       // accept decision at the start point: it sets the gradient the fused
       // sweep writes, and must agree with the one at lambda*
-      const double xz = (static_cast<double>(LOG2E) * (static_cast<double>(tz) - static_cast<double>(sz)) -
-                         static_cast<double>(R.cL)) * LN2_D;
-      const bool Cg = !(u < exp(fmin(0.0, plan.S0.lam * xz - plan.S0.A)));
+      // (in float: a decision within its rounding of a tie may differ from the
+      // one at lambda*, and then takes the final sweep)
+      const float lam_g = static_cast<float>(plan.S0.lam);
+      const float A_g = static_cast<float>(plan.S0.A * static_cast<double>(LOG2E));
+      const bool Cg = uniform(!(sh.u < fexp2(fminf(0.0f, fmaf(lam_g, fmaf(tz - sz, LOG2E, -R.cL), -A_g)))));
       if (Cg) correction_target();
       const float coef_g = coef_of(Cg);
       FusedConst FC;
       FC.msL = R.ms * LOG2E;
       FC.cL = R.cL;
-      FC.lam = static_cast<float>(plan.S0.lam);
-      FC.AL = static_cast<float>(plan.S0.A * static_cast<double>(LOG2E));
-      const float invS = static_cast<float>(shift_correction(R.ms, FC.msL) / R.sum_s);
+      FC.lam = lam_g;
+      FC.AL = A_g;
+      const float invS = static_cast<float>(R.shift * R.inv_s);
       FC.gsc = coef_g * invS;
       FC.set_y();
       // the expm1 form where the lambda sweep would take it (KL below
       // KL_ACCURATE: the radius, or KL(pi || p) at the teacher end) and on
       // peaked rows, whose TV the plain form would often leave too imprecise;
       // elsewhere a row whose TV turns out too small for the plain form is
-      // listed for the accurate second launch (redo_accurate)
+      // processed again in the accurate forms (redo_accurate)
       const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
       tv_acc = facc;
       const FusedSums FS = fused_sweep_any<T, G, NT, GRAD>(B, srow, trow, grow, V, FC, facc, Cg, coef_g, invS,
                                                           Cg ? hot_c : z, Cg ? s_hot_c : sz);
       // wave 0: lambda* from the node's model when it needs no sweep, the
-      // accept decision there and TV from the fused sums
+      // accept decision there and TV from the fused sums; the other waves run
+      // the residual's chunk race meanwhile where a correction is predicted
+      double le0 = 0.0;
       if (B.wave == 0) {
+        FC.set_node();
         const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
         const LamResult L0 = lambda_search_with(R, P.eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
-                                                &E0, facc, true);
-        int state = -1, C0 = 0;
+                                                true, E0, facc, true);
+        int state = -1, C0 = 0, redo = 0;
+        double alpha0 = 0.0;
         FinalConst F0{};
         FusedFinal FF0{};
         if (L0.sweeps == 0) {
           F0 = final_const(R, L0, false);
-          C0 = !(u < exp(fmin(0.0, L0.log_ratio(sz, tz)))) ? 1 : 0;
+          alpha0 = exp(fmin(0.0, L0.log_ratio(sz, tz)));
+          C0 = !(u < alpha0) ? 1 : 0;
           FF0 = fused_tv(R, L0, F0, FC, FS, facc);
           state = (FF0.ok && (C0 != 0) == Cg) ? 1 : 0;
+          redo = (state == 1 && redo_accurate(R, L0, facc, FF0.TV)) ? 1 : 0;
         }
         if (B.lane == 0) {
           plan.L = L0;
           plan.F = F0;
           plan.FF = FF0;
+          plan.E0 = E0;
+          plan.alpha = alpha0;
           plan.state = state;
           plan.C = C0;
+          plan.redo = redo;
         }
+      } else if (Cg) {
+        le0 = res_race_begin<NT>(B, nch, P.seed, g);
       }
       __syncthreads();
-      if (plan.state < 0) {
-        // the node's model did not settle lambda*: the search goes on with
-        // lambda sweeps from that node
-        const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-        L = lambda_search_with(R, P.eps, sweep1, false, 0.0f, &E0, facc);
-        F = final_const(R, L, false);
-        C = !(u < exp(fmin(0.0, L.log_ratio(sz, tz))));
-      } else {
+      const int state = __builtin_amdgcn_readfirstlane(plan.state);
+      search = state < 0;
+      if (!search) {
         L = plan.L;
         F = plan.F;
-        C = plan.C != 0;
-        if (plan.state == 1) {
+        alpha = plan.alpha;
+        C = uniform(plan.C != 0);
+        if (state == 1) {
           TV = plan.FF.TV;
           settled = true;
-          if (C) {
+          redo = uniform(plan.redo != 0);
+          if (C && !redo) {
             // the residual chunk from the masses at the node, each within
             // (2^hmax - 1) of its positive mass plus the sign-change bound
-            const double hb = expm1(plan.FF.hmax * LN2_D) * 1.02 + 2e-6;
-            const double flip = plan.FF.flip;
-            res_chunk = chunk_race_certain<NT>(B, nch, P.seed, RES_CHUNK, g, [&](int c, double& m, double& b) {
-              m = fmax(static_cast<double>(sh.chunk_a[c]), 0.0);
-              b = hb * static_cast<double>(sh.chunk_b[c]) + flip;
-            });
+            // (expm1(x) <= x + x^2 for the x <= 0.007 that fused_tv lets through)
+            const double hx = plan.FF.hmax * LN2_D;
+            const double hb = hx * (1.0 + hx) * 1.02 + 2e-6;
+            res_chunk = __builtin_amdgcn_readfirstlane(
+                res_race_end<NT>(B, nch, P.seed, g, le0, hb, plan.FF.flip));
             if (res_chunk < 0) {
               settled = false;
               res_chunk = nch;
@@ -259,15 +303,21 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
           }
         }
       }
-    } else {
-      L = lambda_search<T, NT>(B, srow, trow, V, R, P.eps, force_acc);
+    }
+    if (search) {
+      // lambda sweeps: from the fused sweep's node where its model did not
+      // settle lambda*, else from the start
+      const LamEval E0 = fused ? plan.E0 : LamEval{};
+      L = lambda_search_with(R, P.eps, [&](float lam, bool acc) {
+        return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc);
+      }, force_acc, 0.0f, fused, E0, tv_acc);
       F = final_const(R, L, force_acc);
-      C = !(u < exp(fmin(0.0, L.log_ratio(sz, tz))));
+      alpha = exp(fmin(0.0, L.log_ratio(sz, tz)));
+      C = uniform(!(u < alpha));
     }
 
-    // accept test, Eq. accept in the log form exp(min(0, log q(z) - log p(z)))
-    const double alpha = exp(fmin(0.0, L.log_ratio(sz, tz)));
-    if (C) correction_target();
+    // alpha: accept test, Eq. accept in the log form exp(min(0, log q(z) - log p(z)))
+    if (C && !redo) correction_target();
     const float coef = coef_of(C);
     const int hot = C ? hot_c : z;
     const float s_hot = C ? s_hot_c : sz;
@@ -281,12 +331,15 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
         });
       }
     }
-    if (!force_acc && redo_accurate(R, L, settled ? tv_acc : F.acc, TV)) {
-      // listed for the second launch, which rewrites the row's gradient and
-      // writes its outputs
-      if (B.tid == 0) P.redo_list[atomicAdd(P.redo_count, 1u)] = static_cast<unsigned int>(r);
+    if (!settled && !force_acc) redo = uniform(redo_accurate(R, L, F.acc, TV));
+    if (redo) {
+      // the same row again: its gradient is rewritten, its outputs written then
+      force_acc = true;
+      ru = static_cast<unsigned int>(r);
+      taken = true;
       continue;
     }
+    force_acc = false;
 
     int y = z;
     float sy = sz, ty = tz;

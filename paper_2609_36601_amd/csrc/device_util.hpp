@@ -295,31 +295,22 @@ __device__ __forceinline__ int wave_min(int v) {
 }
 // true on every lane if pred holds on any active lane
 __device__ __forceinline__ bool wave_any(bool pred) { return __ballot(pred) != 0; }
-// (key, index) minimum; ties go to the lower index.
-__device__ __forceinline__ void wave_argmin(float& key, int& idx) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const float k2 = __shfl_xor(key, o, WAVE);
-    const int i2 = __shfl_xor(idx, o, WAVE);
-    if (k2 < key || (k2 == key && i2 < idx)) { key = k2; idx = i2; }
-  }
+__device__ __forceinline__ double wave_min(double v) {
+  v = fmin(v, dpp_d<DPP_XOR1>(v));
+  v = fmin(v, dpp_d<DPP_XOR2>(v));
+  v = fmin(v, dpp_d<DPP_HALF_MIRROR>(v));
+  v = fmin(v, dpp_d<DPP_MIRROR>(v));
+  return fmin(fmin(lane_d(v, 0), lane_d(v, 16)), fmin(lane_d(v, 32), lane_d(v, 48)));
 }
-__device__ __forceinline__ void wave_argmin(double& key, int& idx) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const double k2 = __shfl_xor(key, o, WAVE);
-    const int i2 = __shfl_xor(idx, o, WAVE);
-    if (k2 < key || (k2 == key && i2 < idx)) { key = k2; idx = i2; }
-  }
-}
-// (value, index) maximum; ties go to the lower index.
-__device__ __forceinline__ void wave_argmax(float& val, int& idx) {
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const float v2 = __shfl_xor(val, o, WAVE);
-    const int i2 = __shfl_xor(idx, o, WAVE);
-    if (v2 > val || (v2 == val && i2 < idx)) { val = v2; idx = i2; }
-  }
+__device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+// (key, index) minimum; ties go to the lower index.  Two DPP reductions, the
+// key's and then the index's among the lanes holding it: a chain of six
+// exchanges of both through the LDS crossbar takes several times as long.
+template <typename K>
+__device__ __forceinline__ void wave_argmin(K& key, int& idx) {
+  const K k = wave_min(key);
+  idx = wave_min(key == k ? idx : 0x7fffffff);
+  key = k;
 }
 
 // ---------------------------------------------------------------------------

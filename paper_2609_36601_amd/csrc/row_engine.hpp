@@ -1,4 +1,7 @@
-// Per-row passes of the SAKI coupling path.  One workgroup of NT threads owns
+// Per-row passes of the SAKI coupling path.  Everything here is inlined into the
+// kernels, with one call site per sweep: a function left out of line takes its
+// Block, statistics and constants through scratch, and reaches LDS by flat
+// loads.  One workgroup of NT threads owns
 // one row at a time; chunk c of the row (1024 entries) belongs to wave c % NW,
 // which streams its chunks with the loads of its next chunk in flight.
 //
@@ -48,6 +51,8 @@ struct RowStats {
   float ms, mt;        // max s, max t
   double lse_s, lse_t; // log-sum-exp of s and t
   double sum_s;        // sum exp(s - ms)
+  double inv_s;        // 1 / sum_s
+  double shift;        // shift_correction(ms, ms log2(e) rounded to float)
   float c;             // centring constant: E_p[d] rounded to float
   float cL;            // c log2(e) rounded to float; X = fma(d, log2 e, -cL)
   double mean_p;       // E_p[d]
@@ -89,15 +94,29 @@ struct RowShared {
   int red_i[NW][4];
   uint4 cache[KC > 0 ? NW * KC * 4 * WAVE : 1];  // [wave][slot][s0, s1, t0, t1][lane]
   RowStatsLDS rs;  // the current row's statistics (stats_sweep)
+  unsigned int next;  // the workgroup's next work item
+  float u;            // the accept uniform
+  double race_key[NW];  // each wave's best chunk of a race run during the combination
+  int race_idx[NW];
 };
 
+
+// wave_argmin carrying two floats of the winner along.
+__device__ __forceinline__ void wave_argmin_with(float& key, int& idx, float& pa, float& pb) {
+  const int own = idx;
+  wave_argmin(key, idx);
+  // the winner's lane (an index is held by one lane; without a winner any lane does)
+  const int l = __builtin_ctzll(__ballot(own == idx));
+  pa = lane_f(pa, l);
+  pb = lane_f(pb, l);
+}
 
 template <int NT, typename SH = RowShared<NT>>
 struct Block {
   static constexpr int NW = NT / WAVE;
   int tid, lane, wave;
   SH& sh;
-  __device__ Block(SH& s) : sh(s) {
+  __device__ __forceinline__ Block(SH& s) : sh(s) {
     tid = threadIdx.x;
     lane = tid & (WAVE - 1);
     wave = tid / WAVE;
@@ -105,7 +124,7 @@ struct Block {
 
   // Sums N doubles over the block; every thread gets the same bits.
   template <int N>
-  __device__ void sum(double (&v)[N]) {
+  __device__ __forceinline__ void sum(double (&v)[N]) {
     static_assert(N <= RED_MAX, "block reduction wider than the LDS buffer");
 #pragma unroll
     for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
@@ -123,7 +142,29 @@ struct Block {
     __syncthreads();
   }
 
-  __device__ float max(float v) {
+  // Sums N doubles over the block for wave 0 alone (the other waves get
+  // partial sums); a barrier must follow before the next reduction.
+  template <int N>
+  __device__ __forceinline__ void sum_wave0(double (&v)[N]) {
+    static_assert(N <= RED_MAX, "block reduction wider than the LDS buffer");
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
+    if (lane == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) sh.red_d[wave][i] = v[i];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        double acc = 0.0;
+        for (int w = 0; w < NW; ++w) acc += sh.red_d[w][i];
+        v[i] = acc;
+      }
+    }
+  }
+
+  __device__ __forceinline__ float max(float v) {
     v = wave_max(v);
     if (lane == 0) sh.red_f[wave][0] = v;
     __syncthreads();
@@ -133,10 +174,10 @@ struct Block {
     return m;
   }
 
-  __device__ float min(float v) { return -max(-v); }
+  __device__ __forceinline__ float min(float v) { return -max(-v); }
 
   template <typename K>
-  __device__ void argmin(K& key, int& idx) {
+  __device__ __forceinline__ void argmin(K& key, int& idx) {
     wave_argmin(key, idx);
     if (lane == 0) {
       sh.red_d[wave][0] = static_cast<double>(key);
@@ -157,15 +198,8 @@ struct Block {
 
   // (key, index) minimum over the block, ties to the lower index, carrying
   // two floats of the winner along.
-  __device__ void argmin_with(float& key, int& idx, float& pa, float& pb) {
-#pragma unroll
-    for (int o = WAVE / 2; o > 0; o >>= 1) {
-      const float k2 = __shfl_xor(key, o, WAVE);
-      const int i2 = __shfl_xor(idx, o, WAVE);
-      const float a2 = __shfl_xor(pa, o, WAVE);
-      const float b2 = __shfl_xor(pb, o, WAVE);
-      if (k2 < key || (k2 == key && i2 < idx)) { key = k2; idx = i2; pa = a2; pb = b2; }
-    }
+  __device__ __forceinline__ void argmin_with(float& key, int& idx, float& pa, float& pb) {
+    wave_argmin_with(key, idx, pa, pb);
     if (lane == 0) {
       sh.red_f[wave][0] = key;
       sh.red_f[wave][1] = pa;
@@ -185,25 +219,6 @@ struct Block {
     idx = bi;
     pa = ba;
     pb = bb;
-  }
-
-  __device__ void argmax(float& val, int& idx) {
-    wave_argmax(val, idx);
-    if (lane == 0) {
-      sh.red_f[wave][0] = val;
-      sh.red_i[wave][0] = idx;
-    }
-    __syncthreads();
-    float bv = sh.red_f[0][0];
-    int bi = sh.red_i[0][0];
-    for (int w = 1; w < NW; ++w) {
-      const float v2 = sh.red_f[w][0];
-      const int i2 = sh.red_i[w][0];
-      if (v2 > bv || (v2 == bv && i2 < bi)) { bv = v2; bi = i2; }
-    }
-    __syncthreads();
-    val = bv;
-    idx = bi;
   }
 };
 
@@ -402,7 +417,7 @@ struct StatsAcc {
   int tidx;                     // wave-uniform lowest index of the running max of t
   float t_smax;                 // wave-uniform: t at an entry holding the running max of s
   float dmin, dmax;             // per-lane range of d
-  __device__ void init() {
+  __device__ __forceinline__ void init() {
     Ms = -finf(); Mt = -finf();
     MsL = -finf(); MtL = -finf();
     Ss = St = Sm = 0.0;
@@ -574,6 +589,7 @@ struct StatsBlock {
   float ms, mt;
   double Ss, S1, S2, S3, S4, St, T1, T2;
   double Sm, Q1, Q2;  // middle-node sums (relative to the row's maxima)
+  double cs;          // shift_correction of s
   float lm;           // the middle node
   float tbest;
   int tidx;
@@ -583,9 +599,10 @@ struct StatsBlock {
 
 // One exchange through LDS: each wave posts its sums (relative to its own
 // running maxima), maxima, argmax and range of d (stats_post); after a
-// barrier one thread combines the waves in a fixed order (stats_combine).
+// barrier wave 0 combines the waves in a fixed order (stats_combine; every lane
+// gets the same values).
 template <int NT, typename SH>
-__device__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
+__device__ __forceinline__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
   double v[11] = {a.Ss, static_cast<double>(a.S1), static_cast<double>(a.S2), static_cast<double>(a.S3),
                   static_cast<double>(a.S4), a.St, static_cast<double>(a.T1), static_cast<double>(a.T2),
                   a.Sm, static_cast<double>(a.Q1), static_cast<double>(a.Q2)};
@@ -610,7 +627,7 @@ __device__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
 }
 
 template <int NT, typename SH>
-__device__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
+__device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
   constexpr int NW = NT / WAVE;
   StatsBlock O;
   O.ms = -finf();
@@ -631,6 +648,19 @@ __device__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
   // msL = ms log2(e) rounded (the MsL of a wave holding the maximum), then
   // remove that rounding (shift_correction)
   const float msL = __fmul_rn(O.ms, LOG2E), mtL = __fmul_rn(O.mt, LOG2E);
+  // The double exponentials of the combination are evaluated side by side, one
+  // per lane: the factors 2^((1 - lm)(wMsL - msL) + lm (wMtL - mtL)) of the
+  // waves' middle-node sums (lanes 0 .. NW - 1), and 2^-d0 of the two shifts'
+  // roundings (shift_correction) and of the middle node's (lanes NW ..).
+  const double lm1 = static_cast<double>(1.0f - lm), lmd = static_cast<double>(lm);
+  const double d0s = static_cast<double>(LOG2E) * static_cast<double>(O.ms) - static_cast<double>(msL);
+  const double d0t = static_cast<double>(LOG2E) * static_cast<double>(O.mt) - static_cast<double>(mtL);
+  static_assert(NW + 3 <= WAVE, "one exponential per lane");
+  double ex = B.lane == NW ? -d0s : B.lane == NW + 1 ? -d0t : -(lm1 * d0s + lmd * d0t);
+  if (B.lane < NW)
+    ex = lm1 * (B.sh.red_d[B.lane][8] - static_cast<double>(msL)) +
+         lmd * (B.sh.red_d[B.lane][9] - static_cast<double>(mtL));
+  ex = exp2(ex);
   for (int w = 0; w < NW; ++w) {
     const float wMs = B.sh.red_f[w][0], wMt = B.sh.red_f[w][1];
     const float wMsL = static_cast<float>(B.sh.red_d[w][8]), wMtL = static_cast<float>(B.sh.red_d[w][9]);
@@ -640,17 +670,14 @@ __device__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
     for (int i = 0; i < 5; ++i) acc[i] += B.sh.red_d[w][i] * gs;
 #pragma unroll
     for (int i = 5; i < 8; ++i) acc[i] += B.sh.red_d[w][i] * gt;
-    // the middle node's sums are relative to 2^((1 - lm) wMsL + lm wMtL)
-    const double gm = (wMs == -finf() || wMt == -finf()) ? 0.0 :
-        exp2(static_cast<double>(1.0f - lm) * (static_cast<double>(wMsL) - static_cast<double>(msL)) +
-             static_cast<double>(lm) * (static_cast<double>(wMtL) - static_cast<double>(mtL)));
+    const double gm = (wMs == -finf() || wMt == -finf()) ? 0.0 : lane_d(ex, w);
 #pragma unroll
     for (int i = 0; i < 3; ++i) acc[8 + i] += B.sh.red_d[w][11 + i] * gm;
     const int wi = B.sh.red_i[w][0];
     if (wMt > tb || (wMt == tb && wi < ti)) { tb = wMt; ti = wi; }
     if (wMs == O.ms) st = fmaxf(st, static_cast<float>(B.sh.red_d[w][10]));
   }
-  const double cs = shift_correction(O.ms, msL), ct = shift_correction(O.mt, mtL);
+  const double cs = lane_d(ex, NW), ct = lane_d(ex, NW + 1), cm = lane_d(ex, NW + 2);
   // The maximum's own term went into the sums as 2^d0 rounded to float (d0 =
   // the rounding of the shift, ~1e-6: a rounding of ~6e-8 next to 1); after
   // the shift correction it is exactly 1.  The log-probability of a dominant
@@ -659,9 +686,8 @@ __device__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
   const double dom_t = 1.0 - static_cast<double>(fexp2(fmaf(O.mt, LOG2E, -mtL))) * ct;
   O.Ss = acc[0] * cs + dom_s; O.S1 = acc[1] * cs; O.S2 = acc[2] * cs; O.S3 = acc[3] * cs; O.S4 = acc[4] * cs;
   O.St = acc[5] * ct + dom_t; O.T1 = acc[6] * ct; O.T2 = acc[7] * ct;
-  // the middle node's weights carry cs^(1 - lm) ct^lm likewise
-  const double cm = exp2(static_cast<double>(1.0f - lm) * log2(cs) + static_cast<double>(lm) * log2(ct));
   O.Sm = acc[8] * cm; O.Q1 = acc[9] * cm; O.Q2 = acc[10] * cm;
+  O.cs = cs;
   O.lm = lm;
   O.tbest = tb;
   O.tidx = ti;
@@ -669,8 +695,11 @@ __device__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
   return O;
 }
 
-// Row statistics from the (combined) block statistics.
-__device__ inline RowStats row_stats_from(const StatsBlock& O, bool k34) {
+// Row statistics from the (combined) block statistics, on one wave.  The three
+// logarithms are taken side by side, one per lane, and the quotients by one
+// reciprocal per sum (the last bit of a double): the wave is alone here, and
+// its dependent double-precision steps are what every row waits for.
+__device__ __forceinline__ RowStats row_stats_from(const StatsBlock& O, bool k34, int lane) {
   RowStats R;
   R.ms = O.ms;
   R.mt = O.mt;
@@ -680,18 +709,24 @@ __device__ inline RowStats row_stats_from(const StatsBlock& O, bool k34) {
   R.vstar = O.tidx;
   R.t_smax = O.t_smax;
   R.sum_s = O.Ss;
-  R.lse_s = static_cast<double>(R.ms) + log(O.Ss);
-  R.lse_t = static_cast<double>(R.mt) + log(O.St);
-  const double Ed = O.S1 / O.Ss, E2 = O.S2 / O.Ss, E3 = O.S3 / O.Ss, E4 = O.S4 / O.Ss;
+  R.shift = O.cs;
+  const double ln = log(lane == 0 ? O.Ss : lane == 1 ? O.St : O.Sm);
+  const double ln_s = lane_d(ln, 0), ln_t = lane_d(ln, 1), ln_m = lane_d(ln, 2);
+  R.lse_s = static_cast<double>(R.ms) + ln_s;
+  R.lse_t = static_cast<double>(R.mt) + ln_t;
+  const double inv = 1.0 / (lane == 0 ? O.Ss : lane == 1 ? O.St : O.Sm);
+  const double is = lane_d(inv, 0), it = lane_d(inv, 1), im = lane_d(inv, 2);
+  const double Ed = O.S1 * is, E2 = O.S2 * is, E3 = O.S3 * is, E4 = O.S4 * is;
   R.var = fmax(E2 - Ed * Ed, 0.0);
   R.k34 = k34;
   R.k3 = k34 ? E3 - 3.0 * Ed * E2 + 2.0 * Ed * Ed * Ed : 0.0;
   R.k4 = k34 ? (E4 - 4.0 * Ed * E3 + 6.0 * Ed * Ed * E2 - 3.0 * Ed * Ed * Ed * Ed) - 3.0 * R.var * R.var : 0.0;
   R.mean_p = Ed;
-  R.mean_pi = O.T1 / O.St;
-  R.var_pi = fmax(O.T2 / O.St - R.mean_pi * R.mean_pi, 0.0);
+  R.mean_pi = O.T1 * it;
+  R.var_pi = fmax(O.T2 * it - R.mean_pi * R.mean_pi, 0.0);
   R.kl1_est = R.mean_pi - (R.lse_t - R.lse_s);
-  R.pmax = exp(static_cast<double>(R.ms) - R.lse_s);
+  R.pmax = is;  // exp(ms - lse_s)
+  R.inv_s = is;
   R.c = static_cast<float>(Ed);
   if (!isfinite(R.c)) R.c = 0.0f;
   R.cL = R.c * LOG2E;
@@ -700,10 +735,10 @@ __device__ inline RowStats row_stats_from(const StatsBlock& O, bool k34) {
   // derivatives are the mean and variance of x under the tilted weights
   {
     const double lm = static_cast<double>(O.lm);
-    const double M1 = O.Q1 / O.Sm, M2 = O.Q2 / O.Sm;
+    const double M1 = O.Q1 * im, M2 = O.Q2 * im;
     R.lam_mid = O.Sm > 0.0 ? O.lm : 0.0f;
     R.mid_A = lm * (static_cast<double>(R.mt) - static_cast<double>(R.ms) - static_cast<double>(R.c)) +
-              log(O.Sm) - log(O.Ss);
+              ln_m - ln_s;
     R.mid_A1 = M1 - static_cast<double>(R.c);
     R.mid_A2 = fmax(M2 - M1 * M1, 0.0);
   }
@@ -713,12 +748,14 @@ __device__ inline RowStats row_stats_from(const StatsBlock& O, bool k34) {
 }
 
 // keep_chunks: store the proposal chunk masses (of p); keep_teacher: those of pi.
-// The statistics are kept in the workgroup's LDS (thread 0 writes them): the
+// The statistics are kept in the workgroup's LDS (wave 0 writes them): the
 // caller reads its fields there where it needs them rather than holding the
-// whole record in registers across the later sweeps.
-template <typename T, int NT, bool MID = true, bool K34 = true, typename SH>
-__device__ const RowStats& stats_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, float lm,
-                                       bool keep_chunks, bool keep_teacher = false) {
+// whole record in registers across the later sweeps.  idle() runs on
+// the other waves while wave 0 combines the sums; the chunk masses are complete
+// then, the row statistics are not.
+template <typename T, int NT, bool MID = true, bool K34 = true, typename SH, typename Idle>
+__device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, float lm,
+                                       bool keep_chunks, bool keep_teacher, Idle&& idle) {
   constexpr int NW = NT / WAVE;
   StatsAcc a;
   a.init();
@@ -729,7 +766,12 @@ __device__ const RowStats& stats_sweep(Block<NT, SH>& B, const T* srow, const T*
                     }, row_cache<T>(B.sh));
   stats_post(B, a);
   __syncthreads();
-  if (B.tid == 0) B.sh.rs.r = row_stats_from(stats_combine(B, MID ? lm : 0.0f), K34);
+  if (B.wave == 0) {
+    const RowStats R = row_stats_from(stats_combine(B, MID ? lm : 0.0f), K34, B.lane);
+    if (B.lane == 0) B.sh.rs.r = R;
+  } else {
+    idle();
+  }
   __syncthreads();
   return B.sh.rs.r;
 }
@@ -834,7 +876,7 @@ __device__ __forceinline__ void lam_math(const float* s, const float* t, uint32_
 // A and its derivatives at lam from the row sums v = {W, S1..S4} (log2
 // units) and b0 = sum p~.  acc: W = sum (w - p~), scaled by 2^-sigl when
 // sigl != 0; otherwise W = sum w when sigl != 0.
-__device__ inline LamEval lam_finish(const double (&v)[5], double b0, float lam, float sigl, bool acc) {
+__device__ __forceinline__ LamEval lam_finish(const double (&v)[5], double b0, float lam, float sigl, bool acc) {
   LamEval E;
   E.lam = lam;
   double S0, r = 1.0;
@@ -888,7 +930,7 @@ __device__ __forceinline__ double dominant_fix(float s, float t, float msL, floa
 }
 
 template <typename T, int NT, int MODE, typename SH>
-__device__ LamEval lam_sweep_mode(Block<NT, SH>& B, const T* srow, const T* trow, int V, const RowStats& R,
+__device__ __forceinline__ LamEval lam_sweep_mode(Block<NT, SH>& B, const T* srow, const T* trow, int V, const RowStats& R,
                                   float lam, float sigl, bool accf) {
   constexpr int NW = NT / WAVE;
   double v[5] = {0, 0, 0, 0, 0};
@@ -900,7 +942,7 @@ __device__ LamEval lam_sweep_mode(Block<NT, SH>& B, const T* srow, const T* trow
                     }, row_cache<T>(B.sh));
   B.sum(v);
   if constexpr (MODE == LAM_FAST) v[0] += dominant_fix(R.ms, R.t_smax, msL, R.cL, lam);
-  const double corr = shift_correction(R.ms, msL);
+  const double corr = R.shift;
 #pragma unroll
   for (int j = 0; j < 5; ++j) v[j] *= corr;
   return lam_finish(v, R.sum_s, lam, sigl, accf);
@@ -911,7 +953,7 @@ __device__ LamEval lam_sweep_mode(Block<NT, SH>& B, const T* srow, const T* trow
 // exponents are shifted by sigl so that lam x - sig <= 60 for every entry.
 // Every thread gets the same result.
 template <typename T, int NT, typename SH>
-__device__ LamEval lam_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, const RowStats& R,
+__device__ __forceinline__ LamEval lam_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, const RowStats& R,
                              float lam, bool acc) {
   const double top = static_cast<double>(lam) * (static_cast<double>(R.dmax) - R.c);  // largest lam x
   const float sigl = top <= 60.0 ? 0.0f : static_cast<float>((top - 60.0) * static_cast<double>(LOG2E));
@@ -950,12 +992,12 @@ struct LamResult {
   bool acc;    // A and KL come from a sweep in the expm1 form
   int sweeps;  // lambda sweeps the search ran
   // x of one entry exactly as the sweeps see it: X ln 2, X = fma(d, log2 e, -cL)
-  __device__ double x_of(float s, float t) const {
+  __device__ __forceinline__ double x_of(float s, float t) const {
     return (static_cast<double>(LOG2E) * (static_cast<double>(t) - static_cast<double>(s)) -
             static_cast<double>(cL)) * LN2_D;
   }
   // log q(v) - log p(v) = lam x_v - A (exactly 0 when q = p)
-  __device__ double log_ratio(float s, float t) const {
+  __device__ __forceinline__ double log_ratio(float s, float t) const {
     return qp ? 0.0 : static_cast<double>(lam) * x_of(s, t) - A;
   }
 };
@@ -964,17 +1006,17 @@ struct LamResult {
 // and KL(l) = l A'(l) - A(l) on it.
 struct TaylorA {
   LamEval n;
-  __device__ void eval(double l, double& A, double& Ap) const {
+  __device__ __forceinline__ void eval(double l, double& A, double& Ap) const {
     const double d = l - n.lam;
     A = n.A + d * (n.A1 + d * (0.5 * n.A2 + d * (n.A3 / 6.0 + d * (n.A4 / 24.0))));
     Ap = n.A1 + d * (n.A2 + d * (0.5 * n.A3 + d * (n.A4 / 6.0)));
   }
-  __device__ double kl(double l) const {
+  __device__ __forceinline__ double kl(double l) const {
     double A, Ap;
     eval(l, A, Ap);
     return l * Ap - A;
   }
-  __device__ bool usable() const {
+  __device__ __forceinline__ bool usable() const {
     return isfinite(n.A) && isfinite(n.A1) && isfinite(n.A2) && isfinite(n.A3) && isfinite(n.A4);
   }
 };
@@ -985,7 +1027,7 @@ struct TaylorA {
 // with A(0) = 0, A^(k)(0) = kappa_k (k = 1..4, of x = d - c under p) and
 // A(1) = lse_t - lse_s - c, A'(1) = E_pi[x], A''(1) = Var_pi(x) at the teacher
 // end; KL = eps is solved on it by bisection.
-__device__ inline double cumulant_start(const RowStats& R, double eps) {
+__device__ __forceinline__ double cumulant_start(const RowStats& R, double eps) {
   if (!(R.var > 0)) return 0.5;
   const double l2 = sqrt(2.0 * eps / R.var);
   double l = l2;
@@ -1002,7 +1044,7 @@ __device__ inline double cumulant_start(const RowStats& R, double eps) {
   return l;
 }
 
-__device__ inline double two_ended_start(const RowStats& R, double eps) {
+__device__ __forceinline__ double two_ended_start(const RowStats& R, double eps) {
   double c[8];
   c[0] = 0.0;
   c[1] = R.mean_p - R.c;
@@ -1042,7 +1084,7 @@ template <int N0>  // conditions at lambda = 0: 5 with k3, k4, else 3
 struct HermiteA {
   static constexpr int N = N0 + 6;
   double z[N], c[N];
-  __device__ explicit HermiteA(const RowStats& R) {
+  __device__ __forceinline__ explicit HermiteA(const RowStats& R) {
     const double lm = static_cast<double>(R.lam_mid);
     const double f0[5] = {0.0, R.mean_p - R.c, R.var, R.k3, R.k4};
     const double fm[3] = {R.mid_A, R.mid_A1, R.mid_A2};
@@ -1069,7 +1111,7 @@ struct HermiteA {
       }
   }
   // the polynomial and its first two derivatives at l
-  __device__ void eval(double l, double& p, double& p1, double& p2) const {
+  __device__ __forceinline__ void eval(double l, double& p, double& p1, double& p2) const {
     p = c[N - 1];
     p1 = 0.0;
     p2 = 0.0;
@@ -1097,7 +1139,7 @@ constexpr double LAM_MAX = 1.0 - 1e-6;
 // found, lies on the wrong side of the middle node, or the interpolant is not
 // convex there).
 template <int N0>
-__device__ inline void hermite_refine(const RowStats& R, double eps, double l0, StartPoint& S) {
+__device__ __forceinline__ void hermite_refine(const RowStats& R, double eps, double l0, StartPoint& S) {
   const HermiteA<N0> H(R);
   double p, p1, p2;
   H.eval(1.0, p, p1, p2);
@@ -1114,7 +1156,8 @@ __device__ inline void hermite_refine(const RowStats& R, double eps, double l0, 
   // keeping the bracket KL(lo) <= eps < KL(hi)
   // (converged once the step is below 1e-10 of lambda: the interpolant's own
   // rounding, ~1e-12 of lambda near the root, would otherwise send a
-  // tighter test into the bisection branch)
+  // tighter test into the bisection branch; the step's quotient by the
+  // hardware reciprocal, ~1e-8 of it, does not slow the convergence)
   double lo = blo, hi = bhi;
   // the search starts from l0, moved inside the bracket when outside it (to
   // its nearer end, so that Newton does not start among the interpolant's
@@ -1126,9 +1169,9 @@ __device__ inline void hermite_refine(const RowStats& R, double eps, double l0, 
     const double f = l * p1 - p - eps;
     if (f <= 0.0) lo = l; else hi = l;
     const double fp = l * p2;
-    const double step = (fp > 0.0) ? -f / fp : __builtin_huge_val();
+    const double step = (fp > 0.0) ? -f * __builtin_amdgcn_rcp(fp) : __builtin_huge_val();
     if (fabs(step) <= 1e-10 * l || hi - lo <= 1e-8 * l) {
-      conv = true;
+      conv = true;  // p and p2 are the interpolant's at l
       break;
     }
     double nl = l + step;
@@ -1136,27 +1179,36 @@ __device__ inline void hermite_refine(const RowStats& R, double eps, double l0, 
     l = nl;
   }
   if (!conv || !(l > blo && l < bhi) || !(l < LAM_MAX)) return;
-  H.eval(l, p, p1, p2);
   if (!(p2 > 0.0) || !isfinite(p)) return;
   S.lam = l;
   S.A = p;
   S.herm = true;
 }
 
-__device__ inline StartPoint start_point(const RowStats& R, double eps) {
+__device__ __forceinline__ StartPoint start_point(const RowStats& R, double eps) {
+  StartPoint S;
+  S.herm = false;
+  if (R.lam_mid > 0.0f) {
+    // the interpolant's search is seeded by the power law KL ~ lambda^n through
+    // KL and its derivative at the middle node (n = lambda KL' / KL): it starts
+    // within a few percent, so the ends' starts below (twenty Newton and
+    // fourteen bisection steps) are left to the rows without a usable interpolant
+    const double lm = static_cast<double>(R.lam_mid);
+    const double klm = lm * R.mid_A1 - R.mid_A;
+    const float n = static_cast<float>(lm * lm * R.mid_A2) / static_cast<float>(klm);
+    const float l0 = R.lam_mid * fexp2(flog2(static_cast<float>(eps / klm)) / fminf(fmaxf(n, 1.0f), 4.0f));
+    const double seed = (l0 > 0.0f && l0 < 1.0f) ? static_cast<double>(l0) : lm;
+    if (R.k34)
+      hermite_refine<5>(R, eps, seed, S);
+    else
+      hermite_refine<3>(R, eps, seed, S);
+    if (S.herm) return S;
+  }
   const double l_cum = cumulant_start(R, eps);
   const double l_two = two_ended_start(R, eps);
-  double l0 = (l_two > 0.0 && fabs(l_two - l_cum) <= 0.3 * l_cum) ? l_two : l_cum;
-  l0 = fmin(fmax(l0, 1e-7), LAM_MAX);
-  StartPoint S;
-  S.lam = l0;
+  const double l0 = (l_two > 0.0 && fabs(l_two - l_cum) <= 0.3 * l_cum) ? l_two : l_cum;
+  S.lam = fmin(fmax(l0, 1e-7), LAM_MAX);
   S.A = 0.0;
-  S.herm = false;
-  if (!(R.lam_mid > 0.0f)) return S;
-  if (R.k34)
-    hermite_refine<5>(R, eps, l0, S);
-  else
-    hermite_refine<3>(R, eps, l0, S);
   return S;
 }
 
@@ -1169,16 +1221,17 @@ __device__ inline StartPoint start_point(const RowStats& R, double eps) {
 // otherwise the next node is that root (or the edge of the trust interval).
 // sweep1(lam, acc) evaluates one node over the whole row.
 // force_acc: every sweep in the expm1 form; lam_hint > 0: the first node (a
-// lambda* found before, resolved again in the accurate form); first: the
-// first node already evaluated (by the fused sweep, at first->lam; in the
-// expm1 form if first_acc), used in place of the first sweep.  out.sweeps
+// lambda* found before, resolved again in the accurate form); first (with
+// given_first): the first node already evaluated (by the fused sweep, at
+// first.lam; in the expm1 form if first_acc), used in place of the first sweep.  out.sweeps
 // counts the sweeps run here.
 // no_sweep: stop where a sweep would be needed (out.sweeps = -1), so that one
 // wave can settle the common case of an accepted first node alone.
 template <typename Sweep1>
-__device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& sweep1, bool force_acc = false,
-                                        float lam_hint = 0.0f, const LamEval* first = nullptr,
-                                        bool first_acc = false, bool no_sweep = false) {
+__device__ __forceinline__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& sweep1, bool force_acc = false,
+                                        float lam_hint = 0.0f, bool given_first = false,
+                                        LamEval first = LamEval{}, bool first_acc = false,
+                                        bool no_sweep = false) {
   LamResult out;
   out.acc = true;
   out.sweeps = 0;
@@ -1197,7 +1250,7 @@ __device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& 
   // A KL below KL_ACCURATE is resolved with the expm1 form of the sweep: the
   // plain form carries ~2^-24 absolute error per weight, too much next to a
   // KL of that size.
-  bool acc = force_acc || eps < KL_ACCURATE || (first != nullptr && first_acc);
+  bool acc = force_acc || eps < KL_ACCURATE || (given_first && first_acc);
   out.acc = acc;
   constexpr double TAYLOR_TOL = 1e-7;
   constexpr double TRUST = 0.3;
@@ -1205,14 +1258,14 @@ __device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& 
   double lo = 0.0, hi = 1.0;  // KL(lo) <= eps < KL(hi) (hi = 1 until a node above is seen)
   LamEval feas;               // the largest evaluated lambda that is feasible (lambda = 0 is)
   feas.lam = 0.0; feas.A = 0.0; feas.KL = 0.0;
-  double lg = (first == nullptr && !(lam_hint > 0.0f)) ? start_point(R, eps).lam : 0.0;
+  double lg = (!given_first && !(lam_hint > 0.0f)) ? start_point(R, eps).lam : 0.0;
   bool try_one = R.kl1_est <= 1.05 * eps + 1e-5;
   if (lam_hint > 0.0f) {
     lg = lam_hint;
     try_one = lam_hint == 1.0f;
   }
-  if (first != nullptr) {
-    lg = first->lam;
+  if (given_first) {
+    lg = first.lam;
     try_one = false;
   }
   // The first TRUST_SWEEPS sweeps step within TRUST of the node.  A row still
@@ -1225,12 +1278,12 @@ __device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& 
   double step1 = 2.0, step2 = 2.0;  // the last two node steps (safeguard)
   for (int sweep = 0; sweep < MAX_SWEEPS; ++sweep) {
     const float lf = try_one ? 1.0f : static_cast<float>(lg);
-    const bool given = sweep == 0 && first != nullptr;
+    const bool given = sweep == 0 && given_first;
     if (!given && no_sweep) {
       out.sweeps = -1;
       return out;
     }
-    const LamEval E = given ? *first : sweep1(lf, acc);
+    const LamEval E = given ? first : sweep1(lf, acc);
     if (!given) ++out.sweeps;
     if (lf == 1.0f && E.KL <= eps) {
       if (!acc && E.KL < KL_ACCURATE) {
@@ -1276,7 +1329,8 @@ __device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& 
         if (f < 0.0) xa = l; else xb = l;
         const double dd = l - E.lam;
         const double fp = l * (E.A2 + dd * (E.A3 + dd * (0.5 * E.A4)));  // l A''
-        double nl = (fp > 0.0) ? l - f / fp : 0.5 * (xa + xb);
+        // (the hardware reciprocal, ~1e-8 of the step, costs no extra iteration)
+        double nl = (fp > 0.0) ? l - f * __builtin_amdgcn_rcp(fp) : 0.5 * (xa + xb);
         if (!(nl > xa && nl < xb)) nl = 0.5 * (xa + xb);
         const bool done = fabs(nl - l) <= 1e-14 * l || (xb - xa) <= 1e-14 * l;
         l = nl;
@@ -1324,7 +1378,7 @@ __device__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& 
 }
 
 template <typename T, int NT, typename SH>
-__device__ LamResult lambda_search(Block<NT, SH>& B, const T* srow, const T* trow, int V,
+__device__ __forceinline__ LamResult lambda_search(Block<NT, SH>& B, const T* srow, const T* trow, int V,
                                    const RowStats& R, double eps, bool force_acc = false, float lam_hint = 0.0f) {
   return lambda_search_with(R, eps, [&](float lam, bool acc) {
     return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc);
@@ -1333,12 +1387,13 @@ __device__ LamResult lambda_search(Block<NT, SH>& B, const T* srow, const T* tro
 
 // A row resolved in a plain form whose TV is too small for that form's
 // rounding (TV_PLAIN_MIN) is resolved again in the expm1 forms.
-__device__ inline bool redo_accurate(const RowStats& R, const LamResult& L, bool final_acc, double TV) {
+__device__ __forceinline__ bool redo_accurate(const RowStats& R, const LamResult& L, bool final_acc, double TV) {
   if (L.qp || (L.acc && final_acc)) return false;
   const double rest = 1.0 - R.pmax;
-  const double lam_err = L.acc ? 0.0 : sqrt(fmax(fmin(R.pmax, rest) * rest, 0.0));
-  const double fin_err = final_acc ? 0.0 : sqrt(R.pmax);
-  return TV < TV_PLAIN_MIN * fmax(lam_err, fin_err);
+  // the squares of the two bounds
+  const double lam_err = L.acc ? 0.0 : fmax(fmin(R.pmax, rest) * rest, 0.0);
+  const double fin_err = final_acc ? 0.0 : R.pmax;
+  return TV * TV < TV_PLAIN_MIN * TV_PLAIN_MIN * fmax(lam_err, fin_err);
 }
 
 // ---------------------------------------------------------------------------
@@ -1358,11 +1413,11 @@ struct FinalConst {
 // q/p would overflow), the FIN_FAST / FIN_ACC form (by F.acc) elsewhere.
 enum FinMode { FIN_FAST = 0, FIN_ACC = 1, FIN_WIDE = 2 };
 
-__device__ inline FinalConst final_const(const RowStats& R, const LamResult& L, bool force_acc = false) {
+__device__ __forceinline__ FinalConst final_const(const RowStats& R, const LamResult& L, bool force_acc = false) {
   FinalConst F;
   F.msL = R.ms * LOG2E;
   // p = 2^{fma(s, log2 e, -msL)} * invS: the shift's rounding is folded into invS
-  F.invS = static_cast<float>(shift_correction(R.ms, F.msL) / R.sum_s);
+  F.invS = static_cast<float>(R.shift * R.inv_s);
   F.cL = L.cL;
   F.lam = L.qp ? 0.0f : L.lam;
   F.AL = L.qp ? 0.0f : static_cast<float>(L.A * static_cast<double>(LOG2E));
@@ -1445,7 +1500,7 @@ __device__ __forceinline__ double final_sweep(Block<NT, SH>& B, const T* srow, c
 // row with non-finite logits, exact zeros at a masked row whatever its
 // logits); the logits are not read.
 template <typename G, int NT>
-__device__ void fill_row(int wave, int lane, G* grow, int V, float value) {
+__device__ __forceinline__ void fill_row(int wave, int lane, G* grow, int V, float value) {
   constexpr int NW = NT / WAVE;
   const int nchunks = (V + CHUNK - 1) / CHUNK;
   const bool ragged = (V % CHUNK) != 0;
@@ -1462,7 +1517,7 @@ __device__ void fill_row(int wave, int lane, G* grow, int V, float value) {
 
 // The final sweep in the form F selects.
 template <typename T, typename G, int NT, bool GRAD, typename SH>
-__device__ double final_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
+__device__ __forceinline__ double final_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                   const FinalConst& F, bool keep_res, float coef, int hot, float s_hot) {
   if (F.wide) return final_sweep<T, G, NT, GRAD, FIN_WIDE>(B, srow, trow, grow, V, F, keep_res, coef, hot, s_hot);
   if (F.acc) return final_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, F, keep_res, coef, hot, s_hot);
@@ -1508,15 +1563,19 @@ struct FusedConst {
   // the node and centring these float constants give exactly: with
   // X = (t - s) log2 e - cL, y = lam_e X - AL_e (the roundings of kL and K
   // are shared by every entry, so they are taken out here, not bounded)
-  double lam_e, AL_e;
-  __device__ void set_y() {
+  double lam_e, AL_e, inv_lam;  // on the wave that settles the row (set_node)
+  __device__ __forceinline__ void set_y() {
     kL = lam * LOG2E;
     K = fmaf(lam, cL, AL);
-    lam_e = static_cast<double>(kL) / static_cast<double>(LOG2E);
+  }
+  __device__ __forceinline__ void set_node() {
+    lam_e = static_cast<double>(kL) * (1.0 / static_cast<double>(LOG2E));
     AL_e = static_cast<double>(K) - lam_e * static_cast<double>(cL);
+    inv_lam = 1.0 / lam_e;
   }
 };
 
+// Valid on wave 0, which alone settles the row.
 struct FusedSums {
   double v[4];   // W, S1, S2, S3 (moments of y, relative to 2^AL)
   double T0, U0, U1, Bd;
@@ -1581,7 +1640,7 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
   }
   double v[8] = {acc[0], acc[1], acc[2], acc[3], acc[4], static_cast<double>(U0), static_cast<double>(U1),
                  static_cast<double>(Bd)};
-  B.sum(v);
+  B.sum_wave0(v);
   FusedSums S;
 #pragma unroll
   for (int i = 0; i < 4; ++i) S.v[i] = v[i];
@@ -1593,7 +1652,7 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
 }
 
 template <typename T, typename G, int NT, bool GRAD, typename SH>
-__device__ FusedSums fused_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
+__device__ __forceinline__ FusedSums fused_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                      const FusedConst& C, bool acc, bool keep_res, float coef, float invS, int hot,
                                      float s_hot) {
   if (acc) return fused_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot);
@@ -1603,14 +1662,17 @@ __device__ FusedSums fused_sweep_any(Block<NT, SH>& B, const T* srow, const T* t
 // The dominant entry's term of the fused sweep's W in the plain form: its
 // float value as the sweep computes it and its value in double (as
 // dominant_fix does for the lambda sweep); the difference corrects W.
-__device__ inline double dominant_fix_fused(float s, float t, const FusedConst& C) {
+__device__ __forceinline__ double dominant_fix_fused(float s, float t, const FusedConst& C) {
   const float a = fmaf(s, LOG2E, -C.msL);
   const float y = fmaf(t - s, C.kL, -C.K);
   const float pt = fexp2(a);
   const float rf = fmaf(pt, fexp2(y), -pt);
   const double yd = (static_cast<double>(C.kL) * (static_cast<double>(t) - static_cast<double>(s)) -
                      static_cast<double>(C.K)) * LN2_D;
-  return exp2(static_cast<double>(a)) * expm1(yd) - static_cast<double>(rf);
+  // |a| ~ 1e-6 (the shift's rounding at an entry holding the maximum): 2^a by
+  // its quadratic, as in dominant_fix
+  const double al = static_cast<double>(a) * LN2_D;
+  return (1.0 + al * (1.0 + 0.5 * al)) * expm1(yd) - static_cast<double>(rf);
 }
 
 // The lambda node of the fused sums: sum_v p~ 2^{lam X} = 2^AL (sum p~ + W).
@@ -1621,20 +1683,20 @@ __device__ inline double dominant_fix_fused(float s, float t, const FusedConst& 
 // whose node only settles lambda* = 1).
 // acc: the sweep took the expm1 form (else the dominant entry's term of W is
 // taken exactly).
-__device__ inline LamEval fused_node(const RowStats& R, const FusedSums& S, const FusedConst& C, bool end_first,
+__device__ __forceinline__ LamEval fused_node(const RowStats& R, const FusedSums& S, const FusedConst& C, bool end_first,
                                      bool acc) {
-  const float msL = R.ms * LOG2E;
-  const double corr = shift_correction(R.ms, msL);
+  const double corr = R.shift;
   const double w = (S.v[0] + (acc ? 0.0 : dominant_fix_fused(R.ms, R.t_smax, C))) * corr;
   const double S0 = R.sum_s + w;
   // moments of y under q_lam, then those of X = (y + AL) / lam; x = X ln 2
-  const double m1 = S.v[1] * corr / S0, m2 = S.v[2] * corr / S0, m3 = S.v[3] * corr / S0;
+  const double r0 = corr / S0;
+  const double m1 = S.v[1] * r0, m2 = S.v[2] * r0, m3 = S.v[3] * r0;
   const double c2 = fmax(m2 - m1 * m1, 0.0);
   const double c3 = m3 - 3.0 * m1 * m2 + 2.0 * m1 * m1 * m1;
-  const double lam = C.lam_e, il = LN2_D / lam;
+  const double il = LN2_D * C.inv_lam;
   LamEval E;
-  E.lam = lam;
-  const double lw = log1p(w / R.sum_s);
+  E.lam = C.lam_e;
+  const double lw = log1p(w * R.inv_s);
   E.A = C.AL_e * LN2_D + lw;
   E.A1 = (m1 + C.AL_e) * il;
   E.A2 = c2 * il * il;
@@ -1660,7 +1722,7 @@ struct FusedFinal {
 // acc: the sweep took the expm1 form, where each r carries ~1e-7 of itself as
 // rounding; in the plain form each carries ~6e-8 of p~ e instead, which over
 // P sums to as much as 1e-7 U0.
-__device__ inline FusedFinal fused_tv(const RowStats& R, const LamResult& L, const FinalConst& F,
+__device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResult& L, const FinalConst& F,
                                       const FusedConst& C, const FusedSums& S, bool acc) {
   FusedFinal out;
   out.ok = false;
@@ -1671,17 +1733,17 @@ __device__ inline FusedFinal fused_tv(const RowStats& R, const LamResult& L, con
   out.why = 2;
   const double dl = static_cast<double>(F.lam) - C.lam_e;
   const double dA = static_cast<double>(F.AL) - C.AL_e;
-  const double lg = C.lam_e;
   // |X| over the row (X = d log2 e - cL), with a margin for its rounding
   const double xa = fmax(fabs(static_cast<double>(R.dmax) * LOG2E - C.cL),
                          fabs(static_cast<double>(R.dmin) * LOG2E - C.cL)) * (1.0 + 1e-6) + 1e-6;
   const double hmax = fabs(dl) * xa + fabs(dA);
   // an entry's exponent moves by h = rho y + H0 (X = (y + AL) / lam_g): its
-  // sign changes only where |y| <= |H0| / (1 - |rho|) (plus the rounding of y)
-  const double rho = dl / lg;
-  const double H0 = dl * C.AL_e / lg - dA;
+  // sign changes only where |y| <= |H0| / (1 - |rho|) (plus the rounding of y);
+  // 1 / (1 - x) <= 1 + 2 x for x <= 1/2
+  const double rho = dl * C.inv_lam;
+  const double H0 = rho * C.AL_e - dA;
   if (!(fabs(rho) < 0.5)) return out;
-  const double Hf = fabs(H0) / (1.0 - fabs(rho)) + 1e-7;
+  const double Hf = fabs(H0) * (1.0 + 2.0 * fabs(rho)) + 1e-7;
   if (!(Hf < static_cast<double>(FUSED_BAND)) || !(hmax < 0.01)) return out;
   out.why = 3;
   // such an entry's residual at lambda* is below p~ e (2^Hf - 1) on either side
@@ -1696,7 +1758,7 @@ __device__ inline FusedFinal fused_tv(const RowStats& R, const LamResult& L, con
   if (!(tvu > 0.0) || !(err <= FUSED_TV_TOL * tvu)) return out;
   out.ok = true;
   out.why = 0;
-  out.TV = tvu * shift_correction(R.ms, C.msL) / R.sum_s;
+  out.TV = tvu * (R.shift * R.inv_s);
   out.hmax = hmax;
   out.flip = flip;
   return out;
@@ -1712,44 +1774,84 @@ struct RowPlan {
   int fused;   // the row takes the fused sweep
   int state;   // after it: 1 settled, 0 final sweep after all, -1 the search needs sweeps
   int C;       // the accept decision at lambda* (state >= 0)
-  int z;       // the proposal, and its s and t (wave_proposal)
+  int redo;    // the plain forms are too coarse for the row's TV (state 1)
+  double alpha;  // exp(min(0, log q(z) - log p(z))) at lambda* (state >= 0)
+  LamEval E0;  // the fused sweep's node (state < 0)
+  int z;       // the proposal, and its s and t
   float sz, tz;
 };
 
-// The chunk level of the residual race from masses known within bounds
-// (mass_bound(c, m, b): |true mass - m| <= b, m >= 0): the winner by the
-// masses m, or -1 when a chunk could still beat it within the bounds (the
-// caller then takes the final sweep).  Keys and ties as in chunk_race.
-template <int NT, typename SH, typename F>
-__device__ int chunk_race_certain(Block<NT, SH>& B, int nchunks, uint64_t seed, uint32_t stream, uint64_t g,
-                                  F mass_bound) {
-  double best = __builtin_huge_val();
+// The chunk level of the residual race from masses known within bounds, in two
+// halves.  res_race_begin, on waves 1 .. NW - 1 while wave 0 settles the row:
+// the winner by the masses at the node (sh.chunk_a), chunk c on wave
+// 1 + (c / WAVE) % (NW - 1); ln E of a lane's first chunk is kept.
+// res_race_end, on every wave once the masses' bounds are known (|true mass - m|
+// <= b, b = hb sh.chunk_b[c] + flip): that winner, or -1 when a chunk could
+// still beat it within the bounds (the caller then takes the final sweep).
+// Keys and ties as in chunk_race.
+__device__ __forceinline__ double ln_exp_race(uint64_t seed, uint32_t stream, uint64_t g, int c) {
+  return log(-log(static_cast<double>(philox_uniform(seed, stream, g, static_cast<uint32_t>(c)))));
+}
+
+template <int NT, typename SH>
+__device__ __forceinline__ double res_race_begin(Block<NT, SH>& B, int nchunks, uint64_t seed, uint64_t g) {
+  const int first = (B.wave - 1) * WAVE + B.lane;
+  double le0 = 0.0, best = __builtin_huge_val();
   int bi = 0x7fffffff;
-  // ln E of this thread's first chunk, kept for the second pass
-  auto ln_e = [&](int c) {
-    return log(-log(static_cast<double>(philox_uniform(seed, stream, g, static_cast<uint32_t>(c)))));
-  };
-  const double le0 = B.tid < nchunks ? ln_e(B.tid) : 0.0;
-  for (int c = B.tid; c < nchunks; c += NT) {
-    double m, b;
-    mass_bound(c, m, b);
-    if (m > 0.0) {
-      const double key = (c == B.tid ? le0 : ln_e(c)) - log(m);
+  for (int c = first; c < nchunks; c += (SH::NW - 1) * WAVE) {
+    const double le = ln_exp_race(seed, RES_CHUNK, g, c);
+    if (c == first) le0 = le;
+    const float m = B.sh.chunk_a[c];
+    if (m > 0.0f) {
+      const double key = le - log(static_cast<double>(m));
       if (key < best) { best = key; bi = c; }
     }
   }
-  B.argmin(best, bi);
+  wave_argmin(best, bi);
+  if (B.lane == 0) {
+    B.sh.race_key[B.wave] = best;
+    B.sh.race_idx[B.wave] = bi;
+  }
+  return le0;
+}
+
+// The best chunk of the waves' shares (posted by waves 1 .. NW - 1).
+template <typename SH>
+__device__ __forceinline__ int race_winner(const SH& sh) {
+  double bk = sh.race_key[1];
+  int bi = sh.race_idx[1];
+#pragma unroll
+  for (int w = 2; w < SH::NW; ++w) {
+    const double k = sh.race_key[w];
+    const int i = sh.race_idx[w];
+    if (k < bk || (k == bk && i < bi)) { bk = k; bi = i; }
+  }
+  return bi;
+}
+
+template <int NT, typename SH>
+__device__ __forceinline__ int res_race_end(Block<NT, SH>& B, int nchunks, uint64_t seed, uint64_t g, double le0, double hb,
+                            double flip) {
+  const int bi = race_winner(B.sh);
   if (bi >= nchunks) return -1;
+  auto mass = [&](int c, double& m, double& b) {
+    m = fmax(static_cast<double>(B.sh.chunk_a[c]), 0.0);
+    b = hb * static_cast<double>(B.sh.chunk_b[c]) + flip;
+  };
   double mw, bw;
-  mass_bound(bi, mw, bw);
-  if (!(mw - bw > 0.0)) return -1;
-  const double key_hi = ln_e(bi) - log(mw - bw);
+  mass(bi, mw, bw);
   float amb = 0.0f;
-  for (int c = B.tid; c < nchunks; c += NT) {
-    if (c == bi) continue;
-    double m, b;
-    mass_bound(c, m, b);
-    if (m + b > 0.0 && (c == B.tid ? le0 : ln_e(c)) - log(m + b) <= key_hi) amb = 1.0f;
+  if (!(mw - bw > 0.0)) {
+    amb = 1.0f;
+  } else if (B.wave > 0) {
+    const double key_hi = ln_exp_race(seed, RES_CHUNK, g, bi) - log(mw - bw);
+    const int first = (B.wave - 1) * WAVE + B.lane;
+    for (int c = first; c < nchunks; c += (SH::NW - 1) * WAVE) {
+      if (c == bi) continue;
+      double m, b;
+      mass(c, m, b);
+      if (m + b > 0.0 && (c == first ? le0 : ln_exp_race(seed, RES_CHUNK, g, c)) - log(m + b) <= key_hi) amb = 1.0f;
+    }
   }
   return B.max(amb) > 0.0f ? -1 : bi;
 }
@@ -1762,7 +1864,7 @@ __device__ int chunk_race_certain(Block<NT, SH>& B, int nchunks, uint64_t seed, 
 // that lse = msL ln 2 + ln S and p_v = 2^(s_v log2 e - msL) / S, the form the
 // gradient sweep evaluates.
 template <typename T, int NT, typename SH>
-__device__ double lse_sweep(Block<NT, SH>& B, const T* srow, int V, float* msL_out) {
+__device__ __forceinline__ double lse_sweep(Block<NT, SH>& B, const T* srow, int V, float* msL_out) {
   constexpr int NW = NT / WAVE;
   float Ms = -finf(), MsL = -finf();
   double Ss = 0.0;
@@ -1807,7 +1909,7 @@ __device__ double lse_sweep(Block<NT, SH>& B, const T* srow, int V, float* msL_o
 // that stored it, as in the final sweep; a row flagged nan_row is all NaN and
 // a row with coef = 0 all zeros.
 template <typename T, typename G, int NT, typename SH>
-__device__ void route_grad_sweep(Block<NT, SH>& B, const T* srow, G* grow, int V, float msL, float invS,
+__device__ __forceinline__ void route_grad_sweep(Block<NT, SH>& B, const T* srow, G* grow, int V, float msL, float invS,
                                  float coef, int hot, float s_hot, bool nan_row) {
   constexpr int NW = NT / WAVE;
   if (!nan_row && coef == 0.0f) {
@@ -1842,7 +1944,7 @@ __device__ void route_grad_sweep(Block<NT, SH>& B, const T* srow, G* grow, int V
 // Chunk level.  logw(c) returns ln W_c up to a row constant, or -inf.  One
 // chunk per thread: the double-precision logs dominate, not the Philox block.
 template <int NT, typename SH, typename F>
-__device__ int chunk_race(Block<NT, SH>& B, int nchunks, uint64_t seed, uint32_t stream, uint64_t g,
+__device__ __forceinline__ int chunk_race(Block<NT, SH>& B, int nchunks, uint64_t seed, uint32_t stream, uint64_t g,
                           F logw) {
   double best = __builtin_huge_val();
   int bi = 0x7fffffff;
@@ -1860,7 +1962,7 @@ __device__ int chunk_race(Block<NT, SH>& B, int nchunks, uint64_t seed, uint32_t
 
 // Entry level inside chunk c.  logw(v) returns ln w_v up to a row constant, or -inf.
 template <int NT, typename SH, typename F>
-__device__ int elem_race(Block<NT, SH>& B, int c, int V, uint64_t seed, uint32_t stream, uint64_t g,
+__device__ __forceinline__ int elem_race(Block<NT, SH>& B, int c, int V, uint64_t seed, uint32_t stream, uint64_t g,
                          F logw) {
   float best = finf();
   int bi = 0x7fffffff;
@@ -1901,11 +2003,11 @@ template <>
 struct ElemFetch<uint16_t> {
   uint2 qs, qt;
   int v0;  // first of this thread's entries
-  __device__ float s(int k) const {
+  __device__ __forceinline__ float s(int k) const {
     const uint32_t w = (k < 2) ? qs.x : qs.y;
     return __uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
   }
-  __device__ float t(int k) const {
+  __device__ __forceinline__ float t(int k) const {
     const uint32_t w = (k < 2) ? qt.x : qt.y;
     return __uint_as_float((k & 1) ? (w & 0xffff0000u) : (w << 16));
   }
@@ -1914,8 +2016,8 @@ template <>
 struct ElemFetch<float> {
   float4 qs, qt;
   int v0;
-  __device__ float s(int k) const { return k == 0 ? qs.x : k == 1 ? qs.y : k == 2 ? qs.z : qs.w; }
-  __device__ float t(int k) const { return k == 0 ? qt.x : k == 1 ? qt.y : k == 2 ? qt.z : qt.w; }
+  __device__ __forceinline__ float s(int k) const { return k == 0 ? qs.x : k == 1 ? qs.y : k == 2 ? qs.z : qs.w; }
+  __device__ __forceinline__ float t(int k) const { return k == 0 ? qt.x : k == 1 ? qt.y : k == 2 ? qt.z : qt.w; }
 };
 
 template <typename T, int NT>
@@ -1960,7 +2062,7 @@ __device__ __forceinline__ ElemFetch<T> elem_fetch(const T* srow, const T* trow,
 }
 
 template <int NT, typename SH, typename T, typename F>
-__device__ int elem_pick(Block<NT, SH>& B, const ElemFetch<T>& f, int c, int V, uint64_t seed, uint32_t stream,
+__device__ __forceinline__ int elem_pick(Block<NT, SH>& B, const ElemFetch<T>& f, int c, int V, uint64_t seed, uint32_t stream,
                          uint64_t g, F logw, float* s_win, float* t_win) {
   float best = finf(), bs = 0.0f, bt = 0.0f;
   int bi = 0x7fffffff;
@@ -1989,44 +2091,52 @@ __device__ int elem_pick(Block<NT, SH>& B, const ElemFetch<T>& f, int c, int V, 
   return bi;
 }
 
-// The two-level race of chunk_race and elem_race run by one wave alone (same
-// uniforms, keys and ties), so that it can overlap other waves' serial
-// steps: the chunk keys in double, chunks lane, lane + 64, ...; then the
-// entries of the winning chunk, four consecutive ones per load as elem_fetch
-// takes them (a lane covers the four quarter-chunks j = 0..3 of a 256-thread
-// block's layout).  chunk_logw(c) as for chunk_race; logw(s, t, v) as for
-// elem_pick.  Returns the winner (or >= V if no entry has weight) with its s
-// and t, on every lane.
-template <typename T, typename FC, typename FE>
-__device__ int wave_proposal(const T* srow, const T* trow, int nchunks, int V, int lane, uint64_t seed,
-                             uint32_t chunk_stream, uint32_t elem_stream, uint64_t g, FC chunk_logw, FE logw,
-                             float* s_win, float* t_win) {
-  double ck = __builtin_huge_val();
-  int ci = 0x7fffffff;
-  for (int c = lane; c < nchunks; c += WAVE) {
-    const double lw = chunk_logw(c);
+// The two levels of a race run by single waves (same uniforms, keys and ties as
+// chunk_race and elem_race), so that they overlap other waves' serial steps.
+// Chunk level: this wave's share of the chunks, first, first + step, ...
+// (one per lane at a time); the minimum on every lane.
+template <typename F>
+__device__ __forceinline__ void wave_chunk_race(int nchunks, int first, int step, uint64_t seed, uint32_t stream, uint64_t g, F logw,
+                                double* key_out, int* idx_out) {
+  double best = __builtin_huge_val();
+  int bi = 0x7fffffff;
+  for (int c = first; c < nchunks; c += step) {
+    const double lw = logw(c);
     if (lw > -__builtin_huge_val()) {
-      const double u = static_cast<double>(philox_uniform(seed, chunk_stream, g, static_cast<uint32_t>(c)));
+      const double u = static_cast<double>(philox_uniform(seed, stream, g, static_cast<uint32_t>(c)));
       const double key = log(-log(u)) - lw;
-      if (key < ck) { ck = key; ci = c; }
+      if (key < best) { best = key; bi = c; }
     }
   }
-  wave_argmin(ck, ci);
-  const int c = ci < nchunks ? ci : 0;
+  wave_argmin(best, bi);
+  *key_out = best;
+  *idx_out = bi;
+}
+
+// Entry level inside chunk c: four consecutive entries per load as elem_fetch
+// takes them (a lane covers the four quarter-chunks j = 0..3 of a 256-thread
+// block's layout).  logw(s, t, v) as for elem_pick.  Returns the winner (or
+// >= V if no entry has weight) with its s and t, on every lane.
+template <typename T, typename FE>
+__device__ __forceinline__ int wave_elem_race(const T* srow, const T* trow, int c, int V, int lane, uint64_t seed, uint32_t stream,
+                              uint64_t g, FE logw, float* s_win, float* t_win) {
+  constexpr int Q = CHUNK / (4 * WAVE);
   const int hi = min(V, c * CHUNK + CHUNK);
   float best = finf(), bs = 0.0f, bt = 0.0f;
   int bi = 0x7fffffff;
+  ElemFetch<T> f[Q];  // all loads in flight while the uniforms are drawn
 #pragma unroll
-  for (int j = 0; j < CHUNK / (4 * WAVE); ++j) {
-    const ElemFetch<T> f = elem_fetch<T, CHUNK / 4>(srow, trow, c, V, lane + WAVE * j);
-    if (f.v0 < hi) {
-      const uint4 w = philox_block(seed, elem_stream, g, static_cast<uint32_t>(f.v0 >> 2));
+  for (int j = 0; j < Q; ++j) f[j] = elem_fetch<T, CHUNK / 4>(srow, trow, c, V, lane + WAVE * j);
+#pragma unroll
+  for (int j = 0; j < Q; ++j) {
+    if (f[j].v0 < hi) {
+      const uint4 w = philox_block(seed, stream, g, static_cast<uint32_t>(f[j].v0 >> 2));
       const uint32_t words[4] = {w.x, w.y, w.z, w.w};
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int v = f.v0 + k;
+        const int v = f[j].v0 + k;
         if (v < hi) {
-          const float sk = f.s(k), tk = f.t(k);
+          const float sk = f[j].s(k), tk = f[j].t(k);
           const float lw = logw(sk, tk, v);
           if (lw > -finf()) {
             const float u = word_to_uniform(words[k]);
@@ -2038,14 +2148,7 @@ __device__ int wave_proposal(const T* srow, const T* trow, int nchunks, int V, i
       }
     }
   }
-#pragma unroll
-  for (int o = WAVE / 2; o > 0; o >>= 1) {
-    const float k2 = __shfl_xor(best, o, WAVE);
-    const int i2 = __shfl_xor(bi, o, WAVE);
-    const float a2 = __shfl_xor(bs, o, WAVE);
-    const float b2 = __shfl_xor(bt, o, WAVE);
-    if (k2 < best || (k2 == best && i2 < bi)) { best = k2; bi = i2; bs = a2; bt = b2; }
-  }
+  wave_argmin_with(best, bi, bs, bt);
   *s_win = bs;
   *t_win = bt;
   return bi;

@@ -271,8 +271,8 @@ size_t saki_workspace_bytes(int op, int64_t n_rows, int64_t vocab) {
   if (n_rows <= 0) return 0;
   switch (op) {
     case SAKI_OP_COUPLE:
-      // the counters, the scaled row losses, the list of rows for the
-      // second (expm1-form) launch
+      // the counter, the scaled row losses, and four bytes a row that callers'
+      // workspaces have always held (unused)
       return 256 + loss_ws_bytes(n_rows) + list_ws_bytes(n_rows);
     case SAKI_OP_ROUTE:
       return 256 + loss_ws_bytes(n_rows);  // the row counter, then the scaled row losses
@@ -287,10 +287,9 @@ size_t saki_workspace_bytes(int op, int64_t n_rows, int64_t vocab) {
 
 }  // extern "C"
 
-// The library's own scratch for saki_couple_static: the work counters (256
-// bytes), one double per row for the scaled row losses, one index per row for
-// the list of rows the second launch processes in the expm1 forms.  Each GPU the
-// library runs on holds its own copy until the process ends.  In host code
+// The library's own scratch for saki_couple_static: a workspace for
+// SAKI_STATIC_MAX_ROWS rows.  Each GPU the library runs on holds its own copy
+// until the process ends.  In host code
 // `scratch` names a host-side stand-in, not the device array: only the
 // address from hipGetSymbolAddress (static_scratch) is passed to kernels.
 static __device__ __align__(256) unsigned char scratch[256 + SAKI_STATIC_MAX_ROWS * (sizeof(double) + sizeof(unsigned int))];
@@ -379,6 +378,7 @@ saki_status couple_impl(const saki_rows* in, double eps, uint64_t seed, const sa
   P.row_offset = in->row_offset;
   P.V = static_cast<int>(in->vocab);
   P.eps = eps;
+  P.lam_mid = saki::mid_lambda(eps);
   P.seed = seed;
   P.out = *out;
   if (route) {
@@ -390,29 +390,21 @@ saki_status couple_impl(const saki_rows* in, double eps, uint64_t seed, const sa
     P.grad_stride = route->grad_stride;
     P.target_mode = route->correction_target;
   }
-  // workspace: [0] row counter, [1] second launch's row counter, [2] listed
-  // rows; then the scaled row losses; then the list
-  unsigned int* const counters = static_cast<unsigned int*>(ws);
-  P.next_row = counters;
-  P.redo_count = counters + 2;
-  P.redo_list = reinterpret_cast<unsigned int*>(static_cast<char*>(ws) + 256 + loss_ws_bytes(in->n_rows));
-  P.redo_pass = 0;
-  const int grid = static_cast<int>(std::min<int64_t>(in->n_rows, static_cast<int64_t>(cus) * saki::WG_PER_CU));
+  // workspace: the row counter, then (behind 256 bytes) the scaled row losses
+  unsigned int* const counter = static_cast<unsigned int*>(ws);
+  const int64_t slots = static_cast<int64_t>(cus) * saki::WG_PER_CU;
+  const int grid = static_cast<int>(std::min<int64_t>(in->n_rows, slots));
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(saki::clear_counter_kernel, dim3(1), dim3(64), 0, hs, counters);
-  st = launched("clear_counter_kernel");
-  if (st != SAKI_OK) return st;
-  const bool grad = route && route->grad;
-  for (int pass = 0; pass < 2; ++pass) {
-    // the second launch: the listed rows, every sweep in the expm1 form
-    if (pass == 1) {
-      P.redo_pass = 1;
-      P.next_row = counters + 1;
-    }
-    st = launch_couple(P, in->dtype == SAKI_BF16, route != nullptr, grad,
-                       route && route->grad_dtype == SAKI_BF16, grid, hs);
+  // one row per workgroup needs no counter (nor the launch that clears it)
+  if (in->n_rows > slots) {
+    P.next_row = counter;
+    hipLaunchKernelGGL(saki::clear_counter_kernel, dim3(1), dim3(64), 0, hs, counter);
+    st = launched("clear_counter_kernel");
     if (st != SAKI_OK) return st;
   }
+  st = launch_couple(P, in->dtype == SAKI_BF16, route != nullptr, route && route->grad,
+                     route && route->grad_dtype == SAKI_BF16, grid, hs);
+  if (st != SAKI_OK) return st;
   if (want_sum) {
     hipLaunchKernelGGL(saki::loss_sum_kernel, dim3(1), dim3(1024), 0, hs,
                        static_cast<const double*>(row_losses), in->n_rows, route->loss_sum);
@@ -523,6 +515,7 @@ saki_status saki_spec_verify(const saki_rows* in, int32_t k, const int32_t* draf
   P.k = k;
   P.draft = draft;
   P.eps = eps;
+  P.lam_mid = saki::mid_lambda(eps);
   P.seed = seed;
   P.eos = eos_id;
   P.accepted_len = accepted_len;

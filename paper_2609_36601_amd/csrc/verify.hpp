@@ -33,6 +33,7 @@ struct VerifyParams {
   int k;
   const int32_t* draft;
   double eps;
+  float lam_mid;  // mid_lambda(eps)
   uint64_t seed;
   int eos;
   int32_t* accepted_len;
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
     if (B.tid == 0) {
       long long i;
       for (;;) {
-        i = static_cast<long long>(atomicAdd(P.next_item, 1ull));
+        i = static_cast<long long>(take_index(P.next_item));
         if (i >= n_items) break;
         // a stale word only costs a position evaluated in vain
         const int32_t w = __hip_atomic_load(P.accepted_len + i % nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -128,7 +129,11 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         }
         break;
       }
-      const RowStats& R = stats_sweep<T, VNT, true, K34>(B, srow, trow, V, mid_lambda(P.eps), false);
+      // while wave 0 combines the sums, a lane of the last wave draws the uniform
+      auto idle = [&]() {
+        if (B.tid == VNT - WAVE) sh.u = philox_uniform(P.seed, ACCEPT, g, 0);
+      };
+      const RowStats& R = stats_sweep<T, VNT, true, K34>(B, srow, trow, V, P.lam_mid, false, false, idle);
       if (uniform(!R.finite)) {
         if (B.tid == 0) {
           if (P.has_pp) write_skipped(o, r, z, SAKI_ROW_NONFINITE);
@@ -137,7 +142,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         break;
       }
       const float sz = Loader<T>::load1(srow + z), tz = Loader<T>::load1(trow + z);
-      const double u = static_cast<double>(philox_uniform(P.seed, ACCEPT, g, 0));
+      const double u = static_cast<double>(sh.u);
       // g(lam) = lam x_z - A(lam) = log q(z) - log p(z) is concave in lam with
       // g(0) = 0, so on a bracket [la, lb] of lambda* it lies above min(g(la),
       // g(lb)): a draft with u below exp of that is accepted whatever lambda*
@@ -227,33 +232,38 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       bool tv_ok = false;
       bool tv_acc = false;   // the fused sweep's form (the final sweep's is F.acc)
       int res_chunk = nch;
-      auto sweep1 = [&](float lam, bool acc) { return lam_sweep<T, VNT>(B, srow, trow, V, R, lam, acc); };
+      bool search = true;    // lambda* by lambda sweeps
       if (fused != 0) {
-        const double xz = (static_cast<double>(LOG2E) * (static_cast<double>(tz) - static_cast<double>(sz)) -
-                           static_cast<double>(R.cL)) * LN2_D;
-        const bool reject_g = !(u < exp(fmin(0.0, plan.S0.lam * xz - plan.S0.A)));
+        // the decision at the start point (in float, as in the coupling kernel)
+        const float lam_g = static_cast<float>(plan.S0.lam);
+        const float A_g = static_cast<float>(plan.S0.A * static_cast<double>(LOG2E));
+        const bool reject_g = uniform(!(sh.u < fexp2(fminf(0.0f, fmaf(lam_g, fmaf(tz - sz, LOG2E, -R.cL), -A_g)))));
         FusedConst FC;
         FC.msL = R.ms * LOG2E;
         FC.cL = R.cL;
-        FC.lam = static_cast<float>(plan.S0.lam);
-        FC.AL = static_cast<float>(plan.S0.A * static_cast<double>(LOG2E));
+        FC.lam = lam_g;
+        FC.AL = A_g;
         FC.gsc = 0.0f;
         FC.set_y();
         const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
         tv_acc = facc;
         const FusedSums FS = fused_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, FC, facc, reject_g,
                                                                   0.0f, 0.0f, -1, 0.0f);
+        double le0 = 0.0;
         if (B.wave == 0) {
+          FC.set_node();
           const int32_t word = __hip_atomic_load(P.accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
           const LamResult L0 = lambda_search_with(R, P.eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
-                                                  &E0, facc, true);
+                                                  true, E0, facc, true);
           int state = -1, C0 = 0;
+          double alpha0 = 0.0;
           FinalConst F0{};
           FusedFinal FF0{};
           if (L0.sweeps == 0) {
             F0 = final_const(R, L0, false);
-            C0 = !(u < exp(fmin(0.0, L0.log_ratio(sz, tz)))) ? 1 : 0;
+            alpha0 = exp(fmin(0.0, L0.log_ratio(sz, tz)));
+            C0 = !(u < alpha0) ? 1 : 0;
             FF0 = fused_tv(R, L0, F0, FC, FS, facc);
             // settled unless the decision or TV needs the final sweep: a
             // rejection needs valid residual masses (kept only where the
@@ -266,31 +276,30 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
             plan.L = L0;
             plan.F = F0;
             plan.FF = FF0;
+            plan.E0 = E0;
+            plan.alpha = alpha0;
             plan.state = state;
             plan.C = C0;
           }
+        } else if (reject_g) {
+          le0 = res_race_begin<VNT>(B, nch, P.seed, g);
         }
         __syncthreads();
         const int state = __builtin_amdgcn_readfirstlane(plan.state);
         if (state == -2) break;
-        if (state < 0) {
-          const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-          L = lambda_search_with(R, P.eps, sweep1, false, 0.0f, &E0, facc);
-          F = final_const(R, L, false);
-        } else {
+        search = state < 0;
+        if (!search) {
           L = plan.L;
           F = plan.F;
           if (state == 1) {
             settled = true;
             tv_ok = plan.FF.ok;
             if (tv_ok) TV = plan.FF.TV;
-            if (plan.C != 0) {
-              const double hb = expm1(plan.FF.hmax * LN2_D) * 1.02 + 2e-6;
-              const double flip = plan.FF.flip;
-              res_chunk = chunk_race_certain<VNT>(B, nch, P.seed, RES_CHUNK, g, [&](int c, double& m, double& bb) {
-                m = fmax(static_cast<double>(sh.chunk_a[c]), 0.0);
-                bb = hb * static_cast<double>(sh.chunk_b[c]) + flip;
-              });
+            if (uniform(plan.C != 0)) {
+              const double hx = plan.FF.hmax * LN2_D;  // expm1(x) <= x + x^2, as in the coupling kernel
+              const double hb = hx * (1.0 + hx) * 1.02 + 2e-6;
+              res_chunk = __builtin_amdgcn_readfirstlane(
+                  res_race_end<VNT>(B, nch, P.seed, g, le0, hb, plan.FF.flip));
               if (res_chunk < 0) {
                 settled = false;
                 res_chunk = nch;
@@ -298,8 +307,12 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
             }
           }
         }
-      } else {
-        L = lambda_search<T, VNT>(B, srow, trow, V, R, P.eps, force_acc);
+      }
+      if (search) {
+        const LamEval E0 = fused != 0 ? plan.E0 : LamEval{};
+        L = lambda_search_with(R, P.eps, [&](float lam, bool acc) {
+          return lam_sweep<T, VNT>(B, srow, trow, V, R, lam, acc);
+        }, force_acc, 0.0f, fused != 0, E0, tv_acc);
         F = final_const(R, L, force_acc);
       }
       const double alpha = exp(fmin(0.0, L.log_ratio(sz, tz)));

@@ -497,6 +497,34 @@ def test_route_loss_f32_ragged_and_bad_rows(saki_lib):
     assert np.max(np.abs(gr_g[ii] - grad)) <= parity.GRAD_ATOL
 
 
+@pytest.mark.parametrize("n", [1, 511, 512, 513, 1024, 1537, 1600])
+def test_row_counts_around_the_grid(saki_lib, n):
+    """Row counts at one, two and three rows per workgroup (512 on 256 CUs): one
+    row per workgroup without the counter, rows taken ahead, and the last rows
+    taken when a workgroup is free.  Every row equals the same row of calls of
+    100 rows bit for bit, and the oracle on a sample; some rows have bad logits."""
+    V = 1100
+    g = torch.Generator(device=DEV).manual_seed(n)
+    s = padded((2 * torch.randn(n, V, generator=g, device=DEV)).to(torch.bfloat16))
+    t = padded((0.8 * s.float() + torch.randn(n, V, generator=g, device=DEV)).to(torch.bfloat16))
+    s[torch.rand(n, generator=g, device=DEV) < 0.05, 3] = float("nan")
+    say(f"couple n={n}")
+    kw = dict(route=True, grad_dtype=torch.float32, grad_scale=0.5)
+    out = saki_lib.couple(s, t, 0.2, 9, 40, **kw)
+    torch.cuda.synchronize()
+    for a in range(0, n, 100):
+        part = saki_lib.couple(s[a:a + 100], t[a:a + 100], 0.2, 9, 40 + a, **kw)
+        for k in part:
+            if k != "loss_sum":
+                x, y = out[k][a:a + 100].contiguous(), part[k].contiguous()
+                assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (k, a)
+    rows = np.unique(np.r_[0, n - 1, np.random.default_rng(n).integers(0, n, 24)])
+    ii = torch.as_tensor(rows, device=DEV)
+    R = parity.compare_couple(np_out(out), f64(s[ii]), f64(t[ii]), 0.2, 9, 40, rows, grad_scale=0.5)
+    say(R.summary())
+    R.check()
+
+
 def test_determinism_and_row_split_invariance(saki_lib):
     s, t = workloads.rows("mid", 0, 512, device=DEV)
     a = saki_lib.couple(s, t, 0.2, 5, 1000, route=True, grad_dtype=torch.float32)
