@@ -35,6 +35,12 @@ __device__ __forceinline__ float min3_raw(float a, float b, float c) {
   return r;
 }
 
+__device__ __forceinline__ float min3_abs(float a, float b, float c) {  // min(a, |b|, |c|)
+  float r;
+  asm("v_min3_f32 %0, %1, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 // ---------------------------------------------------------------------------
 // Row element layout inside a chunk.  Lane l of the wave that owns chunk c
 // holds entries c*1024 + 8l + e (e < 8) and c*1024 + 512 + 8l + (e - 8)
@@ -277,6 +283,25 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += dpp_f<DPP_HALF_MIRROR>(v);
   v += dpp_f<DPP_MIRROR>(v);
   return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
+}
+// The wave's sum on its last lane (the others hold partial sums): a scan inside
+// each row of 16 and two row broadcasts, six adds with the exchange in the
+// operand, a third of wave_sum's instructions.  For sums taken once per chunk.
+constexpr int DPP_ROW_SHR = 0x110;     // + n: lane i reads lane i - n of its row
+constexpr int DPP_ROW_BCAST15 = 0x142; // lane 15 of each row to the next row
+constexpr int DPP_ROW_BCAST31 = 0x143; // lane 31 to rows 2 and 3
+template <int CTRL>
+__device__ __forceinline__ float dpp_or_0(float v) {  // 0 where there is no source lane
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float wave_sum_last(float v) {
+  v += dpp_or_0<DPP_ROW_SHR + 1>(v);
+  v += dpp_or_0<DPP_ROW_SHR + 2>(v);
+  v += dpp_or_0<DPP_ROW_SHR + 4>(v);
+  v += dpp_or_0<DPP_ROW_SHR + 8>(v);
+  v += dpp_or_0<DPP_ROW_BCAST15>(v);
+  v += dpp_or_0<DPP_ROW_BCAST31>(v);
+  return v;
 }
 __device__ __forceinline__ double wave_sum(double v) {
   v += dpp_d<DPP_XOR1>(v);

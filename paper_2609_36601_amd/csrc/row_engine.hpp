@@ -66,7 +66,7 @@ struct RowStats {
   int vstar;           // argmax t, lowest index on ties
   float t_smax;        // t at an entry holding max s (the dominant entry of p)
   double pmax;         // max_v p_v = exp(ms - lse_s)
-  float lam_mid;       // the middle node (mid_lambda)
+  double lam_mid;      // the middle node (mid_lambda), or 0: the row has none
   bool k34;            // k3, k4 were summed (else 0)
   double mid_A, mid_A1, mid_A2;  // A, A', A'' there
   bool finite;
@@ -406,13 +406,18 @@ __device__ __forceinline__ double shift_correction(float ms, float msL) {
   return exp2(-d0);
 }
 
+// The middle node's weights are taken relative to the maximum of p~ alone, so
+// they reach 2^(kLm (mt - ms)): rows where that could leave the range float sums
+// need (maxima of s and t 100 or more apart) go without a middle node.
+constexpr float MID_MAX_SHIFT = 60.0f;
+
 struct StatsAcc {
   float Ms, Mt;                 // wave-uniform running maxima of s and t
   float MsL, MtL;               // Ms log2(e), Mt log2(e) rounded to float
   double Ss, St;                // per-lane sums of 2^(s log2 e - MsL), 2^(t log2 e - MtL)
   float S1, S2, S3, S4;         // per-lane p-weighted powers of d (relative to Ms)
   float T1, T2;                 // per-lane pi-weighted sums of d, d^2 (relative to Mt)
-  double Sm;                    // per-lane sum of 2^((1 - lm) as + lm at), lm the middle node
+  double Sm;                    // per-lane sum of 2^(as + kLm d), the middle node's weights
   float Q1, Q2;                 // per-lane d, d^2 under those weights
   int tidx;                     // wave-uniform lowest index of the running max of t
   float t_smax;                 // wave-uniform: t at an entry holding the running max of s
@@ -438,12 +443,13 @@ struct StatsAcc {
 // is one factor for every term sharing it, removed exactly once the row's
 // maxima are known (shift_correction).  The proposal mass of chunk c is kept as
 // (MsL, sum_c 2^(s log2 e - MsL)), i.e. ln W_c = MsL ln 2 + ln(sum).
-// MID: also the middle node's sums (else the row carries no middle node and
+// kLm: the middle node lm in log2 units (lm = kLm / log2 e exactly, as the
+// sums see it).  MID: also the middle node's sums (else the row carries no middle node and
 // the lambda search starts from the ends alone); K34: the third and fourth
 // p-moments of d.
 template <bool TAIL, bool MID, bool K34, typename SH>
 __device__ __forceinline__ void stats_math(const float* s, const float* t, uint32_t vm, int c,
-                                           int lane, bool keep_chunks, bool keep_teacher, float lm, SH& sh,
+                                           int lane, bool keep_chunks, bool keep_teacher, float kLm, SH& sh,
                                            StatsAcc& a) {
   // this lane's maxima and range of d over the chunk: chains of three-input
   // max / min (EPL - 1 entries after the first, two per instruction)
@@ -488,9 +494,8 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     const float f = fexp2(dsl);
     a.Ss *= static_cast<double>(f);
     a.S1 *= f; a.S2 *= f; a.S3 *= f; a.S4 *= f;
-    const float fm = fexp2((1.0f - lm) * dsl);
-    a.Sm *= static_cast<double>(fm);
-    a.Q1 *= fm; a.Q2 *= fm;
+    a.Sm *= static_cast<double>(f);
+    a.Q1 *= f; a.Q2 *= f;
     a.Ms = cms;
     a.MsL = cmsL;
   }
@@ -508,9 +513,6 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     a.St *= static_cast<double>(f);
     a.T1 *= f;
     a.T2 *= f;
-    const float fm = fexp2(lm * dtl);
-    a.Sm *= static_cast<double>(fm);
-    a.Q1 *= fm; a.Q2 *= fm;
     a.Mt = cmt;
     a.MtL = cmtL;
   }
@@ -525,11 +527,11 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     const float at = fmaf(t[e], LOG2E, -a.MtL);
     float es = fexp2(as);
     float et = fexp2(at);
-    // the middle node's weight p~^(1 - lm) pi~^lm: its exponent is at most 0
-    // (as, at <= 0), so it cannot overflow
-    float em = MID ? fexp2(fmaf(lm, at - as, as)) : 0.0f;
-    if (TAIL && !SAKI_VALID(e)) { es = 0.f; et = 0.f; em = 0.f; }
     const float d = t[e] - s[e];
+    // the middle node's weight p~ e^(lm d) = 2^(as + kLm d): its exponent is
+    // at most lm (Mt - Ms) log2 e (MID_MAX_SHIFT bounds it for a row that uses it)
+    float em = MID ? fexp2(fmaf(d, kLm, as)) : 0.0f;
+    if (TAIL && !SAKI_VALID(e)) { es = 0.f; et = 0.f; em = 0.f; }
     const float d2 = d * d;
     p1 = fmaf(es, d, p1);
     p2 = fmaf(es, d2, p2);
@@ -558,15 +560,15 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
   }
   // chunk masses (stored as float) by a float reduction
   if (keep_chunks) {
-    const float csum = wave_sum(static_cast<float>(ps));
-    if (lane == 0) {
+    const float csum = wave_sum_last(static_cast<float>(ps));
+    if (lane == WAVE - 1) {
       sh.chunk_a[c] = a.MsL;
       sh.chunk_b[c] = csum;
     }
   }
   if (keep_teacher) {
-    const float csum = wave_sum(static_cast<float>(pt));
-    if (lane == 0) {
+    const float csum = wave_sum_last(static_cast<float>(pt));
+    if (lane == WAVE - 1) {
       sh.chunk_c[c] = a.MtL;
       sh.chunk_d[c] = csum;
     }
@@ -590,7 +592,7 @@ struct StatsBlock {
   double Ss, S1, S2, S3, S4, St, T1, T2;
   double Sm, Q1, Q2;  // middle-node sums (relative to the row's maxima)
   double cs;          // shift_correction of s
-  float lm;           // the middle node
+  double lm;          // the middle node, or 0
   float tbest;
   int tidx;
   float t_smax;
@@ -627,7 +629,7 @@ __device__ __forceinline__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
 }
 
 template <int NT, typename SH>
-__device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) {
+__device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float kLm) {
   constexpr int NW = NT / WAVE;
   StatsBlock O;
   O.ms = -finf();
@@ -648,19 +650,6 @@ __device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) 
   // msL = ms log2(e) rounded (the MsL of a wave holding the maximum), then
   // remove that rounding (shift_correction)
   const float msL = __fmul_rn(O.ms, LOG2E), mtL = __fmul_rn(O.mt, LOG2E);
-  // The double exponentials of the combination are evaluated side by side, one
-  // per lane: the factors 2^((1 - lm)(wMsL - msL) + lm (wMtL - mtL)) of the
-  // waves' middle-node sums (lanes 0 .. NW - 1), and 2^-d0 of the two shifts'
-  // roundings (shift_correction) and of the middle node's (lanes NW ..).
-  const double lm1 = static_cast<double>(1.0f - lm), lmd = static_cast<double>(lm);
-  const double d0s = static_cast<double>(LOG2E) * static_cast<double>(O.ms) - static_cast<double>(msL);
-  const double d0t = static_cast<double>(LOG2E) * static_cast<double>(O.mt) - static_cast<double>(mtL);
-  static_assert(NW + 3 <= WAVE, "one exponential per lane");
-  double ex = B.lane == NW ? -d0s : B.lane == NW + 1 ? -d0t : -(lm1 * d0s + lmd * d0t);
-  if (B.lane < NW)
-    ex = lm1 * (B.sh.red_d[B.lane][8] - static_cast<double>(msL)) +
-         lmd * (B.sh.red_d[B.lane][9] - static_cast<double>(mtL));
-  ex = exp2(ex);
   for (int w = 0; w < NW; ++w) {
     const float wMs = B.sh.red_f[w][0], wMt = B.sh.red_f[w][1];
     const float wMsL = static_cast<float>(B.sh.red_d[w][8]), wMtL = static_cast<float>(B.sh.red_d[w][9]);
@@ -669,15 +658,17 @@ __device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) 
 #pragma unroll
     for (int i = 0; i < 5; ++i) acc[i] += B.sh.red_d[w][i] * gs;
 #pragma unroll
-    for (int i = 5; i < 8; ++i) acc[i] += B.sh.red_d[w][i] * gt;
-    const double gm = (wMs == -finf() || wMt == -finf()) ? 0.0 : lane_d(ex, w);
+    for (int i = 0; i < 3; ++i) acc[8 + i] += B.sh.red_d[w][11 + i] * gs;
 #pragma unroll
-    for (int i = 0; i < 3; ++i) acc[8 + i] += B.sh.red_d[w][11 + i] * gm;
+    for (int i = 5; i < 8; ++i) acc[i] += B.sh.red_d[w][i] * gt;
     const int wi = B.sh.red_i[w][0];
     if (wMt > tb || (wMt == tb && wi < ti)) { tb = wMt; ti = wi; }
     if (wMs == O.ms) st = fmaxf(st, static_cast<float>(B.sh.red_d[w][10]));
   }
-  const double cs = lane_d(ex, NW), ct = lane_d(ex, NW + 1), cm = lane_d(ex, NW + 2);
+  // 2^-d0 of the two shifts' roundings, side by side on two lanes (the middle
+  // node's weights carry the shift of s)
+  const double cc = shift_correction(B.lane == 0 ? O.ms : O.mt, B.lane == 0 ? msL : mtL);
+  const double cs = lane_d(cc, 0), ct = lane_d(cc, 1);
   // The maximum's own term went into the sums as 2^d0 rounded to float (d0 =
   // the rounding of the shift, ~1e-6: a rounding of ~6e-8 next to 1); after
   // the shift correction it is exactly 1.  The log-probability of a dominant
@@ -686,9 +677,11 @@ __device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float lm) 
   const double dom_t = 1.0 - static_cast<double>(fexp2(fmaf(O.mt, LOG2E, -mtL))) * ct;
   O.Ss = acc[0] * cs + dom_s; O.S1 = acc[1] * cs; O.S2 = acc[2] * cs; O.S3 = acc[3] * cs; O.S4 = acc[4] * cs;
   O.St = acc[5] * ct + dom_t; O.T1 = acc[6] * ct; O.T2 = acc[7] * ct;
-  O.Sm = acc[8] * cm; O.Q1 = acc[9] * cm; O.Q2 = acc[10] * cm;
+  O.Sm = acc[8] * cs; O.Q1 = acc[9] * cs; O.Q2 = acc[10] * cs;
   O.cs = cs;
-  O.lm = lm;
+  // no middle node on a row whose weights there could leave the float range
+  O.lm = kLm > 0.0f && fabsf(kLm * (O.mt - O.ms)) < MID_MAX_SHIFT
+             ? static_cast<double>(kLm) / static_cast<double>(LOG2E) : 0.0;
   O.tbest = tb;
   O.tidx = ti;
   O.t_smax = st;
@@ -730,15 +723,14 @@ __device__ __forceinline__ RowStats row_stats_from(const StatsBlock& O, bool k34
   R.c = static_cast<float>(Ed);
   if (!isfinite(R.c)) R.c = 0.0f;
   R.cL = R.c * LOG2E;
-  // A at the middle node lm: sum_v p_v e^{lm x_v} = e^{lm (mt - ms - c)}
-  // sum_m / sum_s, with sum_m = sum e^{(1 - lm)(s - ms) + lm (t - mt)}; its
-  // derivatives are the mean and variance of x under the tilted weights
+  // A at the middle node lm: sum_v p_v e^{lm x_v} = e^{-lm c} sum_m / sum_s,
+  // with sum_m = sum e^{(s - ms) + lm d}; its derivatives are the mean and
+  // variance of x under the tilted weights
   {
-    const double lm = static_cast<double>(O.lm);
+    const double lm = O.lm;
     const double M1 = O.Q1 * im, M2 = O.Q2 * im;
-    R.lam_mid = O.Sm > 0.0 ? O.lm : 0.0f;
-    R.mid_A = lm * (static_cast<double>(R.mt) - static_cast<double>(R.ms) - static_cast<double>(R.c)) +
-              ln_m - ln_s;
+    R.lam_mid = lm > 0.0 && O.Sm > 0.0 && isfinite(M2) ? lm : 0.0;
+    R.mid_A = ln_m - ln_s - lm * static_cast<double>(R.c);
     R.mid_A1 = M1 - static_cast<double>(R.c);
     R.mid_A2 = fmax(M2 - M1 * M1, 0.0);
   }
@@ -759,15 +751,16 @@ __device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T
   constexpr int NW = NT / WAVE;
   StatsAcc a;
   a.init();
+  const float kLm = lm * LOG2E;
   for_chunks<T, NW, false, fill_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      stats_math<TAIL, MID, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, lm, B.sh, a);
+                      stats_math<TAIL, MID, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, kLm, B.sh, a);
                     }, row_cache<T>(B.sh));
   stats_post(B, a);
   __syncthreads();
   if (B.wave == 0) {
-    const RowStats R = row_stats_from(stats_combine(B, MID ? lm : 0.0f), K34, B.lane);
+    const RowStats R = row_stats_from(stats_combine(B, MID ? kLm : 0.0f), K34, B.lane);
     if (B.lane == 0) B.sh.rs.r = R;
   } else {
     idle();
@@ -1085,7 +1078,7 @@ struct HermiteA {
   static constexpr int N = N0 + 6;
   double z[N], c[N];
   __device__ __forceinline__ explicit HermiteA(const RowStats& R) {
-    const double lm = static_cast<double>(R.lam_mid);
+    const double lm = R.lam_mid;
     const double f0[5] = {0.0, R.mean_p - R.c, R.var, R.k3, R.k4};
     const double fm[3] = {R.mid_A, R.mid_A1, R.mid_A2};
     const double f1[3] = {R.lse_t - R.lse_s - R.c, R.mean_pi - R.c, R.var_pi};
@@ -1149,7 +1142,7 @@ __device__ __forceinline__ void hermite_refine(const RowStats& R, double eps, do
   // lambda* lies: the search keeps to that side.  The ends' starts can be far
   // off on rows whose largest d dominate q_lambda, where the interpolant is
   // still close, so l0 only seeds the search.
-  const double lm = static_cast<double>(R.lam_mid);
+  const double lm = R.lam_mid;
   const bool above = lm * R.mid_A1 - R.mid_A <= eps;
   const double blo = above ? lm : 0.0, bhi = above ? 1.0 : lm;
   // safeguarded Newton on KL(l) = l A'(l) - A(l) = eps (KL' = l A''),
@@ -1188,15 +1181,15 @@ __device__ __forceinline__ void hermite_refine(const RowStats& R, double eps, do
 __device__ __forceinline__ StartPoint start_point(const RowStats& R, double eps) {
   StartPoint S;
   S.herm = false;
-  if (R.lam_mid > 0.0f) {
+  if (R.lam_mid > 0.0) {
     // the interpolant's search is seeded by the power law KL ~ lambda^n through
     // KL and its derivative at the middle node (n = lambda KL' / KL): it starts
     // within a few percent, so the ends' starts below (twenty Newton and
     // fourteen bisection steps) are left to the rows without a usable interpolant
-    const double lm = static_cast<double>(R.lam_mid);
+    const double lm = R.lam_mid;
     const double klm = lm * R.mid_A1 - R.mid_A;
     const float n = static_cast<float>(lm * lm * R.mid_A2) / static_cast<float>(klm);
-    const float l0 = R.lam_mid * fexp2(flog2(static_cast<float>(eps / klm)) / fminf(fmaxf(n, 1.0f), 4.0f));
+    const float l0 = static_cast<float>(lm) * fexp2(flog2(static_cast<float>(eps / klm)) / fminf(fmaxf(n, 1.0f), 4.0f));
     const double seed = (l0 > 0.0f && l0 < 1.0f) ? static_cast<double>(l0) : lm;
     if (R.k34)
       hermite_refine<5>(R, eps, seed, S);
@@ -1481,8 +1474,8 @@ __device__ __forceinline__ double final_sweep(Block<NT, SH>& B, const T* srow, c
                         if (GRAD) g[e] = coef * p;
                       }
                       if (keep_res) {
-                        const float m = wave_sum(tv);
-                        if (B.lane == 0) B.sh.chunk_a[c] = m;
+                        const float m = wave_sum_last(tv);
+                        if (B.lane == WAVE - 1) B.sh.chunk_a[c] = m;
                       }
                       TV += static_cast<double>(tv);
                       if (GRAD) store_lane<G, TAIL>(grow, c, B.lane, V, g);
@@ -1548,7 +1541,7 @@ __device__ __forceinline__ double final_sweep_any(Block<NT, SH>& B, const T* sro
 // lambda*, accept decision or bounds do not hold takes the final sweep after
 // all (its gradient is then rewritten).
 // ---------------------------------------------------------------------------
-constexpr float FUSED_BAND = 1.0f / 1024.0f;
+constexpr float FUSED_BAND = 1.0f / 2048.0f;
 constexpr double FUSED_REACH = 0.02;
 // largest bound on TV's error accepted from the fused sums (relative; the
 // bound is a worst case, the error itself is far below it)
@@ -1591,8 +1584,8 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
   for_chunks<T, NW, true, use_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      float w = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, t0 = 0.f, u0 = 0.f, u1 = 0.f, bd = 0.f;
-                      float g[EPL];
+                      float w = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, t0 = 0.f, u0 = 0.f, u1 = 0.f;
+                      float g[EPL], ys[EPL], pes[EPL];
 #pragma unroll
                       for (int e = 0; e < EPL; ++e) {
                         const float a = fmaf(s[e], LOG2E, -C.msL);
@@ -1613,13 +1606,25 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                         const float pp = pos ? pe : 0.0f;
                         u0 += pp;
                         u1 = fmaf(pp, y, u1);
-                        bd += (fabsf(y) < FUSED_BAND) ? pe : 0.0f;
+                        ys[e] = y;
+                        pes[e] = pe;
                         if (GRAD) g[e] = C.gsc * pt;
                       }
+                      // the band's mass, summed only in the chunks that reach it
+                      // (one in five): the smallest |y| costs half an instruction
+                      // an entry, the sum three
+                      float ymin = fabsf(ys[0]);
+#pragma unroll
+                      for (int e = 1; e < EPL; e += 2)
+                        ymin = min3_abs(ymin, ys[e], ys[e + 1 < EPL ? e + 1 : e]);
+                      if (wave_any(ymin < FUSED_BAND)) {
+#pragma unroll
+                        for (int e = 0; e < EPL; ++e) Bd += (fabsf(ys[e]) < FUSED_BAND) ? pes[e] : 0.0f;
+                      }
                       if (keep_res) {
-                        const float m = wave_sum(t0);
-                        const float q = wave_sum(u0);
-                        if (B.lane == 0) {
+                        const float m = wave_sum_last(t0);
+                        const float q = wave_sum_last(u0);
+                        if (B.lane == WAVE - 1) {
                           B.sh.chunk_a[c] = m;
                           B.sh.chunk_b[c] = q;
                         }
@@ -1631,7 +1636,6 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                       acc[4] += static_cast<double>(t0);
                       U0 += u0;
                       U1 += u1;
-                      Bd += bd;
                       if (GRAD) store_lane<G, TAIL>(grow, c, B.lane, V, g);
                     }, row_cache<T>(B.sh));
   if (GRAD && hot >= 0 && hot < V && B.tid == entry_owner<NT>(hot)) {

@@ -153,8 +153,8 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       if (!need_lam) {
         const double lr1 = (static_cast<double>(tz) - R.lse_t) - (static_cast<double>(sz) - R.lse_s);
         double gmin = fmin(0.0, lr1);
-        if (R.lam_mid > 0.0f) {
-          const double lm = static_cast<double>(R.lam_mid);
+        if (R.lam_mid > 0.0) {
+          const double lm = R.lam_mid;
           const double xz = static_cast<double>(tz) - static_cast<double>(sz) - static_cast<double>(R.c);
           const double gm = lm * xz - R.mid_A;
           const double klm = lm * R.mid_A1 - R.mid_A;
