@@ -241,7 +241,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
       tv_acc = facc;
       const FusedSums FS = fused_sweep_any<T, G, NT, GRAD>(B, srow, trow, grow, V, FC, facc, Cg, coef_g, invS,
-                                                          Cg ? hot_c : z, Cg ? s_hot_c : sz);
+                                                          Cg ? hot_c : z, Cg ? s_hot_c : sz, R.sum_s / R.shift);
       // wave 0: lambda* from the node's model when it needs no sweep, the
       // accept decision there and TV from the fused sums; the other waves run
       // the residual's chunk race meanwhile where a correction is predicted

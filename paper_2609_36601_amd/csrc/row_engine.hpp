@@ -1577,15 +1577,15 @@ struct FusedSums {
 template <typename T, typename G, int NT, bool GRAD, int MODE, typename SH>
 __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                                  const FusedConst C, bool keep_res, float coef, float invS,
-                                                 int hot, float s_hot) {
+                                                 int hot, float s_hot, double sum_pt) {
   constexpr int NW = NT / WAVE;
-  double acc[5] = {0, 0, 0, 0, 0};  // W, S1, S2, S3, T0
-  float U0 = 0.f, U1 = 0.f, Bd = 0.f;
+  double acc[5] = {0, 0, 0, 0, 0};  // W, S1, S2, S3, R0 = sum |r|
+  float D0 = 0.f, A1 = 0.f, Bd = 0.f;  // sum sgn(r) p~ e, sum p~ e |y|, the band's mass
   for_chunks<T, NW, true, use_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      float w = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, t0 = 0.f, u0 = 0.f, u1 = 0.f;
-                      float g[EPL], ys[EPL], pes[EPL];
+                      float w = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, r0 = 0.f, d0 = 0.f, a1 = 0.f;
+                      float g[EPL], ys[EPL], pes[EPL], rs[EPL];
 #pragma unroll
                       for (int e = 0; e < EPL; ++e) {
                         const float a = fmaf(s[e], LOG2E, -C.msL);
@@ -1601,13 +1601,15 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                         s1 = fmaf(pe, y, s1);
                         s2 = fmaf(pe, y2, s2);
                         s3 = fmaf(pe * y2, y, s3);
-                        const bool pos = r > 0.0f;
-                        t0 += pos ? r : 0.0f;
-                        const float pp = pos ? pe : 0.0f;
-                        u0 += pp;
-                        u1 = fmaf(pp, y, u1);
+                        // the sums over P = {r > 0} as halves of sums and sums of
+                        // absolute values (the absolute value and the sign cost
+                        // nothing or one instruction; a selected sum costs two more)
+                        r0 += fabsf(r);
+                        d0 += copysignf(pe, r);
+                        a1 = fmaf(pe, fabsf(y), a1);
                         ys[e] = y;
                         pes[e] = pe;
+                        rs[e] = r;
                         if (GRAD) g[e] = C.gsc * pt;
                       }
                       // the band's mass, summed only in the chunks that reach it
@@ -1622,6 +1624,14 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                         for (int e = 0; e < EPL; ++e) Bd += (fabsf(ys[e]) < FUSED_BAND) ? pes[e] : 0.0f;
                       }
                       if (keep_res) {
+                        // the chunk's sums over P themselves (the halves would
+                        // cancel where little of the chunk lies in P)
+                        float t0 = 0.f, u0 = 0.f;
+#pragma unroll
+                        for (int e = 0; e < EPL; ++e) {
+                          t0 += fmaxf(rs[e], 0.0f);
+                          u0 += rs[e] > 0.0f ? pes[e] : 0.0f;
+                        }
                         const float m = wave_sum_last(t0);
                         const float q = wave_sum_last(u0);
                         if (B.lane == WAVE - 1) {
@@ -1633,24 +1643,25 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                       acc[1] += static_cast<double>(s1);
                       acc[2] += static_cast<double>(s2);
                       acc[3] += static_cast<double>(s3);
-                      acc[4] += static_cast<double>(t0);
-                      U0 += u0;
-                      U1 += u1;
+                      acc[4] += static_cast<double>(r0);
+                      D0 += d0;
+                      A1 += a1;
                       if (GRAD) store_lane<G, TAIL>(grow, c, B.lane, V, g);
                     }, row_cache<T>(B.sh));
   if (GRAD && hot >= 0 && hot < V && B.tid == entry_owner<NT>(hot)) {
     const float p = fexp2(fmaf(s_hot, LOG2E, -C.msL)) * invS;
     Storer<G>::store1(grow + hot, coef * (p - 1.0f));
   }
-  double v[8] = {acc[0], acc[1], acc[2], acc[3], acc[4], static_cast<double>(U0), static_cast<double>(U1),
+  double v[8] = {acc[0], acc[1], acc[2], acc[3], acc[4], static_cast<double>(D0), static_cast<double>(A1),
                  static_cast<double>(Bd)};
   B.sum_wave0(v);
   FusedSums S;
 #pragma unroll
   for (int i = 0; i < 4; ++i) S.v[i] = v[i];
-  S.T0 = v[4];
-  S.U0 = v[5];
-  S.U1 = v[6];
+  // sum p~ e over the row: sum p~ (the sums carry 2^d0, see shift_correction) + W
+  S.T0 = 0.5 * (v[0] + v[4]);
+  S.U0 = 0.5 * (sum_pt + v[0] + v[5]);
+  S.U1 = 0.5 * (v[1] + v[6]);
   S.Bd = v[7];
   return S;
 }
@@ -1658,9 +1669,10 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
 template <typename T, typename G, int NT, bool GRAD, typename SH>
 __device__ __forceinline__ FusedSums fused_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                      const FusedConst& C, bool acc, bool keep_res, float coef, float invS, int hot,
-                                     float s_hot) {
-  if (acc) return fused_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot);
-  return fused_sweep<T, G, NT, GRAD, FIN_FAST>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot);
+                                     float s_hot, double sum_pt) {
+  if (acc)
+    return fused_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot, sum_pt);
+  return fused_sweep<T, G, NT, GRAD, FIN_FAST>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot, sum_pt);
 }
 
 // The dominant entry's term of the fused sweep's W in the plain form: its
