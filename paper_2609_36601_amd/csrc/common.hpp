@@ -43,6 +43,17 @@ __device__ __forceinline__ unsigned int take_next(unsigned int* counter, unsigne
   return v;
 }
 
+// The kernel's only argument, read where it is used: the pointer is opaque to
+// the compiler at each call, so fields are loaded again (from the scalar cache)
+// instead of being held in scalar registers across the sweeps, where 30 pointers
+// spill into lanes of vector registers and every row pays for reading them back.
+template <typename S>
+__device__ __forceinline__ const __attribute__((address_space(4))) S* kernel_args() {
+  auto p = (const __attribute__((address_space(4))) S*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // A condition that every lane of a wave computes alike (from LDS or uniform
 // data), as one the compiler knows to be uniform: a branch on it that leaves or
 // restarts a loop with barriers is then a scalar branch, never a masked one.

@@ -29,12 +29,13 @@ struct CoupleParams {
 
 // K34: the stats sweep sums k3, k4 (radii below K34_EPS).
 template <typename T, typename G, bool ROUTE, bool GRAD, int KC, bool K34>
-__global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
+__global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams) {
   using SH = RowSharedK<KC>;
   __shared__ SH sh;
   __shared__ RowPlan plan;
   Block<NT, SH> B(sh);
-  const int V = P.V;
+  const auto* P = kernel_args<CoupleParams>();
+  const int V = P->V;
   const int nch = (V + CHUNK - 1) / CHUNK;
   // Workgroups take rows from a counter: their speeds differ (the two
   // workgroups of a CU, and CUs, get unequal shares of the memory system), so
@@ -57,25 +58,26 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
   // form's rounding is processed again with every sweep in the expm1 form (rare)
   bool force_acc = false;
   // unsigned: n_rows < 2^31 and the counter stays below n_rows + grid
-  const unsigned int n_rows = static_cast<unsigned int>(P.n_rows);
+  const unsigned int n_rows = static_cast<unsigned int>(P->n_rows);
   for (;;) {
+    P = kernel_args<CoupleParams>();
     if (!taken) {
-      if (B.tid == 0) sh.next = gridDim.x + take_index(P.next_row);
+      if (B.tid == 0) sh.next = gridDim.x + take_index(P->next_row);
       __syncthreads();
       ru = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)));
     }
     if (ru >= n_rows) break;
-    const bool ahead = P.next_row == nullptr || ru + 2 * gridDim.x < n_rows;
+    const bool ahead = P->next_row == nullptr || ru + 2 * gridDim.x < n_rows;
     const bool take_now = ahead && !force_acc;
     taken = ahead;
     const int64_t r = static_cast<int64_t>(ru);
-    const T* srow = static_cast<const T*>(P.s) + r * P.stride;
-    const T* trow = static_cast<const T*>(P.t) + r * P.stride;
-    G* grow = GRAD ? static_cast<G*>(P.grad) + r * P.grad_stride : nullptr;
-    const uint64_t g = static_cast<uint64_t>(P.row_offset + r);
-    const float M = (ROUTE && P.valid) ? (P.valid[r] ? 1.0f : 0.0f) : 1.0f;
+    const T* srow = static_cast<const T*>(P->s) + r * P->stride;
+    const T* trow = static_cast<const T*>(P->t) + r * P->stride;
+    G* grow = GRAD ? static_cast<G*>(P->grad) + r * P->grad_stride : nullptr;
+    const uint64_t g = static_cast<uint64_t>(P->row_offset + r);
+    const float M = (ROUTE && P->valid) ? (P->valid[r] ? 1.0f : 0.0f) : 1.0f;
 
-    const bool sample_target = ROUTE && P.target_mode == SAKI_TARGET_SAMPLE;
+    const bool sample_target = ROUTE && P->target_mode == SAKI_TARGET_SAMPLE;
     // while wave 0 combines the sums: the proposal's chunk race on the other
     // waves, the accept uniform and the next index on a lane of the last one
     auto idle = [&]() {
@@ -83,10 +85,10 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       const bool last = B.tid == NT - WAVE;
       const bool take = last && take_now;
       unsigned int nx = n_rows;
-      if (take && P.next_row) nx = gridDim.x + take_index(P.next_row);
+      if (take && P->next_row) nx = gridDim.x + take_index(P->next_row);
       double key;
       int idx;
-      wave_chunk_race(nch, (B.wave - 1) * WAVE + B.lane, (NW - 1) * WAVE, P.seed, PROP_CHUNK, g, [&](int c) {
+      wave_chunk_race(nch, (B.wave - 1) * WAVE + B.lane, (NW - 1) * WAVE, P->seed, PROP_CHUNK, g, [&](int c) {
         return static_cast<double>(sh.chunk_a[c]) * LN2_D + log(static_cast<double>(sh.chunk_b[c]));
       }, &key, &idx);
       if (B.lane == 0) {
@@ -95,33 +97,34 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       }
       if (last) {
         if (take) sh.next = nx;
-        sh.u = philox_uniform(P.seed, ACCEPT, g, 0);
+        sh.u = philox_uniform(P->seed, ACCEPT, g, 0);
       }
     };
-    const RowStats& R = stats_sweep<T, NT, true, K34>(B, srow, trow, V, P.lam_mid, true, sample_target, idle);
+    const RowStats& R = stats_sweep<T, NT, true, K34>(B, srow, trow, V, P->lam_mid, true, sample_target, idle);
     if (ahead) ru = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)));
+    P = kernel_args<CoupleParams>();
     if (uniform(!R.finite)) {
       if (GRAD) fill_row<G, NT>(B.wave, B.lane, grow, V, M != 0.0f ? nanf_() : 0.0f);
       if (B.tid == 0) {
-        const saki_couple_out& o = P.out;
-        if (o.lambda) o.lambda[r] = nanf_();
-        if (o.kl) o.kl[r] = nanf_();
-        if (o.tv) o.tv[r] = nanf_();
-        if (o.accept_prob) o.accept_prob[r] = nanf_();
-        if (o.margin) o.margin[r] = nanf_();
-        if (o.logp_token) o.logp_token[r] = nanf_();
-        if (o.logt_token) o.logt_token[r] = nanf_();
-        if (o.logq_token) o.logq_token[r] = nanf_();
-        if (o.proposal) o.proposal[r] = -1;
-        if (o.token) o.token[r] = -1;
-        if (o.teacher_argmax) o.teacher_argmax[r] = -1;
-        if (o.target) o.target[r] = -1;
-        if (o.corrected) o.corrected[r] = 0;
-        if (o.row_status) o.row_status[r] = SAKI_ROW_NONFINITE;
+        const auto* Q = kernel_args<CoupleParams>();
+        if (Q->out.lambda) Q->out.lambda[r] = nanf_();
+        if (Q->out.kl) Q->out.kl[r] = nanf_();
+        if (Q->out.tv) Q->out.tv[r] = nanf_();
+        if (Q->out.accept_prob) Q->out.accept_prob[r] = nanf_();
+        if (Q->out.margin) Q->out.margin[r] = nanf_();
+        if (Q->out.logp_token) Q->out.logp_token[r] = nanf_();
+        if (Q->out.logt_token) Q->out.logt_token[r] = nanf_();
+        if (Q->out.logq_token) Q->out.logq_token[r] = nanf_();
+        if (Q->out.proposal) Q->out.proposal[r] = -1;
+        if (Q->out.token) Q->out.token[r] = -1;
+        if (Q->out.teacher_argmax) Q->out.teacher_argmax[r] = -1;
+        if (Q->out.target) Q->out.target[r] = -1;
+        if (Q->out.corrected) Q->out.corrected[r] = 0;
+        if (Q->out.row_status) Q->out.row_status[r] = SAKI_ROW_NONFINITE;
         if (ROUTE) {
           const float l = (M != 0.0f) ? nanf_() : 0.0f;
-          if (P.row_loss) P.row_loss[r] = l;
-          if (P.scaled_loss) P.scaled_loss[r] = static_cast<double>(l);
+          if (Q->row_loss) Q->row_loss[r] = l;
+          if (Q->scaled_loss) Q->scaled_loss[r] = static_cast<double>(l);
         }
       }
       force_acc = false;
@@ -141,13 +144,13 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     // start point while wave 1 draws the proposal z ~ p in the chunk that won
     // the chunk race, which leaves the other waves' issue slots to the other
     // workgroup of the CU; the results go through LDS (plan).
-    const bool end_first = R.kl1_est <= 1.05 * P.eps + 1e-5;
+    const bool end_first = R.kl1_est <= 1.05 * P->eps + 1e-5;
     if (B.wave == 0) {
-      bool fu = !force_acc && P.eps > 0.0 && R.dmin != R.dmax;
+      bool fu = !force_acc && P->eps > 0.0 && R.dmin != R.dmax;
       StartPoint S0;
       S0.lam = 1.0; S0.A = R.lse_t - R.lse_s - static_cast<double>(R.c); S0.herm = true;
       if (fu) {
-        if (!end_first) S0 = start_point(R, P.eps);
+        if (!end_first) S0 = start_point(R, P->eps);
         const double top = S0.lam * (static_cast<double>(R.dmax) - static_cast<double>(R.c));
         fu = S0.herm && top <= 56.0 && (top - S0.A) * static_cast<double>(LOG2E) <= 56.0;
       }
@@ -158,7 +161,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     } else if (B.wave == 1) {
       float ws, wt;
       const int pc = race_winner(sh);
-      const int zz = wave_elem_race<T>(srow, trow, pc < nch ? pc : 0, V, B.lane, P.seed, PROP_ELEM, g,
+      const int zz = wave_elem_race<T>(srow, trow, pc < nch ? pc : 0, V, B.lane, P->seed, PROP_ELEM, g,
                                        [](float sv, float, int) { return sv; }, &ws, &wt);
       if (B.lane == 0) {
         plan.z = zz;
@@ -181,7 +184,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     const double logt_z = static_cast<double>(tz) - R.lse_t;
     const double adv = logt_z - logp_z;
     auto coef_of = [&](bool corr) {
-      return ROUTE ? static_cast<float>(static_cast<double>(P.grad_scale) * M * (corr ? 1.0 : adv)) : 0.0f;
+      return ROUTE ? static_cast<float>(static_cast<double>(P->grad_scale) * M * (corr ? 1.0 : adv)) : 0.0f;
     };
     // the gradient's indicator at a correction: the teacher mode, or a draw
     // from pi by the same two-level race on its own streams (teacher chunk
@@ -192,13 +195,13 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     auto correction_target = [&]() {
       if (have_hot_c) return;
       have_hot_c = true;
-      const int ct = chunk_race<NT>(B, nch, P.seed, TS_CHUNK, g, [&](int c) {
+      const int ct = chunk_race<NT>(B, nch, P->seed, TS_CHUNK, g, [&](int c) {
         return static_cast<double>(sh.chunk_c[c]) * LN2_D + log(static_cast<double>(sh.chunk_d[c]));
       });
       const int cc = ct < nch ? ct : 0;
       const ElemFetch<T> ft = elem_fetch<T, NT>(srow, trow, cc, V, B.tid);
       float sv, tv;
-      const int vt = elem_pick<NT>(B, ft, cc, V, P.seed, TS_ELEM, g,
+      const int vt = elem_pick<NT>(B, ft, cc, V, P->seed, TS_ELEM, g,
                                    [&](float, float tl, int) { return tl; }, &sv, &tv);
       if (vt < V) {
         hot_c = vt;
@@ -238,10 +241,10 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       // peaked rows, whose TV the plain form would often leave too imprecise;
       // elsewhere a row whose TV turns out too small for the plain form is
       // processed again in the accurate forms (redo_accurate)
-      const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
+      const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P->eps < KL_ACCURATE) || R.pmax > P_PEAKED;
       tv_acc = facc;
-      const FusedSums FS = fused_sweep_any<T, G, NT, GRAD>(B, srow, trow, grow, V, FC, facc, Cg, coef_g, invS,
-                                                          Cg ? hot_c : z, Cg ? s_hot_c : sz, R.sum_s / R.shift);
+      FusedSums FS = fused_sweep_any<T, G, NT, GRAD>(B, srow, trow, grow, V, FC, facc, Cg, coef_g, invS,
+                                                          Cg ? hot_c : z, Cg ? s_hot_c : sz);
       // wave 0: lambda* from the node's model when it needs no sweep, the
       // accept decision there and TV from the fused sums; the other waves run
       // the residual's chunk race meanwhile where a correction is predicted
@@ -249,7 +252,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       if (B.wave == 0) {
         FC.set_node();
         const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-        const LamResult L0 = lambda_search_with(R, P.eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
+        const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
                                                 true, E0, facc, true);
         int state = -1, C0 = 0, redo = 0;
         double alpha0 = 0.0;
@@ -274,7 +277,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
           plan.redo = redo;
         }
       } else if (Cg) {
-        le0 = res_race_begin<NT>(B, nch, P.seed, g);
+        le0 = res_race_begin<NT>(B, nch, P->seed, g);
       }
       __syncthreads();
       const int state = __builtin_amdgcn_readfirstlane(plan.state);
@@ -295,7 +298,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
             const double hx = plan.FF.hmax * LN2_D;
             const double hb = hx * (1.0 + hx) * 1.02 + 2e-6;
             res_chunk = __builtin_amdgcn_readfirstlane(
-                res_race_end<NT>(B, nch, P.seed, g, le0, hb, plan.FF.flip));
+                res_race_end<NT>(B, nch, P->seed, g, le0, hb, plan.FF.flip));
             if (res_chunk < 0) {
               settled = false;
               res_chunk = nch;
@@ -308,7 +311,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       // lambda sweeps: from the fused sweep's node where its model did not
       // settle lambda*, else from the start
       const LamEval E0 = fused ? plan.E0 : LamEval{};
-      L = lambda_search_with(R, P.eps, [&](float lam, bool acc) {
+      L = lambda_search_with(R, P->eps, [&](float lam, bool acc) {
         return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc);
       }, force_acc, 0.0f, fused, E0, tv_acc);
       F = final_const(R, L, force_acc);
@@ -325,7 +328,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
     if (!settled) {
       TV = final_sweep_any<T, G, NT, GRAD>(B, srow, trow, grow, V, F, C, coef, hot, s_hot);
       if (C) {
-        res_chunk = chunk_race<NT>(B, nch, P.seed, RES_CHUNK, g, [&](int c) {
+        res_chunk = chunk_race<NT>(B, nch, P->seed, RES_CHUNK, g, [&](int c) {
           const float m = sh.chunk_a[c];
           return m > 0.0f ? log(static_cast<double>(m)) : -__builtin_huge_val();
         });
@@ -350,7 +353,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       if (c1 < nch) {
         const ElemFetch<T> fr = elem_fetch<T, NT>(srow, trow, c1, V, B.tid);
         float sw, tw;
-        const int yc = elem_pick<NT>(B, fr, c1, V, P.seed, RES_ELEM, g, [&](float sv, float tv, int) {
+        const int yc = elem_pick<NT>(B, fr, c1, V, P->seed, RES_ELEM, g, [&](float sv, float tv, int) {
           float p;
           const float w = res_weight_any(sv, tv, F, &p);
           return w > 0.0f ? flog2(w) * LN2 : -finf();
@@ -367,21 +370,21 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
       const double logp_y = static_cast<double>(sy) - R.lse_s;
       const double logt_y = static_cast<double>(ty) - R.lse_t;
       const double logq_y = logp_y + L.log_ratio(sy, ty);
-      const saki_couple_out& o = P.out;
-      if (o.lambda) o.lambda[r] = L.lam;
-      if (o.kl) o.kl[r] = static_cast<float>(L.KL);
-      if (o.tv) o.tv[r] = static_cast<float>(TV);
-      if (o.accept_prob) o.accept_prob[r] = static_cast<float>(alpha);
-      if (o.margin) o.margin[r] = static_cast<float>(fabs(u - alpha));
-      if (o.logp_token) o.logp_token[r] = static_cast<float>(logp_y);
-      if (o.logt_token) o.logt_token[r] = static_cast<float>(logt_y);
-      if (o.logq_token) o.logq_token[r] = static_cast<float>(logq_y);
-      if (o.proposal) o.proposal[r] = z;
-      if (o.token) o.token[r] = y;
-      if (o.teacher_argmax) o.teacher_argmax[r] = R.vstar;
-      if (o.target) o.target[r] = hot;
-      if (o.corrected) o.corrected[r] = C ? 1 : 0;
-      if (o.row_status) o.row_status[r] = SAKI_ROW_OK;
+      const auto* Q = kernel_args<CoupleParams>();
+      if (Q->out.lambda) Q->out.lambda[r] = L.lam;
+      if (Q->out.kl) Q->out.kl[r] = static_cast<float>(L.KL);
+      if (Q->out.tv) Q->out.tv[r] = static_cast<float>(TV);
+      if (Q->out.accept_prob) Q->out.accept_prob[r] = static_cast<float>(alpha);
+      if (Q->out.margin) Q->out.margin[r] = static_cast<float>(fabs(u - alpha));
+      if (Q->out.logp_token) Q->out.logp_token[r] = static_cast<float>(logp_y);
+      if (Q->out.logt_token) Q->out.logt_token[r] = static_cast<float>(logt_y);
+      if (Q->out.logq_token) Q->out.logq_token[r] = static_cast<float>(logq_y);
+      if (Q->out.proposal) Q->out.proposal[r] = z;
+      if (Q->out.token) Q->out.token[r] = y;
+      if (Q->out.teacher_argmax) Q->out.teacher_argmax[r] = R.vstar;
+      if (Q->out.target) Q->out.target[r] = hot;
+      if (Q->out.corrected) Q->out.corrected[r] = C ? 1 : 0;
+      if (Q->out.row_status) Q->out.row_status[r] = SAKI_ROW_OK;
       if (ROUTE) {
         double l = 0.0;
         if (M != 0.0f) {
@@ -392,8 +395,8 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams P) {
             l = -adv * logp_z;
           }
         }
-        if (P.row_loss) P.row_loss[r] = static_cast<float>(l);
-        if (P.scaled_loss) P.scaled_loss[r] = static_cast<double>(P.grad_scale) * l;
+        if (Q->row_loss) Q->row_loss[r] = static_cast<float>(l);
+        if (Q->scaled_loss) Q->scaled_loss[r] = static_cast<double>(Q->grad_scale) * l;
       }
     }
   }

@@ -1571,13 +1571,14 @@ struct FusedConst {
 // Valid on wave 0, which alone settles the row.
 struct FusedSums {
   double v[4];   // W, S1, S2, S3 (moments of y, relative to 2^AL)
-  double T0, U0, U1, Bd;
+  double T0, U0, U1, Bd;  // U0: from D0 and sum p~ (fused_node)
+  double D0;              // sum sgn(r) p~ e
 };
 
 template <typename T, typename G, int NT, bool GRAD, int MODE, typename SH>
 __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                                  const FusedConst C, bool keep_res, float coef, float invS,
-                                                 int hot, float s_hot, double sum_pt) {
+                                                 int hot, float s_hot) {
   constexpr int NW = NT / WAVE;
   double acc[5] = {0, 0, 0, 0, 0};  // W, S1, S2, S3, R0 = sum |r|
   float D0 = 0.f, A1 = 0.f, Bd = 0.f;  // sum sgn(r) p~ e, sum p~ e |y|, the band's mass
@@ -1658,9 +1659,9 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
   FusedSums S;
 #pragma unroll
   for (int i = 0; i < 4; ++i) S.v[i] = v[i];
-  // sum p~ e over the row: sum p~ (the sums carry 2^d0, see shift_correction) + W
   S.T0 = 0.5 * (v[0] + v[4]);
-  S.U0 = 0.5 * (sum_pt + v[0] + v[5]);
+  S.D0 = v[5];
+  S.U0 = 0.0;
   S.U1 = 0.5 * (v[1] + v[6]);
   S.Bd = v[7];
   return S;
@@ -1669,10 +1670,10 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
 template <typename T, typename G, int NT, bool GRAD, typename SH>
 __device__ __forceinline__ FusedSums fused_sweep_any(Block<NT, SH>& B, const T* srow, const T* trow, G* grow, int V,
                                      const FusedConst& C, bool acc, bool keep_res, float coef, float invS, int hot,
-                                     float s_hot, double sum_pt) {
+                                     float s_hot) {
   if (acc)
-    return fused_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot, sum_pt);
-  return fused_sweep<T, G, NT, GRAD, FIN_FAST>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot, sum_pt);
+    return fused_sweep<T, G, NT, GRAD, FIN_ACC>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot);
+  return fused_sweep<T, G, NT, GRAD, FIN_FAST>(B, srow, trow, grow, V, C, keep_res, coef, invS, hot, s_hot);
 }
 
 // The dominant entry's term of the fused sweep's W in the plain form: its
@@ -1699,11 +1700,13 @@ __device__ __forceinline__ double dominant_fix_fused(float s, float t, const Fus
 // whose node only settles lambda* = 1).
 // acc: the sweep took the expm1 form (else the dominant entry's term of W is
 // taken exactly).
-__device__ __forceinline__ LamEval fused_node(const RowStats& R, const FusedSums& S, const FusedConst& C, bool end_first,
+__device__ __forceinline__ LamEval fused_node(const RowStats& R, FusedSums& S, const FusedConst& C, bool end_first,
                                      bool acc) {
   const double corr = R.shift;
   const double w = (S.v[0] + (acc ? 0.0 : dominant_fix_fused(R.ms, R.t_smax, C))) * corr;
   const double S0 = R.sum_s + w;
+  // U0 = (sum p~ e + D0) / 2, with sum p~ = sum_s / shift (2 - shift: 1e-12)
+  S.U0 = 0.5 * (R.sum_s * (2.0 - R.shift) + S.v[0] + S.D0);
   // moments of y under q_lam, then those of X = (y + AL) / lam; x = X ln 2
   const double r0 = corr / S0;
   const double m1 = S.v[1] * r0, m2 = S.v[2] * r0, m3 = S.v[3] * r0;

@@ -247,8 +247,8 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         FC.set_y();
         const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
         tv_acc = facc;
-        const FusedSums FS = fused_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, FC, facc, reject_g,
-                                                                  0.0f, 0.0f, -1, 0.0f, R.sum_s / R.shift);
+        FusedSums FS = fused_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, FC, facc, reject_g,
+                                                                  0.0f, 0.0f, -1, 0.0f);
         double le0 = 0.0;
         if (B.wave == 0) {
           FC.set_node();
