@@ -58,9 +58,14 @@ constexpr int PROBE_SEL_CAP = NT;
 static_assert(PROBE_SEL_CAP >= SAKI_MAX_PROBE_K, "the gathered set holds the Top-k");
 // Rows of up to PROBE_MAXC chunks keep each chunk's largest teacher logit.
 constexpr int PROBE_MAXC = 512;
-// Workgroups per CU: three, so that while some are in a row's serial steps
-// (reductions, the threshold, the gathering) the others stream.
-constexpr int PROBE_WG_PER_CU = 3;
+// Workgroups per CU: four (128 VGPRs, no spills for bf16), so that while some are
+// in a row's serial steps (reductions, the threshold, the gathering) the others
+// stream, and 1,000 rows are one round.  The sweep is bound by VALU issue and
+// HBM together: its maxima and the finiteness of its entries take one
+// instruction an entry and array instead of three.  V = 151,936 bf16, k = 16,
+// rows 256 / 1,000 / 4,096: 64 / 155 / 502 us with three and isfinite per entry,
+// 55 / 134 / 484 us now.
+constexpr int PROBE_WG_PER_CU = 4;
 
 struct ProbeShared {
   double red_d[NT / WAVE][RED_MAX];
@@ -142,21 +147,23 @@ __global__ __launch_bounds__(NT, PROBE_WG_PER_CU) void probe_kernel(ProbeParams 
     float Ms = -finf(), Mt = -finf();
     double Ss = 0, Sa = 0, St = 0, Td = 0;
     float Lt = -finf();  // this thread's largest teacher logit
-    bool finite = true;
+    float lo = finf();     // the smallest entry of s and t
     for_chunks<T, NW>(srow, trow, V, B.wave, B.lane,
                       [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                         constexpr bool TAIL = decltype(tail)::value;
+                        // maxima of s and t and the smallest entry of both, in
+                        // chains of three-input operations; the row is finite
+                        // when that is above -inf and the maxima and the sums
+                        // are finite (a NaN entry makes a sum NaN)
                         float ls = -finf(), lt = -finf();
-                        bool fin = true;
 #pragma unroll
-                        for (int e = 0; e < EPL; ++e) {
-                          if (!TAIL || ((vm >> e) & 1u)) {
-                            ls = fmaxf(ls, s[e]);
-                            lt = fmaxf(lt, t[e]);
-                            fin = fin && isfinite(s[e]) && isfinite(t[e]);
-                          }
+                        for (int e = 0; e < EPL; e += 2) {
+                          const bool v0 = !TAIL || ((vm >> e) & 1u), v1 = !TAIL || ((vm >> (e + 1)) & 1u);
+                          ls = max3_raw(ls, v0 ? s[e] : -finf(), v1 ? s[e + 1] : -finf());
+                          lt = max3_raw(lt, v0 ? t[e] : -finf(), v1 ? t[e + 1] : -finf());
+                          lo = min3_raw(lo, v0 ? s[e] : finf(), v0 ? t[e] : finf());
+                          lo = min3_raw(lo, v1 ? s[e + 1] : finf(), v1 ? t[e + 1] : finf());
                         }
-                        finite = finite && !wave_any(!fin);
                         Lt = fmaxf(Lt, lt);
                         const float cmt = wave_max(lt);
                         if (c < PROBE_MAXC && B.lane == 0) sh.chunk_tmax[c] = cmt;
@@ -192,15 +199,16 @@ __global__ __launch_bounds__(NT, PROBE_WG_PER_CU) void probe_kernel(ProbeParams 
                       });
     // combine the waves (rescaled to the block maxima)
     const float ms = B.max(Ms), mt = B.max(Mt);
+    bool finite;
     {
       const double fs = (Ms == -finf()) ? 0.0 : static_cast<double>(fexp2((Ms - ms) * LOG2E));
       const double ft = (Mt == -finf()) ? 0.0 : static_cast<double>(fexp2((Mt - mt) * LOG2E));
       const double dm = static_cast<double>(ms) - Ms;
       double v[5] = {Ss * fs, (Ms == -finf()) ? 0.0 : fs * (Sa - dm * Ss), St * ft, Td * ft,
-                     finite ? 0.0 : 1.0};
+                     lo > -finf() ? 0.0 : 1.0};
       B.sum(v);
       Ss = v[0]; Sa = v[1]; St = v[2]; Td = v[3];
-      finite = v[4] == 0.0;
+      finite = v[4] == 0.0 && ms < finf() && mt < finf() && isfinite(Ss) && isfinite(St);
     }
     const double lse_s = static_cast<double>(ms) + log(Ss);
     const double lse_t = static_cast<double>(mt) + log(St);
