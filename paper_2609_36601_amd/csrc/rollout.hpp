@@ -6,8 +6,7 @@
 // ---------------------------------------------------------------------------
 // Draft sampling, z ~ p = softmax(s), by the two-level exponential race on the
 // proposal streams.  One workgroup per row: one read of the row for the chunk
-// masses (each wave owns whole chunks, shifted by the chunk's own maximum, so
-// no running maximum is needed: the race compares ln W_c, and a per-chunk
+// masses (each wave owns whole chunks; the race compares ln W_c, and a chunk's
 // shift is carried in the key), then the entry race inside the winning chunk
 // re-reads one chunk.
 // ---------------------------------------------------------------------------
@@ -23,63 +22,156 @@ struct SampleParams {
   uint8_t* status;
 };
 
-// Mass of one chunk from this lane's 16 entries s (valid mask vm): the chunk's
-// maximum and the sum of 2^((s - max) log2 e) over the wave.
-template <bool TAIL>
-__device__ __forceinline__ bool chunk_mass(const float* s, uint32_t vm, float* ref, float* sum) {
-  float m = -finf();
+// What bounds it: with fewer rows than CUs the row's one CU (one exponential and
+// five more VALU instructions an entry, ~7 us for 151,936 entries, and the
+// races' serial steps); with more, HBM.  Eight waves per workgroup, each with
+// SAMPLE_DEPTH chunks in flight, hide the load latency, and two workgroups per
+// CU each other's serial steps.  Sixteen waves were no faster on long rows and
+// 1-2 us slower below 32,000 entries.  Rows are not split over CUs: the call
+// has no workspace to exchange partial races through.  V = 151,936 bf16, rows
+// 16 / 256 / 1,000: 20.5 / 21.6 / 79 us with one chunk ahead, the maximum and
+// finiteness of each chunk taken separately and one workgroup per CU, 15.1 /
+// 18.5 / 56 us now; V = 32,000, 1,000 rows: 36 -> 22 us.
+constexpr int SAMPLE_NT = 512;
+constexpr int SAMPLE_WG_PER_CU = 2;
+template <typename T>
+constexpr int SAMPLE_DEPTH = sizeof(T) == 2 ? 4 : 2;
+
+constexpr float SAMPLE_MAX_TOP = 1e38f;
+
+// The chunk masses of any row: every chunk against its own maximum by
+// differences (chunk c keeps that maximum, in natural units, and the sum of
+// e^(s - max)), every entry's finiteness taken.  Returns whether all are finite.
+template <typename T, int SNT, typename BL>
+__device__ __forceinline__ bool sample_masses_any(BL& B, const T* srow, int V) {
+  const int nch = (V + CHUNK - 1) / CHUNK;
   bool fin = true;
+  for (int c = B.wave; c < nch; c += SNT / WAVE) {
+    float x[EPL];
+    uint32_t vm;
+    load_lane<T, true>(srow, c, B.lane, V, x, &vm);
+    float m = -finf();
 #pragma unroll
-  for (int e = 0; e < EPL; ++e)
-    if (!TAIL || ((vm >> e) & 1u)) {
-      m = fmaxf(m, s[e]);
-      fin = fin && (s[e] - s[e] == 0.0f);  // false for NaN and +-inf
+    for (int e = 0; e < EPL; ++e)
+      if ((vm >> e) & 1u) {
+        m = fmaxf(m, x[e]);
+        fin = fin && (x[e] - x[e] == 0.0f);  // false for NaN and +-inf
+      }
+    const float cm = wave_max(m);
+    float acc = 0.0f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e)
+      if ((vm >> e) & 1u) acc += fexp2((x[e] - cm) * LOG2E);
+    const float sum = wave_sum(acc);
+    if (B.lane == 0) {
+      B.sh.chunk_a[c] = cm;
+      B.sh.chunk_b[c] = sum;
     }
-  const float cm = wave_max(m);
-  float acc = 0.0f;
-#pragma unroll
-  for (int e = 0; e < EPL; ++e)
-    if (!TAIL || ((vm >> e) & 1u)) acc += fexp2((s[e] - cm) * LOG2E);
-  *ref = cm;
-  *sum = wave_sum(acc);
-  return fin;
+  }
+  return B.max(fin ? 0.0f : 1.0f) == 0.0f;
 }
 
-// One workgroup of SNT = 512 threads (eight waves) per row and one workgroup
-// per CU: rollout batches are a few hundred rows, so a row's sweep is spread
-// over more waves, each streaming its chunks with the next chunk's loads in
-// flight (the row engine's chunk loop, on the one array).
-constexpr int SAMPLE_NT = 512;
-
 template <typename T>
-__global__ __launch_bounds__(SAMPLE_NT, 1) void sample_kernel(SampleParams P) {
-  constexpr int SNT = SAMPLE_NT;
+__global__ __launch_bounds__(SAMPLE_NT, SAMPLE_WG_PER_CU) void sample_kernel(SampleParams P) {
+  constexpr int SNT = SAMPLE_NT, D = SAMPLE_DEPTH<T>;
   __shared__ RowShared<SNT> sh;
   Block<SNT> B(sh);
   constexpr int NW = SNT / WAVE;
   const int V = P.V;
-  const int nch = (V + CHUNK - 1) / CHUNK;
+  const int nch = (V + CHUNK - 1) / CHUNK, nfull = V / CHUNK;
+  const int nw = B.wave < nfull ? (nfull - 1 - B.wave) / NW + 1 : 0;  // this wave's full chunks
   for (int64_t r = blockIdx.x; r < P.n_rows; r += gridDim.x) {
     const T* srow = static_cast<const T*>(P.s) + r * P.stride;
     const uint64_t g = static_cast<uint64_t>(P.row_offset + r * P.row_step);
+    // chunk i of the wave; past its last one the last is read again (unused),
+    // so that every load is issued on every path
+    auto load = [&](Frag<T>& f, int i) { frag_load<false>(f, srow, B.wave + min(i, nw - 1) * NW, B.lane); };
+    Frag<T> f[D];
+    if (nw > 0) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) load(f[j], j);
+    }
+    // ln E of this thread's chunk, while the first loads are in flight
+    double le = 0.0;
+    if (B.tid < nch) le = ln_exp_race(P.seed, PROP_CHUNK, g, B.tid);
+    // Exponents are relative to the wave's running maximum, as in the stats
+    // sweep: chunk c keeps (MsL, sum 2^(s log2 e - MsL)).  A row whose smallest
+    // entry is above -inf and whose maxima and sums are finite is finite (a NaN
+    // or +inf entry makes a chunk's sum NaN or infinite); any other, and one
+    // whose maximum times log2 e nears the end of the float range, goes through
+    // sample_masses_any.  MsL stays finite on a wave that has only met entries
+    // at the type's lowest value (masks): their sum is then 0.
+    float Ms = -finf(), MsL = -finf(), lo = finf();
     bool fin = true;
-    for_chunks1<T, NW>(srow, V, B.wave, B.lane, [&](auto tail, const float* s, uint32_t vm, int c) {
+    auto mass = [&](auto tail, const float* x, uint32_t vm, int c) {
       constexpr bool TAIL = decltype(tail)::value;
-      float ref, sum;
-      fin = chunk_mass<TAIL>(s, vm, &ref, &sum) && fin;
-      if (B.lane == 0) {
-        sh.chunk_a[c] = ref;
+      float ls = -finf();
+#pragma unroll
+      for (int e = 0; e < EPL; e += 2) {
+        const bool v0 = !TAIL || ((vm >> e) & 1u), v1 = !TAIL || ((vm >> (e + 1)) & 1u);
+        ls = max3_raw(ls, v0 ? x[e] : -finf(), v1 ? x[e + 1] : -finf());
+        lo = min3_raw(lo, v0 ? x[e] : finf(), v1 ? x[e + 1] : finf());
+      }
+      if (wave_any(ls > Ms)) {
+        Ms = wave_max(ls);
+        MsL = fmaxf(__fmul_rn(Ms, LOG2E), -FLT_MAX);
+      }
+      float acc = 0.0f;
+#pragma unroll
+      for (int e = 0; e < EPL; ++e) {
+        const float es = fexp2(fmaf(x[e], LOG2E, -MsL));
+        acc += (!TAIL || ((vm >> e) & 1u)) ? es : 0.0f;
+      }
+      fin = fin && acc < finf();  // false for NaN
+      const float sum = wave_sum_last(acc);
+      if (B.lane == WAVE - 1) {
+        sh.chunk_a[c] = MsL;
         sh.chunk_b[c] = sum;
       }
-    });
+    };
+    auto full = [&](const Frag<T>& fr, int i) {
+      float x[EPL];
+      frag_unpack(fr, x);
+      mass(std::integral_constant<bool, false>(), x, 0xffffu, B.wave + i * NW);
+    };
+    int i = 0;
+    for (; i + D <= nw; i += D) {
+#pragma unroll
+      for (int j = 0; j < D; ++j) {
+        const Frag<T> cur = f[j];
+        load(f[j], i + j + D);
+        full(cur, i + j);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < D - 1; ++j)
+      if (i + j < nw) full(f[j], i + j);
+    if ((V % CHUNK) != 0 && (nfull % NW) == B.wave) {
+      float x[EPL];
+      uint32_t vm;
+      load_lane<T, true>(srow, nfull, B.lane, V, x, &vm);
+      mass(std::integral_constant<bool, true>(), x, vm, nfull);
+    }
+    fin = fin && lo > -finf();
     // the block max is also the barrier that publishes the chunk masses
-    const bool finite = B.max(fin ? 0.0f : 1.0f) == 0.0f;
+    const float top = B.max(fin ? Ms : finf());
+    double unit = LN2_D;  // of the chunks' references
+    bool finite = true;
+    if (uniform(!(fabsf(top) < SAMPLE_MAX_TOP))) {
+      unit = 1.0;
+      finite = uniform(sample_masses_any<T, SNT>(B, srow, V));
+    }
     int z = -1;
     if (finite) {
-      const int c0 = chunk_race<SNT>(B, nch, P.seed, PROP_CHUNK, g, [&](int c) {
-        return static_cast<double>(sh.chunk_a[c]) + log(static_cast<double>(sh.chunk_b[c]));
-      });
-      z = elem_race<SNT>(B, c0 < nch ? c0 : 0, V, P.seed, PROP_ELEM, g,
+      double best = __builtin_huge_val();
+      int bi = 0x7fffffff;
+      for (int c = B.tid; c < nch; c += SNT) {
+        const double e = c == B.tid ? le : ln_exp_race(P.seed, PROP_CHUNK, g, c);
+        const double key = e - (static_cast<double>(sh.chunk_a[c]) * unit + log(static_cast<double>(sh.chunk_b[c])));
+        if (key < best) { best = key; bi = c; }
+      }
+      B.argmin(best, bi);
+      z = elem_race<SNT>(B, bi < nch ? bi : 0, V, P.seed, PROP_ELEM, g,
                          [&](int v) { return Loader<T>::load1(srow + v); });
       if (z >= V) z = -1;  // unreachable for finite rows: every chunk has a winner
     }

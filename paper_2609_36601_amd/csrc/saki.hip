@@ -6,6 +6,7 @@
 // the other's streaming sweeps.  The row engine (row_engine.hpp) runs the
 // stats sweep, the lambda sweeps and the final sweep over a row.
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <math.h>
 #include <stdint.h>
 #include <stdio.h>
@@ -564,9 +565,10 @@ saki_status saki_sample(const saki_rows* in, int64_t row_step, uint64_t seed, in
   P.seed = seed;
   P.token = token;
   P.status = row_status;
-  const int grid = static_cast<int>(std::min<int64_t>(P.n_rows, static_cast<int64_t>(cus)));
+  const int grid = static_cast<int>(std::min<int64_t>(P.n_rows, static_cast<int64_t>(cus) * saki::SAMPLE_WG_PER_CU));
   hipStream_t hs = static_cast<hipStream_t>(stream);
-  if (in->dtype == SAKI_BF16)
+  const bool bf16 = in->dtype == SAKI_BF16;
+  if (bf16)
     hipLaunchKernelGGL(saki::sample_kernel<uint16_t>, dim3(grid), dim3(saki::SAMPLE_NT), 0, hs, P);
   else
     hipLaunchKernelGGL(saki::sample_kernel<float>, dim3(grid), dim3(saki::SAMPLE_NT), 0, hs, P);

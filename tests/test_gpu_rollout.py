@@ -243,6 +243,42 @@ def test_sample_vocab_edges_and_large_keys(saki_lib, V):
     assert not ((tok != z_o) & ~near).any(), np.nonzero(tok != z_o)[0]
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("nch", [7, 8, 33, 40, 41])
+def test_sample_chunk_groups_and_extreme_logits(saki_lib, dtype, nch):
+    """Full-chunk counts around the groups of chunks in flight, with and without
+    a ragged end, and rows at the ends of the float range: masks of the type's
+    lowest value over whole chunks, over all but one entry and over the row, a
+    row near the largest value, and non-finite entries anywhere."""
+    for V in (nch * 1024, nch * 1024 - 700):
+        s = _random_rows(10, V, dtype, nch)
+        low = torch.finfo(dtype).min
+        s[1, :6 * 1024 - 50] = low
+        s[2] = low
+        s[2, V - 2] = 1.5
+        s[3] = low
+        s[4] = torch.tensor(3.2e38, dtype=dtype)
+        s[4, 17] = torch.tensor(3.3e38, dtype=dtype)
+        s[5, V - 1] = float("-inf")
+        s[6, 0] = float("nan")
+        s[7, V // 2] = float("inf")
+        s[8] = low
+        s[8, 3] = float("nan")
+        say(f"sample extremes V={V} {dtype}")
+        tok, status = saki_lib.sample(s, 77, row_offset=5, row_step=3)
+        torch.cuda.synchronize()
+        tok, status = tok.cpu().numpy(), status.cpu().numpy()
+        bad = [5, 6, 7, 8]
+        assert (tok[bad] == -1).all() and (status[bad] == binding.ROW_NONFINITE).all()
+        good = [0, 1, 2, 3, 4, 9]
+        assert (status[good] == 0).all() and ((tok[good] >= 0) & (tok[good] < V)).all()
+        # (a row of one value at the end of the range: its race keys tie in float)
+        good.remove(3)
+        z, gc, ge = zip(*[orollout.draft_tokens(f64(s[r:r + 1]), 77, 5 + 3 * r, 1) for r in good])
+        for i, r in enumerate(good):
+            assert tok[r] == z[i][0] or min(gc[i][0], ge[i][0]) < parity.MARGIN, (r, tok[r], z[i][0])
+
+
 @pytest.mark.parametrize("same", [False, True])
 def test_rollout_without_corrections(saki_lib, same):
     """eps = 0 (q = p), or a teacher equal to the student (q = pi = p): every
