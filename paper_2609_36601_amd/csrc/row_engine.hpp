@@ -125,13 +125,8 @@ struct Block {
   // Sums N doubles over the block; every thread gets the same bits.
   template <int N>
   __device__ __forceinline__ void sum(double (&v)[N]) {
-    static_assert(N <= RED_MAX, "block reduction wider than the LDS buffer");
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
-    if (lane == 0) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) sh.red_d[wave][i] = v[i];
-    }
+    static_assert(N <= RED_MAX && RED_MAX % 4 == 0, "block reduction wider than the LDS buffer");
+    wave_sums_post(v, sh.red_d[wave], lane);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -146,13 +141,8 @@ struct Block {
   // partial sums); a barrier must follow before the next reduction.
   template <int N>
   __device__ __forceinline__ void sum_wave0(double (&v)[N]) {
-    static_assert(N <= RED_MAX, "block reduction wider than the LDS buffer");
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
-    if (lane == 0) {
-#pragma unroll
-      for (int i = 0; i < N; ++i) sh.red_d[wave][i] = v[i];
-    }
+    static_assert(N <= RED_MAX && RED_MAX % 4 == 0, "block reduction wider than the LDS buffer");
+    wave_sums_post(v, sh.red_d[wave], lane);
     __syncthreads();
     if (wave == 0) {
 #pragma unroll
@@ -586,19 +576,6 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
   a.Q2 += q2;
 }
 
-// The block's maxima, rescaled sums, argmax and range of d.
-struct StatsBlock {
-  float ms, mt;
-  double Ss, S1, S2, S3, S4, St, T1, T2;
-  double Sm, Q1, Q2;  // middle-node sums (relative to the row's maxima)
-  double cs;          // shift_correction of s
-  double lm;          // the middle node, or 0
-  float tbest;
-  int tidx;
-  float t_smax;
-  float dmin, dmax;
-};
-
 // One exchange through LDS: each wave posts its sums (relative to its own
 // running maxima), maxima, argmax and range of d (stats_post); after a
 // barrier wave 0 combines the waves in a fixed order (stats_combine; every lane
@@ -608,115 +585,85 @@ __device__ __forceinline__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
   double v[11] = {a.Ss, static_cast<double>(a.S1), static_cast<double>(a.S2), static_cast<double>(a.S3),
                   static_cast<double>(a.S4), a.St, static_cast<double>(a.T1), static_cast<double>(a.T2),
                   a.Sm, static_cast<double>(a.Q1), static_cast<double>(a.Q2)};
-#pragma unroll
-  for (int i = 0; i < 11; ++i) v[i] = wave_sum(v[i]);
   const float wdmin = -wave_max(-a.dmin);
   const float wdmax = wave_max(a.dmax);
+  wave_sums_post(v, B.sh.red_d[B.wave], B.lane);  // entries 0 .. 11
   if (B.lane == 0) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) B.sh.red_d[B.wave][i] = v[i];
-    B.sh.red_d[B.wave][8] = static_cast<double>(a.MsL);
-    B.sh.red_d[B.wave][9] = static_cast<double>(a.MtL);
+    B.sh.red_d[B.wave][12] = static_cast<double>(a.MsL);
+    B.sh.red_d[B.wave][13] = static_cast<double>(a.MtL);
+    B.sh.red_d[B.wave][14] = static_cast<double>(a.t_smax);
     B.sh.red_f[B.wave][0] = a.Ms;
     B.sh.red_f[B.wave][1] = a.Mt;
     B.sh.red_f[B.wave][2] = wdmin;
     B.sh.red_f[B.wave][3] = wdmax;
     B.sh.red_i[B.wave][0] = a.tidx;
-    B.sh.red_d[B.wave][10] = static_cast<double>(a.t_smax);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) B.sh.red_d[B.wave][11 + i] = v[8 + i];
   }
 }
 
+// Row statistics from the waves' posts, on one wave.  Sum i (in the order of
+// stats_post) is combined on lane i, and the exponentials, logarithms and
+// reciprocals are taken there too, side by side: the wave is alone here, and its
+// dependent double-precision steps are what every row waits for.
 template <int NT, typename SH>
-__device__ __forceinline__ StatsBlock stats_combine(Block<NT, SH>& B, float kLm) {
+__device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float kLm, bool k34) {
   constexpr int NW = NT / WAVE;
-  StatsBlock O;
-  O.ms = -finf();
-  O.mt = -finf();
-  O.dmin = finf();
-  O.dmax = -finf();
+  RowStats R;
+  R.ms = -finf();
+  R.mt = -finf();
+  R.dmin = finf();
+  R.dmax = -finf();
   for (int w = 0; w < NW; ++w) {
-    O.ms = fmaxf(O.ms, B.sh.red_f[w][0]);
-    O.mt = fmaxf(O.mt, B.sh.red_f[w][1]);
-    O.dmin = fminf(O.dmin, B.sh.red_f[w][2]);
-    O.dmax = fmaxf(O.dmax, B.sh.red_f[w][3]);
+    R.ms = fmaxf(R.ms, B.sh.red_f[w][0]);
+    R.mt = fmaxf(R.mt, B.sh.red_f[w][1]);
+    R.dmin = fminf(R.dmin, B.sh.red_f[w][2]);
+    R.dmax = fmaxf(R.dmax, B.sh.red_f[w][3]);
   }
-  double acc[11] = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  float tb = -finf();
-  int ti = 0x7fffffff;
-  float st = -finf();
-  // each wave's sums are relative to 2^(its MsL): rescale to the block's
-  // msL = ms log2(e) rounded (the MsL of a wave holding the maximum), then
-  // remove that rounding (shift_correction)
-  const float msL = __fmul_rn(O.ms, LOG2E), mtL = __fmul_rn(O.mt, LOG2E);
+  R.tmax = -finf();
+  R.vstar = 0x7fffffff;
+  R.t_smax = -finf();
+  // each wave's sums are relative to 2^(its MsL) (sums of pi: MtL): rescale to
+  // the row's ML = m log2(e) rounded (the ML of a wave holding the maximum),
+  // then remove that rounding, 2^-d0 (shift_correction)
+  const int i = B.lane < 11 ? B.lane : 10;
+  const bool pi_sum = i >= 5 && i < 8;
+  const float m = pi_sum ? R.mt : R.ms, mL = __fmul_rn(m, LOG2E);
+  double acc = 0.0;
   for (int w = 0; w < NW; ++w) {
+    const float wM = B.sh.red_f[w][pi_sum ? 1 : 0];
+    const float wML = static_cast<float>(B.sh.red_d[w][pi_sum ? 13 : 12]);
+    const double f = (wM == -finf()) ? 0.0 : (wM == m) ? 1.0 : static_cast<double>(fexp2(__fsub_rn(wML, mL)));
+    acc += B.sh.red_d[w][i] * f;
     const float wMs = B.sh.red_f[w][0], wMt = B.sh.red_f[w][1];
-    const float wMsL = static_cast<float>(B.sh.red_d[w][8]), wMtL = static_cast<float>(B.sh.red_d[w][9]);
-    const double gs = (wMs == -finf()) ? 0.0 : (wMs == O.ms) ? 1.0 : static_cast<double>(fexp2(__fsub_rn(wMsL, msL)));
-    const double gt = (wMt == -finf()) ? 0.0 : (wMt == O.mt) ? 1.0 : static_cast<double>(fexp2(__fsub_rn(wMtL, mtL)));
-#pragma unroll
-    for (int i = 0; i < 5; ++i) acc[i] += B.sh.red_d[w][i] * gs;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) acc[8 + i] += B.sh.red_d[w][11 + i] * gs;
-#pragma unroll
-    for (int i = 5; i < 8; ++i) acc[i] += B.sh.red_d[w][i] * gt;
     const int wi = B.sh.red_i[w][0];
-    if (wMt > tb || (wMt == tb && wi < ti)) { tb = wMt; ti = wi; }
-    if (wMs == O.ms) st = fmaxf(st, static_cast<float>(B.sh.red_d[w][10]));
+    if (wMt > R.tmax || (wMt == R.tmax && wi < R.vstar)) { R.tmax = wMt; R.vstar = wi; }
+    if (wMs == R.ms) R.t_smax = fmaxf(R.t_smax, static_cast<float>(B.sh.red_d[w][14]));
   }
-  // 2^-d0 of the two shifts' roundings, side by side on two lanes (the middle
-  // node's weights carry the shift of s)
-  const double cc = shift_correction(B.lane == 0 ? O.ms : O.mt, B.lane == 0 ? msL : mtL);
-  const double cs = lane_d(cc, 0), ct = lane_d(cc, 1);
+  const double corr = shift_correction(m, mL);
+  acc *= corr;
   // The maximum's own term went into the sums as 2^d0 rounded to float (d0 =
   // the rounding of the shift, ~1e-6: a rounding of ~6e-8 next to 1); after
   // the shift correction it is exactly 1.  The log-probability of a dominant
   // entry (near 0 on a peaked row) needs that term exact.
-  const double dom_s = 1.0 - static_cast<double>(fexp2(fmaf(O.ms, LOG2E, -msL))) * cs;
-  const double dom_t = 1.0 - static_cast<double>(fexp2(fmaf(O.mt, LOG2E, -mtL))) * ct;
-  O.Ss = acc[0] * cs + dom_s; O.S1 = acc[1] * cs; O.S2 = acc[2] * cs; O.S3 = acc[3] * cs; O.S4 = acc[4] * cs;
-  O.St = acc[5] * ct + dom_t; O.T1 = acc[6] * ct; O.T2 = acc[7] * ct;
-  O.Sm = acc[8] * cs; O.Q1 = acc[9] * cs; O.Q2 = acc[10] * cs;
-  O.cs = cs;
-  // no middle node on a row whose weights there could leave the float range
-  O.lm = kLm > 0.0f && fabsf(kLm * (O.mt - O.ms)) < MID_MAX_SHIFT
-             ? static_cast<double>(kLm) / static_cast<double>(LOG2E) : 0.0;
-  O.tbest = tb;
-  O.tidx = ti;
-  O.t_smax = st;
-  return O;
-}
-
-// Row statistics from the (combined) block statistics, on one wave.  The three
-// logarithms are taken side by side, one per lane, and the quotients by one
-// reciprocal per sum (the last bit of a double): the wave is alone here, and
-// its dependent double-precision steps are what every row waits for.
-__device__ __forceinline__ RowStats row_stats_from(const StatsBlock& O, bool k34, int lane) {
-  RowStats R;
-  R.ms = O.ms;
-  R.mt = O.mt;
-  R.dmin = O.dmin;
-  R.dmax = O.dmax;
-  R.tmax = O.tbest;
-  R.vstar = O.tidx;
-  R.t_smax = O.t_smax;
-  R.sum_s = O.Ss;
-  R.shift = O.cs;
-  const double ln = log(lane == 0 ? O.Ss : lane == 1 ? O.St : O.Sm);
-  const double ln_s = lane_d(ln, 0), ln_t = lane_d(ln, 1), ln_m = lane_d(ln, 2);
+  if (i == 0 || i == 5) acc += 1.0 - static_cast<double>(fexp2(fmaf(m, LOG2E, -mL))) * corr;
+  const double ln = log(acc), inv = 1.0 / acc;
+  R.shift = lane_d(corr, 0);
+  R.sum_s = lane_d(acc, 0);
+  const double ln_s = lane_d(ln, 0), ln_t = lane_d(ln, 5), ln_m = lane_d(ln, 8);
+  const double is = lane_d(inv, 0), it = lane_d(inv, 5), im = lane_d(inv, 8);
   R.lse_s = static_cast<double>(R.ms) + ln_s;
   R.lse_t = static_cast<double>(R.mt) + ln_t;
-  const double inv = 1.0 / (lane == 0 ? O.Ss : lane == 1 ? O.St : O.Sm);
-  const double is = lane_d(inv, 0), it = lane_d(inv, 1), im = lane_d(inv, 2);
-  const double Ed = O.S1 * is, E2 = O.S2 * is, E3 = O.S3 * is, E4 = O.S4 * is;
+  const double Ed = lane_d(acc, 1) * is, E2 = lane_d(acc, 2) * is;
   R.var = fmax(E2 - Ed * Ed, 0.0);
   R.k34 = k34;
-  R.k3 = k34 ? E3 - 3.0 * Ed * E2 + 2.0 * Ed * Ed * Ed : 0.0;
-  R.k4 = k34 ? (E4 - 4.0 * Ed * E3 + 6.0 * Ed * Ed * E2 - 3.0 * Ed * Ed * Ed * Ed) - 3.0 * R.var * R.var : 0.0;
+  R.k3 = R.k4 = 0.0;
+  if (k34) {
+    const double E3 = lane_d(acc, 3) * is, E4 = lane_d(acc, 4) * is;
+    R.k3 = E3 - 3.0 * Ed * E2 + 2.0 * Ed * Ed * Ed;
+    R.k4 = (E4 - 4.0 * Ed * E3 + 6.0 * Ed * Ed * E2 - 3.0 * Ed * Ed * Ed * Ed) - 3.0 * R.var * R.var;
+  }
   R.mean_p = Ed;
-  R.mean_pi = O.T1 * it;
-  R.var_pi = fmax(O.T2 * it - R.mean_pi * R.mean_pi, 0.0);
+  R.mean_pi = lane_d(acc, 6) * it;
+  R.var_pi = fmax(lane_d(acc, 7) * it - R.mean_pi * R.mean_pi, 0.0);
   R.kl1_est = R.mean_pi - (R.lse_t - R.lse_s);
   R.pmax = is;  // exp(ms - lse_s)
   R.inv_s = is;
@@ -725,11 +672,13 @@ __device__ __forceinline__ RowStats row_stats_from(const StatsBlock& O, bool k34
   R.cL = R.c * LOG2E;
   // A at the middle node lm: sum_v p_v e^{lm x_v} = e^{-lm c} sum_m / sum_s,
   // with sum_m = sum e^{(s - ms) + lm d}; its derivatives are the mean and
-  // variance of x under the tilted weights
+  // variance of x under the tilted weights.  No middle node on a row whose
+  // weights there could leave the float range.
   {
-    const double lm = O.lm;
-    const double M1 = O.Q1 * im, M2 = O.Q2 * im;
-    R.lam_mid = lm > 0.0 && O.Sm > 0.0 && isfinite(M2) ? lm : 0.0;
+    const double lm = kLm > 0.0f && fabsf(kLm * (R.mt - R.ms)) < MID_MAX_SHIFT
+                          ? static_cast<double>(kLm) / static_cast<double>(LOG2E) : 0.0;
+    const double M1 = lane_d(acc, 9) * im, M2 = lane_d(acc, 10) * im;
+    R.lam_mid = lm > 0.0 && lane_d(acc, 8) > 0.0 && isfinite(M2) ? lm : 0.0;
     R.mid_A = ln_m - ln_s - lm * static_cast<double>(R.c);
     R.mid_A1 = M1 - static_cast<double>(R.c);
     R.mid_A2 = fmax(M2 - M1 * M1, 0.0);
@@ -760,7 +709,7 @@ __device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T
   stats_post(B, a);
   __syncthreads();
   if (B.wave == 0) {
-    const RowStats R = row_stats_from(stats_combine(B, MID ? kLm : 0.0f), K34, B.lane);
+    const RowStats R = stats_combine(B, MID ? kLm : 0.0f, K34);
     if (B.lane == 0) B.sh.rs.r = R;
   } else {
     idle();
