@@ -49,7 +49,7 @@ __global__ __launch_bounds__(256) void verify_end_kernel(VerifyParams P) {
   if (P.has_pp) {
     for (int jj = j + 1; jj < P.k; ++jj) {
       const int64_t r = b * P.k + jj;
-      write_skipped(P.pp, r, P.draft[r], SAKI_ROW_SKIPPED);
+      write_skipped(&P.pp, r, P.draft[r], SAKI_ROW_SKIPPED);
     }
   }
 }

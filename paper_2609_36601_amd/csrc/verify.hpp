@@ -53,53 +53,56 @@ __host__ __device__ inline int32_t stop_word(int j, bool eos, int corr) {
 __host__ __device__ inline int stop_pos(int32_t w) { return w >> 23; }
 static_assert(SAKI_MAX_BLOCK_K <= 64 && SAKI_MAX_VOCAB <= (1 << 21), "stop_word holds k and the vocabulary");
 
-__device__ inline void write_skipped(const saki_couple_out& o, int64_t r, int32_t draft, uint8_t status) {
-  if (o.lambda) o.lambda[r] = nanf_();
-  if (o.kl) o.kl[r] = nanf_();
-  if (o.tv) o.tv[r] = nanf_();
-  if (o.accept_prob) o.accept_prob[r] = nanf_();
-  if (o.margin) o.margin[r] = nanf_();
-  if (o.logp_token) o.logp_token[r] = nanf_();
-  if (o.logt_token) o.logt_token[r] = nanf_();
-  if (o.logq_token) o.logq_token[r] = nanf_();
-  if (o.proposal) o.proposal[r] = draft;
-  if (o.token) o.token[r] = -1;
-  if (o.teacher_argmax) o.teacher_argmax[r] = -1;
-  if (o.target) o.target[r] = -1;
-  if (o.corrected) o.corrected[r] = 0;
-  if (o.row_status) o.row_status[r] = status;
+// o: the per-position outputs, in the argument segment or elsewhere
+template <typename O>
+__device__ __forceinline__ void write_skipped(const O* o, int64_t r, int32_t draft, uint8_t status) {
+  if (o->lambda) o->lambda[r] = nanf_();
+  if (o->kl) o->kl[r] = nanf_();
+  if (o->tv) o->tv[r] = nanf_();
+  if (o->accept_prob) o->accept_prob[r] = nanf_();
+  if (o->margin) o->margin[r] = nanf_();
+  if (o->logp_token) o->logp_token[r] = nanf_();
+  if (o->logt_token) o->logt_token[r] = nanf_();
+  if (o->logq_token) o->logq_token[r] = nanf_();
+  if (o->proposal) o->proposal[r] = draft;
+  if (o->token) o->token[r] = -1;
+  if (o->teacher_argmax) o->teacher_argmax[r] = -1;
+  if (o->target) o->target[r] = -1;
+  if (o->corrected) o->corrected[r] = 0;
+  if (o->row_status) o->row_status[r] = status;
 }
 
 // VNT threads per workgroup: 256 (two workgroups per CU), or 512 (one per CU)
 // when a call has no more positions than CUs, so that each position's sweeps
 // are spread over eight waves.
 template <typename T, int KC, int VNT, bool K34>
-__global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyParams P) {
+__global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyParams) {
   using SH = RowShared<VNT, (KC > 0 ? CACHED_MAXC : MAX_CHUNKS), KC>;
   __shared__ SH sh;
   __shared__ RowPlan plan;
   Block<VNT, SH> B(sh);
-  const int V = P.V;
+  const auto* P = kernel_args<VerifyParams>();
+  const int V = P->V;
   const int nch = (V + CHUNK - 1) / CHUNK;
-  const saki_couple_out& o = P.pp;
-  const bool need_tv = P.has_pp && o.tv != nullptr;
+  const bool need_tv = P->has_pp && P->pp.tv != nullptr;
   // outputs that need lambda* at an accepted position
-  const bool need_lam = P.has_pp && (o.lambda || o.kl || o.tv || o.accept_prob || o.margin || o.logq_token);
+  const bool need_lam = P->has_pp && (P->pp.lambda || P->pp.kl || P->pp.tv || P->pp.accept_prob || P->pp.margin || P->pp.logq_token);
   // Thread 0 takes the next item that its block does not rule out and posts it
   // in LDS; readfirstlane makes it, and so the loop's exit, uniform in every
   // wave, so all threads reach the same barriers.  The counter only grows, so
   // every thread 0 reaches n_items and every loop ends.
   __shared__ long long next_i;
-  const long long n_items = P.n_blocks * P.k;
-  const unsigned int nb = static_cast<unsigned int>(P.n_blocks);
+  const long long n_items = P->n_blocks * P->k;
+  const unsigned int nb = static_cast<unsigned int>(P->n_blocks);
   for (;;) {
+    P = kernel_args<VerifyParams>();
     if (B.tid == 0) {
       long long i;
       for (;;) {
-        i = static_cast<long long>(take_index(P.next_item));
+        i = static_cast<long long>(take_index(P->next_item));
         if (i >= n_items) break;
         // a stale word only costs a position evaluated in vain
-        const int32_t w = __hip_atomic_load(P.accepted_len + i % nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const int32_t w = __hip_atomic_load(P->accepted_len + i % nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (stop_pos(w) >= static_cast<int>(i / nb)) break;
       }
       next_i = i;
@@ -112,32 +115,33 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
     if (item >= n_items) break;
     const int j = static_cast<int>(item / nb);
     const int64_t b = item % nb;
-    const int64_t r = b * P.k + j;
+    const int64_t r = b * P->k + j;
     // a position resolved in a plain form whose TV turns out too small for
     // that form's rounding is processed again with every sweep in the expm1
     // form (rare): force_acc is all that crosses the restart
     bool force_acc = false;
     for (;;) {
-      const T* srow = static_cast<const T*>(P.s) + r * P.stride;
-      const T* trow = static_cast<const T*>(P.t) + r * P.stride;
-      const uint64_t g = static_cast<uint64_t>(P.row_offset + r);
-      const int z = P.draft[r];
+      const T* srow = static_cast<const T*>(P->s) + r * P->stride;
+      const T* trow = static_cast<const T*>(P->t) + r * P->stride;
+      const uint64_t g = static_cast<uint64_t>(P->row_offset + r);
+      const int z = P->draft[r];
       if (uniform(z < 0 || z >= V)) {
         if (B.tid == 0) {
-          if (P.has_pp) write_skipped(o, r, z, SAKI_ROW_BAD_DRAFT);
-          atomicMin(P.accepted_len + b, stop_word(j, false, -1));
+          if (P->has_pp) write_skipped(&P->pp, r, z, SAKI_ROW_BAD_DRAFT);
+          atomicMin(P->accepted_len + b, stop_word(j, false, -1));
         }
         break;
       }
       // while wave 0 combines the sums, a lane of the last wave draws the uniform
       auto idle = [&]() {
-        if (B.tid == VNT - WAVE) sh.u = philox_uniform(P.seed, ACCEPT, g, 0);
+        if (B.tid == VNT - WAVE) sh.u = philox_uniform(P->seed, ACCEPT, g, 0);
       };
-      const RowStats& R = stats_sweep<T, VNT, true, K34>(B, srow, trow, V, P.lam_mid, false, false, idle);
+      const RowStats& R = stats_sweep<T, VNT, true, K34>(B, srow, trow, V, P->lam_mid, false, false, idle);
+      P = kernel_args<VerifyParams>();
       if (uniform(!R.finite)) {
         if (B.tid == 0) {
-          if (P.has_pp) write_skipped(o, r, z, SAKI_ROW_NONFINITE);
-          atomicMin(P.accepted_len + b, stop_word(j, false, -1));
+          if (P->has_pp) write_skipped(&P->pp, r, z, SAKI_ROW_NONFINITE);
+          atomicMin(P->accepted_len + b, stop_word(j, false, -1));
         }
         break;
       }
@@ -169,30 +173,30 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
           // Guards keep lh away from cancellations in the float sums.
           const double A1 = R.lse_t - R.lse_s - static_cast<double>(R.c);
           const double D1 = R.mean_pi - static_cast<double>(R.c);
-          const double num = R.kl1_est - P.eps, den = lm * D1 - R.mid_A - P.eps;
+          const double num = R.kl1_est - P->eps, den = lm * D1 - R.mid_A - P->eps;
           double g_hi = lr1;
-          if (num > 1e-2 * (fabs(R.kl1_est) + P.eps) &&
-              den > 1e-2 * (fabs(lm * D1) + fabs(R.mid_A) + P.eps)) {
+          if (num > 1e-2 * (fabs(R.kl1_est) + P->eps) &&
+              den > 1e-2 * (fabs(lm * D1) + fabs(R.mid_A) + P->eps)) {
             const double lh = fmax(lm, lm * num / den * (1.0 + 1e-3) + 1e-6);
             if (lh < 1.0) g_hi = lh * xz - (R.mid_A + (A1 - R.mid_A) * (lh - lm) / (1.0 - lm));
           }
           const double lo_side = fmin(0.0, gm), hi_side = fmin(gm, g_hi);
-          const double gb = (klm < P.eps * (1.0 - 1e-3)) ? hi_side : (klm > P.eps * (1.0 + 1e-3)) ? lo_side
+          const double gb = (klm < P->eps * (1.0 - 1e-3)) ? hi_side : (klm > P->eps * (1.0 + 1e-3)) ? lo_side
                                                                      : fmin(lo_side, hi_side);
           gmin = fmax(gmin, gb - 2e-6);
         }
         if (uniform(u < exp(gmin))) {
-          if (P.has_pp && B.tid == 0) {
-            if (o.logp_token) o.logp_token[r] = static_cast<float>(static_cast<double>(sz) - R.lse_s);
-            if (o.logt_token) o.logt_token[r] = static_cast<float>(static_cast<double>(tz) - R.lse_t);
-            if (o.proposal) o.proposal[r] = z;
-            if (o.token) o.token[r] = z;
-            if (o.teacher_argmax) o.teacher_argmax[r] = R.vstar;
-            if (o.target) o.target[r] = z;
-            if (o.corrected) o.corrected[r] = 0;
-            if (o.row_status) o.row_status[r] = SAKI_ROW_OK;
+          if (P->has_pp && B.tid == 0) {
+            if (P->pp.logp_token) P->pp.logp_token[r] = static_cast<float>(static_cast<double>(sz) - R.lse_s);
+            if (P->pp.logt_token) P->pp.logt_token[r] = static_cast<float>(static_cast<double>(tz) - R.lse_t);
+            if (P->pp.proposal) P->pp.proposal[r] = z;
+            if (P->pp.token) P->pp.token[r] = z;
+            if (P->pp.teacher_argmax) P->pp.teacher_argmax[r] = R.vstar;
+            if (P->pp.target) P->pp.target[r] = z;
+            if (P->pp.corrected) P->pp.corrected[r] = 0;
+            if (P->pp.row_status) P->pp.row_status[r] = SAKI_ROW_OK;
           }
-          if (P.eos >= 0 && z == P.eos && B.tid == 0) atomicMin(P.accepted_len + b, stop_word(j, true, -1));
+          if (P->eos >= 0 && z == P->eos && B.tid == 0) atomicMin(P->accepted_len + b, stop_word(j, true, -1));
           break;
         }
       }
@@ -204,16 +208,16 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       // behind another workgroup's, and the fused sweep's serial start and
       // settling cost more than the lambda sweep they replace: every position
       // takes the search there.
-      const bool end_first = R.kl1_est <= 1.05 * P.eps + 1e-5;
+      const bool end_first = R.kl1_est <= 1.05 * P->eps + 1e-5;
       if (B.wave == 0) {
         // the block's word again, loaded while the start point is computed: the
         // position is dropped when an earlier one has stopped the block meanwhile
-        const int32_t word = __hip_atomic_load(P.accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool fu = VNT == 256 && !force_acc && P.eps > 0.0 && R.dmin != R.dmax;
+        const int32_t word = __hip_atomic_load(P->accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        bool fu = VNT == 256 && !force_acc && P->eps > 0.0 && R.dmin != R.dmax;
         StartPoint S0;
         S0.lam = 1.0; S0.A = R.lse_t - R.lse_s - static_cast<double>(R.c); S0.herm = true;
         if (fu) {
-          if (!end_first) S0 = start_point(R, P.eps);
+          if (!end_first) S0 = start_point(R, P->eps);
           const double top = S0.lam * (static_cast<double>(R.dmax) - static_cast<double>(R.c));
           fu = S0.herm && top <= 56.0 && (top - S0.A) * static_cast<double>(LOG2E) <= 56.0;
         }
@@ -245,16 +249,16 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         FC.AL = A_g;
         FC.gsc = 0.0f;
         FC.set_y();
-        const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P.eps < KL_ACCURATE) || R.pmax > P_PEAKED;
+        const bool facc = (end_first ? R.kl1_est < 1.01 * KL_ACCURATE : P->eps < KL_ACCURATE) || R.pmax > P_PEAKED;
         tv_acc = facc;
         FusedSums FS = fused_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, FC, facc, reject_g,
                                                                   0.0f, 0.0f, -1, 0.0f);
         double le0 = 0.0;
         if (B.wave == 0) {
           FC.set_node();
-          const int32_t word = __hip_atomic_load(P.accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          const int32_t word = __hip_atomic_load(P->accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-          const LamResult L0 = lambda_search_with(R, P.eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
+          const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
                                                   true, E0, facc, true);
           int state = -1, C0 = 0;
           double alpha0 = 0.0;
@@ -282,7 +286,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
             plan.C = C0;
           }
         } else if (reject_g) {
-          le0 = res_race_begin<VNT>(B, nch, P.seed, g);
+          le0 = res_race_begin<VNT>(B, nch, P->seed, g);
         }
         __syncthreads();
         const int state = __builtin_amdgcn_readfirstlane(plan.state);
@@ -299,7 +303,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
               const double hx = plan.FF.hmax * LN2_D;  // expm1(x) <= x + x^2, as in the coupling kernel
               const double hb = hx * (1.0 + hx) * 1.02 + 2e-6;
               res_chunk = __builtin_amdgcn_readfirstlane(
-                  res_race_end<VNT>(B, nch, P.seed, g, le0, hb, plan.FF.flip));
+                  res_race_end<VNT>(B, nch, P->seed, g, le0, hb, plan.FF.flip));
               if (res_chunk < 0) {
                 settled = false;
                 res_chunk = nch;
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       }
       if (search) {
         const LamEval E0 = fused != 0 ? plan.E0 : LamEval{};
-        L = lambda_search_with(R, P.eps, [&](float lam, bool acc) {
+        L = lambda_search_with(R, P->eps, [&](float lam, bool acc) {
           return lam_sweep<T, VNT>(B, srow, trow, V, R, lam, acc);
         }, force_acc, 0.0f, fused != 0, E0, tv_acc);
         F = final_const(R, L, force_acc);
@@ -321,7 +325,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         TV = final_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, F, !accept, 0.0f, -1, 0.0f);
         tv_ok = true;
         if (!accept) {
-          res_chunk = chunk_race<VNT>(B, nch, P.seed, RES_CHUNK, g, [&](int c) {
+          res_chunk = chunk_race<VNT>(B, nch, P->seed, RES_CHUNK, g, [&](int c) {
             const float m = sh.chunk_a[c];
             return m > 0.0f ? log(static_cast<double>(m)) : -__builtin_huge_val();
           });
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         if (c1 < nch) {
           const ElemFetch<T> fr = elem_fetch<T, VNT>(srow, trow, c1, V, B.tid);
           float sw, tw;
-          const int yc = elem_pick<VNT>(B, fr, c1, V, P.seed, RES_ELEM, g, [&](float sv, float tv, int) {
+          const int yc = elem_pick<VNT>(B, fr, c1, V, P->seed, RES_ELEM, g, [&](float sv, float tv, int) {
             float p;
             const float w = res_weight_any(sv, tv, F, &p);
             return w > 0.0f ? flog2(w) * LN2 : -finf();
@@ -351,29 +355,30 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
           }
         }
       }
-      if (P.has_pp && B.tid == 0) {
+      P = kernel_args<VerifyParams>();
+      if (P->has_pp && B.tid == 0) {
         const double logp_y = static_cast<double>(sy) - R.lse_s;
         const double logt_y = static_cast<double>(ty) - R.lse_t;
-        if (o.lambda) o.lambda[r] = L.lam;
-        if (o.kl) o.kl[r] = static_cast<float>(L.KL);
-        if (o.tv) o.tv[r] = static_cast<float>(TV);
-        if (o.accept_prob) o.accept_prob[r] = static_cast<float>(alpha);
-        if (o.margin) o.margin[r] = static_cast<float>(fabs(u - alpha));
-        if (o.logp_token) o.logp_token[r] = static_cast<float>(logp_y);
-        if (o.logt_token) o.logt_token[r] = static_cast<float>(logt_y);
-        if (o.logq_token) o.logq_token[r] = static_cast<float>(logp_y + L.log_ratio(sy, ty));
-        if (o.proposal) o.proposal[r] = z;
-        if (o.token) o.token[r] = y;
-        if (o.teacher_argmax) o.teacher_argmax[r] = R.vstar;
-        if (o.target) o.target[r] = accept ? z : R.vstar;
-        if (o.corrected) o.corrected[r] = accept ? 0 : 1;
-        if (o.row_status) o.row_status[r] = SAKI_ROW_OK;
+        if (P->pp.lambda) P->pp.lambda[r] = L.lam;
+        if (P->pp.kl) P->pp.kl[r] = static_cast<float>(L.KL);
+        if (P->pp.tv) P->pp.tv[r] = static_cast<float>(TV);
+        if (P->pp.accept_prob) P->pp.accept_prob[r] = static_cast<float>(alpha);
+        if (P->pp.margin) P->pp.margin[r] = static_cast<float>(fabs(u - alpha));
+        if (P->pp.logp_token) P->pp.logp_token[r] = static_cast<float>(logp_y);
+        if (P->pp.logt_token) P->pp.logt_token[r] = static_cast<float>(logt_y);
+        if (P->pp.logq_token) P->pp.logq_token[r] = static_cast<float>(logp_y + L.log_ratio(sy, ty));
+        if (P->pp.proposal) P->pp.proposal[r] = z;
+        if (P->pp.token) P->pp.token[r] = y;
+        if (P->pp.teacher_argmax) P->pp.teacher_argmax[r] = R.vstar;
+        if (P->pp.target) P->pp.target[r] = accept ? z : R.vstar;
+        if (P->pp.corrected) P->pp.corrected[r] = accept ? 0 : 1;
+        if (P->pp.row_status) P->pp.row_status[r] = SAKI_ROW_OK;
       }
       if (B.tid == 0) {
         if (!accept)
-          atomicMin(P.accepted_len + b, stop_word(j, false, y));
-        else if (P.eos >= 0 && z == P.eos)
-          atomicMin(P.accepted_len + b, stop_word(j, true, -1));
+          atomicMin(P->accepted_len + b, stop_word(j, false, y));
+        else if (P->eos >= 0 && z == P->eos)
+          atomicMin(P->accepted_len + b, stop_word(j, true, -1));
       }
       break;
     }
