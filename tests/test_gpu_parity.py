@@ -437,6 +437,28 @@ def test_route_loss_standalone(saki_lib):
     assert np.max(np.abs(out["grad"].cpu().numpy() - grad)) <= parity.GRAD_ATOL
 
 
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1023, 1024, 1025, 7169, 8191, 8192, 8193, 20000])
+def test_loss_sum_row_counts(saki_lib, n):
+    """The sum of the row losses at row counts around its wave, its workgroup and
+    its group of loads in flight.  The sum is in double: it differs from the sum
+    of the returned row losses by their rounding to float, 2^-24 of each."""
+    g = torch.Generator(device=DEV).manual_seed(n)
+    s = torch.randn(n, 16, generator=g, device=DEV)
+    token = torch.randint(0, 16, (n,), generator=g, device=DEV, dtype=torch.int32)
+    corrected = (torch.rand(n, generator=g, device=DEV) < 0.3).to(torch.uint8)
+    adv = torch.randn(n, generator=g, device=DEV)
+    say(f"loss sum n={n}")
+    first = None
+    for _ in range(2):
+        out = saki_lib.route_loss(s, token, corrected, token, adv, grad_scale=0.25)
+        torch.cuda.synchronize()
+        rl = 0.25 * out["row_loss"].double().cpu().numpy()
+        got = out["loss_sum"].item()
+        assert abs(got - rl.sum()) <= 2.0 ** -23 * np.abs(rl).sum()
+        assert first is None or got == first
+        first = got
+
+
 @pytest.mark.parametrize("V", [36 * 1024, 37 * 1024 + 5, 151936])
 def test_route_loss_row_cache(saki_lib, V):
     """bf16 rows keep each wave's last nine full chunks of s in LDS between the
