@@ -32,8 +32,7 @@ KERNEL_SOURCES["stream"] = KERNEL_SOURCES["couple"]
 
 # HBM traffic of one step of the dominant kernel, from two rocprofv3 --pmc runs
 # (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch): the couple kernel on the large
-# workload at eps 0.2 (its main launch and the short launch that redoes flagged
-# rows, profiles/couple_kernel_large.md), the verify kernel on the verification
+# workload at eps 0.2 (profiles/couple_kernel_large.md), the verify kernel on the verification
 # workload (profiles/verify_kernel.md), the couple kernel on one 4,096-row chunk
 # of the long-rollout workload (mean of five chunks, profiles/couple_kernel_stream.md),
 # the route kernel on the large workload's coupled rows
@@ -42,15 +41,17 @@ KERNEL_SOURCES["stream"] = KERNEL_SOURCES["couple"]
 # reads FETCH_SIZE = 524,300-524,320 KiB and WRITE_SIZE = 1,048,576 KiB, so
 # FETCH_SIZE is scaled by 2.0 and WRITE_SIZE by 1.0.  Keyed by the SHA-256 of
 # the kernel's sources: a changed kernel reports traffic = null until re-measured.
-_CORE_HASH = "fab9e12252029b7344abf907affbc80908491c42be492c4d9797e374b81230dd"
 MEASURED_TRAFFIC = {
-    "couple": {_CORE_HASH: dict(fetch_kib=38406715.5 + 59.8, write_kib=41888169.2 + 5648.0,
-                                fetch_scale=2.0, write_scale=1.0)},
-    "verify": {_CORE_HASH: dict(fetch_kib=13062836.5, write_kib=97980.9, fetch_scale=2.0, write_scale=1.0)},
-    "stream": {_CORE_HASH: dict(fetch_kib=2662206.5, write_kib=2924365.7, fetch_scale=2.0, write_scale=1.0)},
-    "route": {_CORE_HASH: dict(fetch_kib=17097281.9, write_kib=41756980.5, fetch_scale=2.0, write_scale=1.0)},
-    "probe": {"a242e6a694f019423bc917d1dada40291711f9267150294d94c60238e7bdba2c":
-              dict(fetch_kib=1284932.0, write_kib=975.4, fetch_scale=2.0, write_scale=1.0)},
+    "couple": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1":
+               dict(fetch_kib=38032057.5, write_kib=40658839.2, fetch_scale=2.0, write_scale=1.0)},
+    "verify": {"3245bc13811329aa826ac93fd332e32affc9623fff5af17fa3cbf0a5b3667232":
+               dict(fetch_kib=13034843.4, write_kib=4339.4, fetch_scale=2.0, write_scale=1.0)},
+    "stream": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1":
+               dict(fetch_kib=2623863.2, write_kib=2845783.1, fetch_scale=2.0, write_scale=1.0)},
+    "route": {"b052037693f473bf4a315548335b8981897d705cc1be078d74890b3d181353de":
+               dict(fetch_kib=17097070.8, write_kib=41516477.4, fetch_scale=2.0, write_scale=1.0)},
+    "probe": {"fbdb1a7eacd3ac26c99e68125dcce42615ebf2df3103139a0eb00301c7bf3d9a":
+               dict(fetch_kib=1285172.5, write_kib=978.1, fetch_scale=2.0, write_scale=1.0)},
 }
 
 
@@ -62,8 +63,8 @@ MEASURED_TRAFFIC = {
 # four cycles each), 256 CUs x 2.4 GHz = 6.14e11 per second.
 VALU_ISSUE_PEAK = 256 * 2.4e9
 MEASURED_VALU = {
-    "couple": {_CORE_HASH: 9.762e9},
-    "verify": {_CORE_HASH: 3.113e9},
+    "couple": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1": 8.719e9},
+    "verify": {"3245bc13811329aa826ac93fd332e32affc9623fff5af17fa3cbf0a5b3667232": 2.892e9},
 }
 
 
