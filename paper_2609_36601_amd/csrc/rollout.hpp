@@ -37,7 +37,13 @@ constexpr int SAMPLE_WG_PER_CU = 2;
 template <typename T>
 constexpr int SAMPLE_DEPTH = sizeof(T) == 2 ? 4 : 2;
 
-constexpr float SAMPLE_MAX_TOP = 1e38f;
+// Rows whose largest logit is below this take the exponents against the wave's
+// maximum times log2 e rounded once: that rounding (a sixteenth of a power of two
+// at most here) scales all of a chunk's terms alike and is part of the chunk's
+// reference.  For larger logits it grows with them, past 2^127 from a few
+// 10^9 on, where a chunk's terms would all become 0 or infinite: those rows take the
+// per-chunk form.
+constexpr float SAMPLE_MAX_TOP = 0x1p20f;
 
 // The chunk masses of any row: every chunk against its own maximum by
 // differences (chunk c keeps that maximum, in natural units, and the sum of
@@ -98,7 +104,7 @@ __global__ __launch_bounds__(SAMPLE_NT, SAMPLE_WG_PER_CU) void sample_kernel(Sam
     // sweep: chunk c keeps (MsL, sum 2^(s log2 e - MsL)).  A row whose smallest
     // entry is above -inf and whose maxima and sums are finite is finite (a NaN
     // or +inf entry makes a chunk's sum NaN or infinite); any other, and one
-    // whose maximum times log2 e nears the end of the float range, goes through
+    // whose maximum is SAMPLE_MAX_TOP or more in size, goes through
     // sample_masses_any.  MsL stays finite on a wave that has only met entries
     // at the type's lowest value (masks): their sum is then 0.
     float Ms = -finf(), MsL = -finf(), lo = finf();

@@ -279,6 +279,27 @@ def test_sample_chunk_groups_and_extreme_logits(saki_lib, dtype, nch):
             assert tok[r] == z[i][0] or min(gc[i][0], ge[i][0]) < parity.MARGIN, (r, tok[r], z[i][0])
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_sample_large_finite_logits(saki_lib, dtype):
+    """One entry far above the others draws the token at every finite magnitude,
+    above zero and below it, whatever chunk and wave it lies in: from a few
+    1e9 on the float rounding of max * log2 e exceeds the range of an exponent."""
+    V, n = 12 * 1024 + 300, 140
+    s = _random_rows(n, V, dtype, 3)
+    size = torch.logspace(3, 38, n // 2)
+    at = torch.randint(0, V, (n,), generator=torch.Generator().manual_seed(8))
+    for i in range(n // 2):
+        s[2 * i, at[2 * i]] = size[i].item()
+        s[2 * i + 1] = -size[i].item()
+        s[2 * i + 1, at[2 * i + 1]] = -0.5 * size[i].item()
+    say(f"sample large logits {dtype}")
+    tok, status = saki_lib.sample(s, 12)
+    torch.cuda.synchronize()
+    assert (status == 0).all()
+    bad = np.nonzero(tok.cpu().numpy() != at.numpy())[0]
+    assert not bad.size, [(int(r), f"{size[r // 2].item():.1e}") for r in bad[:10]]
+
+
 @pytest.mark.parametrize("same", [False, True])
 def test_rollout_without_corrections(saki_lib, same):
     """eps = 0 (q = p), or a teacher equal to the student (q = pi = p): every
