@@ -52,7 +52,7 @@ struct RowStats {
   double lse_s, lse_t; // log-sum-exp of s and t
   double sum_s;        // sum exp(s - ms)
   double inv_s;        // 1 / sum_s
-  double shift;        // shift_correction(ms, ms log2(e) rounded to float)
+  double shift;        // 2^-d0, d0 the rounding of the float shift ms log2(e) (shift_rounding)
   float c;             // centring constant: E_p[d] rounded to float
   float cL;            // c log2(e) rounded to float; X = fma(d, log2 e, -cL)
   double mean_p;       // E_p[d]
@@ -390,16 +390,11 @@ constexpr int use_mode() { return (SH::CACHE_CHUNKS > 0 && sizeof(T) == 2) ? CAC
 // ---------------------------------------------------------------------------
 // Stats sweep.
 // ---------------------------------------------------------------------------
-// 2^-d0 for d0 = ms log2(e) - msL, the rounding of the float shift msL.
-__device__ __forceinline__ double shift_correction(float ms, float msL) {
-  const double d0 = static_cast<double>(LOG2E) * static_cast<double>(ms) - static_cast<double>(msL);
-  return exp2(-d0);
+// d0 = ms log2(e) - msL, the rounding of the float shift msL: the row's sums are
+// multiplied by 2^-d0.
+__device__ __forceinline__ double shift_rounding(float ms, float msL) {
+  return static_cast<double>(LOG2E) * static_cast<double>(ms) - static_cast<double>(msL);
 }
-
-// The middle node's weights are taken relative to the maximum of p~ alone, so
-// they reach 2^(kLm (mt - ms)): rows where that could leave the range float sums
-// need (maxima of s and t 100 or more apart) go without a middle node.
-constexpr float MID_MAX_SHIFT = 60.0f;
 
 struct StatsAcc {
   float Ms, Mt;                 // wave-uniform running maxima of s and t
@@ -407,7 +402,7 @@ struct StatsAcc {
   double Ss, St;                // per-lane sums of 2^(s log2 e - MsL), 2^(t log2 e - MtL)
   float S1, S2, S3, S4;         // per-lane p-weighted powers of d (relative to Ms)
   float T1, T2;                 // per-lane pi-weighted sums of d, d^2 (relative to Mt)
-  double Sm;                    // per-lane sum of 2^(as + kLm d), the middle node's weights
+  double Sm;                    // per-lane sum of 2^((1 - lm) as + lm at), lm the middle node
   float Q1, Q2;                 // per-lane d, d^2 under those weights
   int tidx;                     // wave-uniform lowest index of the running max of t
   float t_smax;                 // wave-uniform: t at an entry holding the running max of s
@@ -431,15 +426,20 @@ struct StatsAcc {
 // fma(x, log2 e, -ML) with ML = M log2(e) rounded to float, rounded once, so
 // the largest terms carry no rounding from the shift; the rounding of ML itself
 // is one factor for every term sharing it, removed exactly once the row's
-// maxima are known (shift_correction).  The proposal mass of chunk c is kept as
+// maxima are known (shift_rounding).  The proposal mass of chunk c is kept as
 // (MsL, sum_c 2^(s log2 e - MsL)), i.e. ln W_c = MsL ln 2 + ln(sum).
-// kLm: the middle node lm in log2 units (lm = kLm / log2 e exactly, as the
-// sums see it).  MID: also the middle node's sums (else the row carries no middle node and
+// lm: the middle node.  Its weights p~^(1 - lm) pi~^lm are taken relative to both
+// running maxima, so that an offset between the logits of s and t, which changes
+// nothing in p and pi, changes neither their range nor their rounding (relative
+// to the maximum of s alone they cost one instruction an entry less, but reach
+// 2^(lm (mt - ms) log2 e): the rounding of A(lm) grows with the offset, and with
+// maxima 60 / lm log2 units apart the row would have to go without the node).
+// MID: also the middle node's sums (else the row carries no middle node and
 // the lambda search starts from the ends alone); K34: the third and fourth
 // p-moments of d.
 template <bool TAIL, bool MID, bool K34, typename SH>
 __device__ __forceinline__ void stats_math(const float* s, const float* t, uint32_t vm, int c,
-                                           int lane, bool keep_chunks, bool keep_teacher, float kLm, SH& sh,
+                                           int lane, bool keep_chunks, bool keep_teacher, float lm, SH& sh,
                                            StatsAcc& a) {
   // this lane's maxima and range of d over the chunk: chains of three-input
   // max / min (EPL - 1 entries after the first, two per instruction)
@@ -484,8 +484,9 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     const float f = fexp2(dsl);
     a.Ss *= static_cast<double>(f);
     a.S1 *= f; a.S2 *= f; a.S3 *= f; a.S4 *= f;
-    a.Sm *= static_cast<double>(f);
-    a.Q1 *= f; a.Q2 *= f;
+    const float fm = fexp2((1.0f - lm) * dsl);
+    a.Sm *= static_cast<double>(fm);
+    a.Q1 *= fm; a.Q2 *= fm;
     a.Ms = cms;
     a.MsL = cmsL;
   }
@@ -503,6 +504,9 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     a.St *= static_cast<double>(f);
     a.T1 *= f;
     a.T2 *= f;
+    const float fm = fexp2(lm * dtl);
+    a.Sm *= static_cast<double>(fm);
+    a.Q1 *= fm; a.Q2 *= fm;
     a.Mt = cmt;
     a.MtL = cmtL;
   }
@@ -518,9 +522,9 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     float es = fexp2(as);
     float et = fexp2(at);
     const float d = t[e] - s[e];
-    // the middle node's weight p~ e^(lm d) = 2^(as + kLm d): its exponent is
-    // at most lm (Mt - Ms) log2 e (MID_MAX_SHIFT bounds it for a row that uses it)
-    float em = MID ? fexp2(fmaf(d, kLm, as)) : 0.0f;
+    // the middle node's weight p~^(1 - lm) pi~^lm: its exponent is at most 0
+    // (as, at <= 0), so it cannot overflow
+    float em = MID ? fexp2(fmaf(lm, at - as, as)) : 0.0f;
     if (TAIL && !SAKI_VALID(e)) { es = 0.f; et = 0.f; em = 0.f; }
     const float d2 = d * d;
     p1 = fmaf(es, d, p1);
@@ -605,7 +609,7 @@ __device__ __forceinline__ void stats_post(Block<NT, SH>& B, StatsAcc& a) {
 // reciprocals are taken there too, side by side: the wave is alone here, and its
 // dependent double-precision steps are what every row waits for.
 template <int NT, typename SH>
-__device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float kLm, bool k34) {
+__device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float lm, bool k34) {
   constexpr int NW = NT / WAVE;
   RowStats R;
   R.ms = -finf();
@@ -621,24 +625,35 @@ __device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float kLm, b
   R.tmax = -finf();
   R.vstar = 0x7fffffff;
   R.t_smax = -finf();
-  // each wave's sums are relative to 2^(its MsL) (sums of pi: MtL): rescale to
-  // the row's ML = m log2(e) rounded (the ML of a wave holding the maximum),
-  // then remove that rounding, 2^-d0 (shift_correction)
+  // each wave's sums are relative to 2^((1 - b) MsL + b MtL) of its own maxima
+  // (b: 0 for the sums of p, 1 for those of pi, lm for the middle node's):
+  // rescale to the row's (ML = m log2(e) rounded, the ML of a wave holding the
+  // maximum), then remove that rounding, 2^-d0 (shift_rounding)
   const int i = B.lane < 11 ? B.lane : 10;
-  const bool pi_sum = i >= 5 && i < 8;
-  const float m = pi_sum ? R.mt : R.ms, mL = __fmul_rn(m, LOG2E);
+  const bool pi_sum = i >= 5 && i < 8, mid_sum = i >= 8;
+  const float bt = mid_sum ? lm : pi_sum ? 1.0f : 0.0f, bs = 1.0f - bt;
+  const float msL = __fmul_rn(R.ms, LOG2E), mtL = __fmul_rn(R.mt, LOG2E);
+  const float m = pi_sum ? R.mt : R.ms, mL = pi_sum ? mtL : msL;
   double acc = 0.0;
   for (int w = 0; w < NW; ++w) {
-    const float wM = B.sh.red_f[w][pi_sum ? 1 : 0];
-    const float wML = static_cast<float>(B.sh.red_d[w][pi_sum ? 13 : 12]);
-    const double f = (wM == -finf()) ? 0.0 : (wM == m) ? 1.0 : static_cast<double>(fexp2(__fsub_rn(wML, mL)));
-    acc += B.sh.red_d[w][i] * f;
     const float wMs = B.sh.red_f[w][0], wMt = B.sh.red_f[w][1];
+    // a wave without entries has -inf maxima and zero sums
+    double f = 0.0;
+    if (wMs != -finf()) {
+      const double ds = static_cast<double>(__fsub_rn(static_cast<float>(B.sh.red_d[w][12]), msL));
+      const double dt = static_cast<double>(__fsub_rn(static_cast<float>(B.sh.red_d[w][13]), mtL));
+      // 2^e by the hardware at e rounded to float, and the rest of e linearly
+      const double e = static_cast<double>(bs) * ds + static_cast<double>(bt) * dt;
+      const float ef = static_cast<float>(e);
+      f = static_cast<double>(fexp2(ef)) * (1.0 + (e - static_cast<double>(ef)) * LN2_D);
+    }
+    acc += B.sh.red_d[w][i] * f;
     const int wi = B.sh.red_i[w][0];
     if (wMt > R.tmax || (wMt == R.tmax && wi < R.vstar)) { R.tmax = wMt; R.vstar = wi; }
     if (wMs == R.ms) R.t_smax = fmaxf(R.t_smax, static_cast<float>(B.sh.red_d[w][14]));
   }
-  const double corr = shift_correction(m, mL);
+  const double corr = exp2(-(static_cast<double>(bs) * shift_rounding(R.ms, msL) +
+                             static_cast<double>(bt) * shift_rounding(R.mt, mtL)));
   acc *= corr;
   // The maximum's own term went into the sums as 2^d0 rounded to float (d0 =
   // the rounding of the shift, ~1e-6: a rounding of ~6e-8 next to 1); after
@@ -670,16 +685,14 @@ __device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float kLm, b
   R.c = static_cast<float>(Ed);
   if (!isfinite(R.c)) R.c = 0.0f;
   R.cL = R.c * LOG2E;
-  // A at the middle node lm: sum_v p_v e^{lm x_v} = e^{-lm c} sum_m / sum_s,
-  // with sum_m = sum e^{(s - ms) + lm d}; its derivatives are the mean and
-  // variance of x under the tilted weights.  No middle node on a row whose
-  // weights there could leave the float range.
+  // A at the middle node lm: sum_v p_v e^{lm x_v} = e^{lm (mt - ms - c)}
+  // sum_m / sum_s, with sum_m = sum e^{(1 - lm)(s - ms) + lm (t - mt)}; its
+  // derivatives are the mean and variance of x under the tilted weights.
   {
-    const double lm = kLm > 0.0f && fabsf(kLm * (R.mt - R.ms)) < MID_MAX_SHIFT
-                          ? static_cast<double>(kLm) / static_cast<double>(LOG2E) : 0.0;
+    const double l = static_cast<double>(lm);
     const double M1 = lane_d(acc, 9) * im, M2 = lane_d(acc, 10) * im;
-    R.lam_mid = lm > 0.0 && lane_d(acc, 8) > 0.0 && isfinite(M2) ? lm : 0.0;
-    R.mid_A = ln_m - ln_s - lm * static_cast<double>(R.c);
+    R.lam_mid = lane_d(acc, 8) > 0.0 && isfinite(M2) ? l : 0.0;
+    R.mid_A = l * (static_cast<double>(R.mt) - static_cast<double>(R.ms) - static_cast<double>(R.c)) + ln_m - ln_s;
     R.mid_A1 = M1 - static_cast<double>(R.c);
     R.mid_A2 = fmax(M2 - M1 * M1, 0.0);
   }
@@ -700,16 +713,15 @@ __device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T
   constexpr int NW = NT / WAVE;
   StatsAcc a;
   a.init();
-  const float kLm = lm * LOG2E;
   for_chunks<T, NW, false, fill_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      stats_math<TAIL, MID, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, kLm, B.sh, a);
+                      stats_math<TAIL, MID, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, lm, B.sh, a);
                     }, row_cache<T>(B.sh));
   stats_post(B, a);
   __syncthreads();
   if (B.wave == 0) {
-    const RowStats R = stats_combine(B, MID ? kLm : 0.0f, K34);
+    const RowStats R = stats_combine(B, MID ? lm : 0.0f, K34);
     if (B.lane == 0) B.sh.rs.r = R;
   } else {
     idle();
@@ -773,7 +785,7 @@ struct LamEval {
 // a = fma(s, log2 e, -msL) with msL = ms log2 e rounded to float: the rounding
 // of the shift, d0 = ms log2 e - msL (exact in double), is one offset for every
 // entry of the row, so every weight and every p~ carries the factor 2^d0; the
-// row sums are multiplied by 2^-d0 once (shift_correction).
+// row sums are multiplied by 2^-d0 once (RowStats::shift).
 template <int MODE, bool TAIL>
 __device__ __forceinline__ void lam_math(const float* s, const float* t, uint32_t vm, float msL,
                                          float cL, float lam, float sigl, bool accf, double (&acc)[5]) {

@@ -736,3 +736,70 @@ def test_rows_resolved_again_in_the_expm1_forms(saki_lib, D):
     assert np.all(b["kl"] >= 0.1) and np.all(pmax < 0.25) and np.all(b["tv"] < 0.02 * np.sqrt(pmax))
     out, o, R = run_and_compare(saki_lib, S, T, 0.2, 8080, row_offset=7)
     _row_properties(o, 0.2)
+
+
+def _min_ms(run, reps=7):
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        run()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b))
+    return best
+
+
+@pytest.mark.parametrize("offset", [-200.0, -60.0, 60.0, 200.0])
+def test_teacher_logits_with_an_offset(saki_lib, offset):
+    """A constant added to every teacher logit changes neither pi nor anything
+    computed from it: the coupling and the verification of the shifted rows give
+    the unshifted rows' results to rounding, and take about their time (a row
+    that loses its middle node to the offset falls back to lambda sweeps, half
+    as long again).  Logits are multiples of 2^-12 so that the sum is exact."""
+    n, V, eps, seed, k = 1024, 100000, 0.2, 71, 8
+    g = torch.Generator(device=DEV).manual_seed(2)
+    s, t, t2 = (saki_lib.alloc_rows(n, V, torch.float32, DEV) for _ in range(3))
+    for a in range(0, n, 128):
+        x = torch.randn(128, V, generator=g, device=DEV) * 3.0
+        y = 0.8 * x + 1.8 * torch.randn(128, V, generator=g, device=DEV)
+        s[a:a + 128] = (x * 4096).round() / 4096
+        t[a:a + 128] = (y * 4096).round() / 4096
+    t2.copy_(t + offset)
+    draft, _ = saki_lib.sample(s, seed + 1)
+    say(f"teacher offset {offset}")
+    res, times = [], []
+    for tt in (t, t2):
+        out = saki_lib.alloc_couple_out(n, DEV)
+        ws = torch.empty(saki_lib.workspace_bytes(saki_lib.SAKI_OP_COUPLE, n, V), dtype=torch.uint8, device=DEV)
+        couple = lambda: saki_lib.saki_couple(s, tt, eps, seed, 0, out, None, ws)  # noqa: E731
+        acc, corr = (torch.empty(n // k, dtype=torch.int32, device=DEV) for _ in range(2))
+        verify = lambda: saki_lib.saki_spec_verify(s, tt, k, draft, eps, seed, 0, -1, acc, corr, None, ws)  # noqa: E731
+        couple(), verify()
+        times.append((_min_ms(couple), _min_ms(verify)))
+        res.append(dict({key: v.cpu().numpy() for key, v in out.items()}, n=acc.cpu().numpy()))
+    a, b = res
+    assert np.array_equal(a["proposal"], b["proposal"])
+    same = (a["corrected"] == b["corrected"])
+    assert np.all(same | (a["margin"] < parity.MARGIN))
+    for key in ("lambda", "kl", "tv", "accept_prob"):
+        assert np.all(parity.close(b[key], a[key], rtol=3e-6)), (key, parity.rel_err(b[key], a[key]))
+    say(f"ms (couple, verify): {times}")
+    for i in range(2):
+        assert times[1][i] <= 1.25 * times[0][i], times
+    assert np.mean(a["n"] == b["n"]) > 0.99
+
+
+@pytest.mark.parametrize("of", ["teacher", "both"])
+def test_masked_leading_chunks(saki_lib, of):
+    """Waves whose first chunks hold a mask value (-1e4) in t or in both arrays, so
+    that every sum of the stats sweep is rescaled from there when the wave meets
+    an ordinary chunk: all rows against the oracle."""
+    g = torch.Generator(device=DEV).manual_seed(4)
+    n, V = 8, 9 * 1024 + 100
+    s = 2.0 * torch.randn(n, V, generator=g, device=DEV)
+    t = 0.8 * s + torch.randn(n, V, generator=g, device=DEV)
+    if of == "both":
+        s[:, :4 * 1024] = -1e4
+    t[:, :4 * 1024] = -1e4
+    run_and_compare(saki_lib, padded(s), padded(t), 0.2, 15)
