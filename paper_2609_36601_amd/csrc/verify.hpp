@@ -73,8 +73,14 @@ __device__ __forceinline__ void write_skipped(const O* o, int64_t r, int32_t dra
 }
 
 // VNT threads per workgroup: 256 (two workgroups per CU), or 512 (one per CU)
-// when a call has no more positions than CUs, so that each position's sweeps
-// are spread over eight waves.
+// when a call has no more blocks than CUs: each position's sweeps are spread
+// over eight waves, nothing shares its CU, and at most CUs / n_blocks positions
+// of a block run ahead of the first stop.  (Two workgroups per CU from more
+// positions than CUs on took the average batch a little faster, 64 blocks of 8
+// x 151,936 with every output in 190 instead of 210 us, but the batch whose
+// blocks all stop early much slower, its positions sharing the chip with twice
+// as many evaluated in vain: 256 blocks stopped at position 0 466 instead of 321
+// us.)
 template <typename T, int KC, int VNT, bool K34>
 __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyParams) {
   using SH = RowShared<VNT, (KC > 0 ? CACHED_MAXC : MAX_CHUNKS), KC>;
@@ -203,16 +209,19 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       // Positions the interpolating start places well take the fused sweep
       // (the lambda node, and the residual chunk masses where the start
       // predicts a rejection); the others the lambda search and, when rejected
-      // or when TV is asked for, the final sweep.  (With one workgroup per CU,
-      // where nothing hides the fused sweep's serial start and settling, it
-      // gains too since those were shortened: one block of eight positions 106
-      // us without it, 94 us with it.)
+      // or when TV is asked for, the final sweep.  With one workgroup per CU
+      // every position takes the search: it evaluates a node at lambda* itself,
+      // where the fused sweep's node can lie 2% away (200 blocks of 8 x 5,000:
+      // lambda* and TV within 6e-7 against 4e-6 and 7e-6), and the batch waits for
+      // its slowest position, which the fused sweep, run in vain there, delays
+      // (32 blocks of 8 x 151,936, every output: 119 us, 136 with it; one block,
+      // whose positions may all settle in it: 103 us, 92 with it).
       const bool end_first = R.kl1_est <= 1.05 * P->eps + 1e-5;
       if (B.wave == 0) {
         // the block's word again, loaded while the start point is computed: the
         // position is dropped when an earlier one has stopped the block meanwhile
         const int32_t word = __hip_atomic_load(P->accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool fu = !force_acc && P->eps > 0.0 && R.dmin != R.dmax;
+        bool fu = VNT == 256 && !force_acc && P->eps > 0.0 && R.dmin != R.dmax;
         StartPoint S0;
         S0.lam = 1.0; S0.A = R.lse_t - R.lse_s - static_cast<double>(R.c); S0.herm = true;
         if (fu) {

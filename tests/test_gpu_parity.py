@@ -325,6 +325,30 @@ def test_verify_positions_evaluated_ahead(saki_lib, nb, k):
     assert np.array_equal(pp["proposal"], draft.cpu().numpy()) and np.all(pp["corrected"][skipped] == 0)
 
 
+def test_verify_precision_of_small_batches(saki_lib):
+    """lambda*, KL and TV of batches of at most one block per CU against 64 bits:
+    2e-6 at every position, three times the largest error measured (6e-7, the
+    rounding of float sums; a node 2% away from lambda* leaves up to 7e-6)."""
+    g = torch.Generator(device=DEV).manual_seed(10)
+    n, V, eps, nb = 1600, 5000, 0.2, 200
+    rho = 0.2 + 0.79 * torch.rand(n, 1, generator=g, device=DEV)
+    s = 4.3 * torch.randn(n, V, generator=g, device=DEV)
+    t = rho * s + 3.0 * torch.sqrt(1 - rho ** 2) * torch.randn(n, V, generator=g, device=DEV)
+    s, t = padded(s.to(torch.bfloat16)), padded(t.to(torch.bfloat16))
+    draft, _ = saki_lib.sample(s, 3)
+    say("verify precision")
+    pp = {}
+    for a in range(0, n, nb):
+        o = saki_lib.spec_verify(s[a:a + nb], t[a:a + nb], 1, draft[a:a + nb], eps, 5, row_offset=a)["per_pos"]
+        for key in ("lambda", "kl", "tv"):
+            pp.setdefault(key, []).append(o[key].cpu().numpy())
+    b = bridge.bridge_rows(f64(s), f64(t), eps)
+    for key, ref in (("lambda", b["lam"]), ("kl", b["kl"]), ("tv", b["tv"])):
+        err = np.abs(np.concatenate(pp[key]) / ref - 1.0)
+        say(f"{key}: rms {np.sqrt(np.mean(err ** 2)):.1e} max {err.max():.1e}")
+        assert err.max() < 2e-6, (key, np.argsort(-err)[:5], np.sort(-err)[:5])
+
+
 def padded(x):
     """Copy of a [n, V] tensor in storage whose row pitch is a multiple of 16 bytes."""
     n, V = x.shape
