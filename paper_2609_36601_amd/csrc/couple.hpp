@@ -252,8 +252,8 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams) {
       if (B.wave == 0) {
         FC.set_node();
         const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-        const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
-                                                true, E0, facc, true);
+        const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; },
+                                                [] { return true; }, false, 0.0f, true, E0, facc);
         int state = -1, C0 = 0, redo = 0;
         double alpha0 = 0.0;
         FinalConst F0{};
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams) {
       const LamEval E0 = fused ? plan.E0 : LamEval{};
       L = lambda_search_with(R, P->eps, [&](float lam, bool acc) {
         return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc);
-      }, force_acc, 0.0f, fused, E0, tv_acc);
+      }, [] { return false; }, force_acc, 0.0f, fused, E0, tv_acc);
       F = final_const(R, L, force_acc);
       alpha = exp(fmin(0.0, L.log_ratio(sz, tz)));
       C = uniform(!(u < alpha));

@@ -1174,18 +1174,18 @@ __device__ __forceinline__ StartPoint start_point(const RowStats& R, double eps)
 // (the next term is smaller by about |l - node| times the cumulant growth);
 // otherwise the next node is that root (or the edge of the trust interval).
 // sweep1(lam, acc) evaluates one node over the whole row.
-// force_acc: every sweep in the expm1 form; lam_hint > 0: the first node (a
-// lambda* found before, resolved again in the accurate form); first (with
+// force_acc: every sweep in the expm1 form; lam_hint > 0: the first node, already
+// computed by start_point (1: the teacher end); first (with
 // given_first): the first node already evaluated (by the fused sweep, at
 // first.lam; in the expm1 form if first_acc), used in place of the first sweep.  out.sweeps
 // counts the sweeps run here.
-// no_sweep: stop where a sweep would be needed (out.sweeps = -1), so that one
-// wave can settle the common case of an accepted first node alone.
-template <typename Sweep1>
-__device__ __forceinline__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& sweep1, bool force_acc = false,
-                                        float lam_hint = 0.0f, bool given_first = false,
-                                        LamEval first = LamEval{}, bool first_acc = false,
-                                        bool no_sweep = false) {
+// stop(): asked before each sweep; true ends the search there (out.sweeps = -1):
+// so that one wave can settle the common case of an accepted first node alone,
+// and a position whose block has stopped meanwhile is dropped.
+template <typename Sweep1, typename Stop>
+__device__ __forceinline__ LamResult lambda_search_with(const RowStats& R, double eps, Sweep1&& sweep1, Stop&& stop,
+                                        bool force_acc = false, float lam_hint = 0.0f, bool given_first = false,
+                                        LamEval first = LamEval{}, bool first_acc = false) {
   LamResult out;
   out.acc = true;
   out.sweeps = 0;
@@ -1233,7 +1233,7 @@ __device__ __forceinline__ LamResult lambda_search_with(const RowStats& R, doubl
   for (int sweep = 0; sweep < MAX_SWEEPS; ++sweep) {
     const float lf = try_one ? 1.0f : static_cast<float>(lg);
     const bool given = sweep == 0 && given_first;
-    if (!given && no_sweep) {
+    if (!given && stop()) {
       out.sweeps = -1;
       return out;
     }
@@ -1329,14 +1329,6 @@ __device__ __forceinline__ LamResult lambda_search_with(const RowStats& R, doubl
   // largest feasible evaluated lambda
   out.lam = static_cast<float>(feas.lam); out.A = feas.A; out.KL = feas.KL;
   return out;
-}
-
-template <typename T, int NT, typename SH>
-__device__ __forceinline__ LamResult lambda_search(Block<NT, SH>& B, const T* srow, const T* trow, int V,
-                                   const RowStats& R, double eps, bool force_acc = false, float lam_hint = 0.0f) {
-  return lambda_search_with(R, eps, [&](float lam, bool acc) {
-    return lam_sweep<T, NT>(B, srow, trow, V, R, lam, acc);
-  }, force_acc, lam_hint);
 }
 
 // A row resolved in a plain form whose TV is too small for that form's

@@ -13,7 +13,9 @@ namespace saki {
 // stopping one decides: each block keeps its smallest stopping position with
 // its outcome in one word (atomicMin on accepted_len[b]; stop_word), items
 // after it are skipped, and a short second kernel turns the words into the
-// outputs.  In a batch large enough to fill the chip, position j of a block is
+// outputs.  A position whose rejection is certain from the row statistics says
+// so before it has its lambda* and correction (the smallest such position of a
+// block, atomicMin on correction[b]): positions behind it are skipped too.  In a batch large enough to fill the chip, position j of a block is
 // taken long after its position j - 1 has ended, so few positions are
 // evaluated in vain; in a small batch the idle workgroups evaluate them ahead
 // instead of the block's positions running one after another.
@@ -36,8 +38,8 @@ struct VerifyParams {
   float lam_mid;  // mid_lambda(eps)
   uint64_t seed;
   int eos;
-  int32_t* accepted_len;
-  int32_t* correction;
+  int32_t* accepted_len;  // the blocks' words until verify_end_kernel
+  int32_t* correction;    // the blocks' first position known to reject until then (k: none)
   saki_couple_out pp;  // per-position outputs (fields may be NULL)
   int has_pp;
   unsigned long long* next_item;  // work counter in the caller's workspace, zero at launch
@@ -52,6 +54,29 @@ __host__ __device__ inline int32_t stop_word(int j, bool eos, int corr) {
 }
 __host__ __device__ inline int stop_pos(int32_t w) { return w >> 23; }
 static_assert(SAKI_MAX_BLOCK_K <= 64 && SAKI_MAX_VOCAB <= (1 << 21), "stop_word holds k and the vocabulary");
+
+// An upper bound of log q(z) - log p(z) = g(lambda*), g(lam) = lam x_z - A(lam),
+// from the row statistics: g is concave, so it lies below its tangents at
+// lambda = 0 and at the middle node lm, whose largest values over a bracket of
+// lambda* are at its ends.  KL(lm) against eps tells on which side of lm lambda*
+// lies (both, when too close to tell); below, KL(lam) = int_0^lam l A''(l) dl <=
+// lam (A'(lm) - A'(0)), so lambda* is at least eps / (A'(lm) - A'(0)).  `slack`
+// covers the float sums: the moments of d to 1e-5 of its range (ten times their
+// rounding), A to 1e-4.
+__device__ __forceinline__ double log_ratio_bound(const RowStats& R, double eps, float s, float t) {
+  if (!(R.lam_mid > 0.0)) return 0.0;
+  const double lm = R.lam_mid, c = static_cast<double>(R.c);
+  const double slack = 1e-5 * (static_cast<double>(R.dmax) - static_cast<double>(R.dmin));
+  const double xz = static_cast<double>(t) - static_cast<double>(s) - c;
+  const double klm = lm * R.mid_A1 - R.mid_A, rise = R.mid_A1 - (R.mean_p - c) + slack;
+  const double low = eps < lm * rise ? eps / rise : lm;
+  const double la = klm < eps * (1.0 - 1e-3) - slack ? lm : low, lb = klm > eps * (1.0 + 1e-3) + slack ? lm : 1.0;
+  const double k0 = xz - (R.mean_p - c), km = xz - R.mid_A1;
+  const double u0 = fmax(k0 * la, k0 * lb);
+  const double um = lm * xz - R.mid_A + fmax(km * (la - lm), km * (lb - lm));
+  const double b = fmin(u0, um) + 1e-4 + slack;
+  return b < 0.0 ? b : 0.0;  // (NaN: no bound)
+}
 
 // o: the per-position outputs, in the argument segment or elsewhere
 template <typename O>
@@ -74,13 +99,13 @@ __device__ __forceinline__ void write_skipped(const O* o, int64_t r, int32_t dra
 
 // VNT threads per workgroup: 256 (two workgroups per CU), or 512 (one per CU)
 // when a call has no more blocks than CUs: each position's sweeps are spread
-// over eight waves, nothing shares its CU, and at most CUs / n_blocks positions
+// over eight waves, nothing shares its CU, and about CUs / n_blocks positions
 // of a block run ahead of the first stop.  (Two workgroups per CU from more
-// positions than CUs on took the average batch a little faster, 64 blocks of 8
-// x 151,936 with every output in 190 instead of 210 us, but the batch whose
-// blocks all stop early much slower, its positions sharing the chip with twice
-// as many evaluated in vain: 256 blocks stopped at position 0 466 instead of 321
-// us.)
+// positions than CUs on take the average batch faster, 64 / 256 blocks of 8 x
+// 151,936 with every output in 190 / 415 instead of 206 / 470 us, but a batch
+// whose blocks stop early slower, its positions sharing the chip with twice as
+// many evaluated in vain: 64 / 128 / 256 blocks stopped at position 0 309 / 370 /
+// 460 us, 169 / 192 / 269 now.)
 template <typename T, int KC, int VNT, bool K34>
 __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyParams) {
   using SH = RowShared<VNT, (KC > 0 ? CACHED_MAXC : MAX_CHUNKS), KC>;
@@ -100,6 +125,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
   __shared__ long long next_i;
   const long long n_items = P->n_blocks * P->k;
   const unsigned int nb = static_cast<unsigned int>(P->n_blocks);
+  auto look = [](const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
   for (;;) {
     P = kernel_args<VerifyParams>();
     if (B.tid == 0) {
@@ -108,8 +134,8 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         i = static_cast<long long>(take_index(P->next_item));
         if (i >= n_items) break;
         // a stale word only costs a position evaluated in vain
-        const int32_t w = __hip_atomic_load(P->accepted_len + i % nb, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (stop_pos(w) >= static_cast<int>(i / nb)) break;
+        const int32_t w = look(P->accepted_len + i % nb), rj = look(P->correction + i % nb);
+        if (stop_pos(w) >= static_cast<int>(i / nb) && rj >= static_cast<int>(i / nb)) break;
       }
       next_i = i;
     }
@@ -122,6 +148,8 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
     const int j = static_cast<int>(item / nb);
     const int64_t b = item % nb;
     const int64_t r = b * P->k + j;
+    // is this position behind its block's stop, or behind one known to reject?
+    auto behind = [&](int32_t word, int32_t rj) { return stop_pos(word) < j || rj < j; };
     // a position resolved in a plain form whose TV turns out too small for
     // that form's rounding is processed again with every sweep in the expm1
     // form (rare): force_acc is all that crosses the restart
@@ -218,25 +246,31 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       // whose positions may all settle in it: 103 us, 92 with it).
       const bool end_first = R.kl1_est <= 1.05 * P->eps + 1e-5;
       if (B.wave == 0) {
-        // the block's word again, loaded while the start point is computed: the
-        // position is dropped when an earlier one has stopped the block meanwhile
-        const int32_t word = __hip_atomic_load(P->accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        bool fu = VNT == 256 && !force_acc && P->eps > 0.0 && R.dmin != R.dmax;
+        // the block's words again, loaded while the start point is computed: the
+        // position is dropped when an earlier one stops the block
+        const int32_t word = look(P->accepted_len + b), rj = look(P->correction + b);
+        const bool place = P->eps > 0.0 && R.dmin != R.dmax;  // lambda* is searched for
         StartPoint S0;
         S0.lam = 1.0; S0.A = R.lse_t - R.lse_s - static_cast<double>(R.c); S0.herm = true;
-        if (fu) {
-          if (!end_first) S0 = start_point(R, P->eps);
-          const double top = S0.lam * (static_cast<double>(R.dmax) - static_cast<double>(R.c));
-          fu = S0.herm && top <= 56.0 && (top - S0.A) * static_cast<double>(LOG2E) <= 56.0;
-        }
+        if (place && !end_first) S0 = start_point(R, P->eps);
+        const double top = S0.lam * (static_cast<double>(R.dmax) - static_cast<double>(R.c));
+        const bool fu = VNT == 256 && !force_acc && place && S0.herm && top <= 56.0 &&
+                        (top - S0.A) * static_cast<double>(LOG2E) <= 56.0;
+        // rejected whatever lambda* turns out to be: the positions behind are not needed
+        const bool reject = place && sh.u > fexp2(static_cast<float>(log_ratio_bound(R, P->eps, sz, tz)) * LOG2E);
         if (B.lane == 0) {
+          const bool drop = behind(word, rj);
+          if (reject && !drop) atomicMin(P->correction + b, j);
+          plan.C = reject ? 1 : 0;
           plan.S0 = S0;
-          plan.fused = stop_pos(word) < j ? -1 : fu ? 1 : 0;
+          plan.fused = drop ? -1 : fu ? 1 : 0;
         }
       }
       __syncthreads();
       const int fused = __builtin_amdgcn_readfirstlane(plan.fused);
       if (fused < 0) break;
+      // once said, a rejection stands (the positions behind may have been skipped)
+      const bool rejected = uniform(plan.C != 0);
       LamResult L;
       FinalConst F;
       double TV = __builtin_nan("");
@@ -245,6 +279,16 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       bool tv_acc = false;   // the fused sweep's form (the final sweep's is F.acc)
       int res_chunk = nch;
       bool search = true;    // lambda* by lambda sweeps
+      // between the sweeps of a search: has the block stopped meanwhile?  (The
+      // words as they were before the last sweep, so that nothing waits for them.)
+      int32_t word = 0, rj = 0;
+      int swept = 0;
+      auto gone = [&]() {
+        if (j == 0) return false;
+        if (B.tid == 0) sh.next = behind(word, rj) ? 1u : 0u;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)) != 0;
+      };
       if (fused != 0) {
         // the decision at the start point (in float, as in the coupling kernel)
         const float lam_g = static_cast<float>(plan.S0.lam);
@@ -264,10 +308,11 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         double le0 = 0.0;
         if (B.wave == 0) {
           FC.set_node();
-          const int32_t word = __hip_atomic_load(P->accepted_len + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          word = look(P->accepted_len + b);
+          rj = look(P->correction + b);
           const LamEval E0 = fused_node(R, FS, FC, end_first, facc);
-          const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; }, false, 0.0f,
-                                                  true, E0, facc, true);
+          const LamResult L0 = lambda_search_with(R, P->eps, [](float, bool) { LamEval e{}; return e; },
+                                                  [] { return true; }, false, 0.0f, true, E0, facc);
           int state = -1, C0 = 0;
           double alpha0 = 0.0;
           FinalConst F0{};
@@ -275,7 +320,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
           if (L0.sweeps == 0) {
             F0 = final_const(R, L0, false);
             alpha0 = exp(fmin(0.0, L0.log_ratio(sz, tz)));
-            C0 = !(u < alpha0) ? 1 : 0;
+            C0 = rejected || !(u < alpha0) ? 1 : 0;
             FF0 = fused_tv(R, L0, F0, FC, FS, facc);
             // settled unless the decision or TV needs the final sweep: a
             // rejection needs valid residual masses (kept only where the
@@ -283,7 +328,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
             const bool need_final = (C0 != 0) ? !(FF0.ok && reject_g) : (need_tv && !FF0.ok);
             state = need_final ? 0 : 1;
           }
-          if (state != 1 && stop_pos(word) < j) state = -2;  // more sweeps, in vain
+          if (state != 1 && behind(word, rj)) state = -2;  // more sweeps, in vain
           if (B.lane == 0) {
             plan.L = L0;
             plan.F = F0;
@@ -323,13 +368,20 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       if (search) {
         const LamEval E0 = fused != 0 ? plan.E0 : LamEval{};
         L = lambda_search_with(R, P->eps, [&](float lam, bool acc) {
+          ++swept;
+          if (B.tid == 0) {
+            word = look(P->accepted_len + b);
+            rj = look(P->correction + b);
+          }
           return lam_sweep<T, VNT>(B, srow, trow, V, R, lam, acc);
-        }, force_acc, 0.0f, fused != 0, E0, tv_acc);
+        }, [&] { return swept > 0 && gone(); }, force_acc, static_cast<float>(plan.S0.lam), fused != 0, E0, tv_acc);
+        if (L.sweeps < 0) break;
         F = final_const(R, L, force_acc);
       }
       const double alpha = exp(fmin(0.0, L.log_ratio(sz, tz)));
-      const bool accept = u < alpha;
+      const bool accept = u < alpha && !rejected;
       if (!settled && (need_tv || !accept)) {
+        if (swept > 0 && gone()) break;
         TV = final_sweep_any<T, float, VNT, false>(B, srow, trow, nullptr, V, F, !accept, 0.0f, -1, 0.0f);
         tv_ok = true;
         if (!accept) {

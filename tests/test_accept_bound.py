@@ -11,6 +11,11 @@ middle node lm (KL(lm) < eps) the bracket can end below 1, where convexity
 alone forces KL > eps:
     lh = lm (KL(pi||p) - eps) / (lm A'(1) - A(lm) - eps),
 and on [lm, lh] g lies above lam x_z minus the chord of A from lm to 1.
+
+From above, g lies below its tangents at 0 and at lm, and where KL(lm) > eps
+    lambda* >= eps / (A'(lm) - A'(0)),
+so a draft whose uniform lies above exp of their smallest value over the
+bracket is rejected whatever lambda* is.
 """
 import numpy as np
 import pytest
@@ -76,3 +81,33 @@ def test_bracket_end_bounds_lambda_star_and_the_bound_holds(eps):
         assert np.all(new >= old - 1e-12)  # never looser than the bracket [lm, 1]
         tightened += int(np.any(new > old + 1e-3))
     assert tightened > 0
+
+
+@pytest.mark.parametrize("eps", [0.02, 0.05, 0.2, 0.5])
+def test_bound_from_above_holds(eps):
+    s, t = _rows(12, 64, 512)
+    logp, logpi = bridge.log_softmax(s), bridge.log_softmax(t)
+    lam_star = bridge.lambda_star(s, t, eps)
+    lm = _mid_lambda(eps)
+    sides, clear, decided = set(), 0, 0
+    for r in range(s.shape[0]):
+        x = logpi[r] - logp[r]
+        Am, Dm = _A_and_slope(logp[r], x, lm)
+        _, D0 = _A_and_slope(logp[r], x, 0.0)
+        above = lm * Dm - Am < eps
+        sides.add(above)
+        low = min(lm, eps / (Dm - D0))
+        la, lb = (lm, 1.0) if above else (low, lm)
+        assert la - 1e-12 <= lam_star[r] <= lb + 1e-12
+        k0, km = x - D0, x - Dm
+        u0 = np.maximum(k0 * la, k0 * lb)
+        um = lm * x - Am + np.maximum(km * (la - lm), km * (lb - lm))
+        bound = np.minimum(np.minimum(u0, um), 0.0)
+        logq, _ = bridge.bridge_log_q(logp[r], logpi[r], [lam_star[r]])
+        g_star = logq[0] - logp[r]
+        assert np.all(np.minimum(g_star, 0.0) <= bound + 1e-10)
+        far = g_star < np.log(0.05)  # accept probability below 5%, u at 1/2
+        clear += int(far.sum())
+        decided += int((bound[far] < np.log(0.5)).sum())
+    assert True in sides or eps < 0.05
+    assert eps < 0.2 or decided > 0.5 * clear > 0

@@ -325,6 +325,42 @@ def test_verify_positions_evaluated_ahead(saki_lib, nb, k):
     assert np.array_equal(pp["proposal"], draft.cpu().numpy()) and np.all(pp["corrected"][skipped] == 0)
 
 
+@pytest.mark.parametrize("nb", [64, 256])
+def test_verify_of_blocks_that_stop_at_once(saki_lib, nb):
+    """Blocks of eight whose first draft the teacher all but excludes: the
+    positions behind it are dropped as soon as the rejection is certain, so the
+    call takes little longer than one with the first positions alone: 1.05 / 1.2
+    times for 64 / 256 blocks (1.7 times when they are evaluated to the end
+    beside them)."""
+    k, V, eps, seed = 8, 151936, 0.2, 33
+    g = torch.Generator(device=DEV).manual_seed(nb)
+    s, t = (saki_lib.alloc_rows(nb * k, V, torch.bfloat16, DEV) for _ in range(2))
+    for b in range(0, nb * k, 128):
+        x = 4.3 * torch.randn(min(128, nb * k - b), V, generator=g, device=DEV)
+        s[b:b + 128] = x
+        t[b:b + 128] = 0.6 * x + 2.4 * torch.randn(x.shape, generator=g, device=DEV)
+    draft, _ = saki_lib.sample(s, seed + 1)
+    at = draft.long()[:, None]
+    t.scatter_(1, at, s.gather(1, at) - 40.0)
+    say(f"verify blocks that stop at once: {nb}")
+    ws = torch.empty(256, dtype=torch.uint8, device=DEV)
+
+    def call(ss, tt, kk, d):
+        acc, corr = (torch.empty(nb, dtype=torch.int32, device=DEV) for _ in range(2))
+        run = lambda: saki_lib.saki_spec_verify(ss, tt, kk, d, eps, seed, 0, -1, acc, corr, None, ws)  # noqa: E731
+        run()
+        return _min_ms(run), acc.cpu().numpy(), corr.cpu().numpy()
+
+    whole, acc, corr = call(s, t, k, draft)
+    # position 0 of every block (other rows of the random streams: times only)
+    first, _, _ = call(s[::k], t[::k], 1, draft[::k].contiguous())
+    say(f"ms: {whole:.3f}, first positions alone {first:.3f}; stopped at 0: {(acc == 0).mean():.2f}")
+    assert whole <= 1.4 * first, (whole, first)
+    full = saki_lib.spec_verify(s, t, k, draft, eps, seed)
+    assert np.array_equal(acc, full["accepted_len"].cpu().numpy()) and np.array_equal(corr, full["correction"].cpu().numpy())
+    assert (acc == 0).mean() > 0.8
+
+
 def test_verify_precision_of_small_batches(saki_lib):
     """lambda*, KL and TV of batches of at most one block per CU against 64 bits:
     2e-6 at every position, three times the largest error measured (6e-7, the
