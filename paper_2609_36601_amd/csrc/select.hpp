@@ -124,6 +124,10 @@ __device__ void sel_histogram(Block<SNT, SelShared<SNT>>& B, const SelectParams&
   SelShared<SNT>& sh = B.sh;
 #pragma unroll
   for (int i = 0; i < PER; ++i) sh.hist[B.tid + i * SNT] = 0u;
+  if (B.tid == 0) {
+    sh.bin = 0;
+    sh.before = sh.in_bin = sh.n_cand = 0u;
+  }
   __syncthreads();
   for (int64_t r = lo_r + B.tid; r < hi_r; r += SNT) {
     const double key = P.keys[r];
@@ -156,7 +160,6 @@ __device__ void sel_histogram(Block<SNT, SelShared<SNT>>& B, const SelectParams&
     }
     cum += own[i];
   }
-  if (B.tid == 0) sh.n_cand = 0u;
   __syncthreads();
 }
 
@@ -277,15 +280,20 @@ __global__ __launch_bounds__(SNT) void select_kernel(SelectParams P) {
           const int sd = side(key);
           mark = sd < 0 ? 1 : 0;
           if (sd == 0) {
-            const unsigned int slot = atomicAdd(&sh.n_cand, 1u);  // at most in_bin <= SEL_CAP
-            sh.cand_key[slot] = key;
-            sh.cand_row[slot] = r;
+            // in_bin rows <= SEL_CAP, unless malformed ranges overlap and another
+            // workgroup has changed `sel` since they were counted: the list stays
+            // in its bounds whatever the ranges
+            const unsigned int slot = atomicAdd(&sh.n_cand, 1u);
+            if (slot < SEL_CAP) {
+              sh.cand_key[slot] = key;
+              sh.cand_row[slot] = r;
+            }
           }
         }
         P.sel[r] = mark;
       }
       __syncthreads();
-      const unsigned int n = sh.n_cand;
+      const unsigned int n = sh.n_cand < SEL_CAP ? sh.n_cand : SEL_CAP;
       const unsigned int take = static_cast<unsigned int>(k) - below;
       for (unsigned int c = B.tid; c < n; c += SNT) {
         const double key = sh.cand_key[c];

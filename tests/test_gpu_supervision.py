@@ -141,3 +141,34 @@ def test_selection_sizes_and_key_ranges(saki_lib, lengths, special, mode):
     torch.cuda.synchronize()
     with np.errstate(invalid="ignore"):
         _compare_selection(sel.cpu().numpy(), tv.astype(np.float64), C, valid, off, 99, 1000, mode)
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_selection_with_overlapping_ranges(saki_lib, mode):
+    """Offsets that do not increase: the malformed range is skipped, its
+    neighbours overlap, and two workgroups mark the same rows.  What they select
+    there is not defined, but nothing outside the ranges is written, and the
+    other trajectories are selected as ever."""
+    rng = np.random.default_rng(5 + mode)
+    off = np.array([0, 300] + [300 + 5000, 310] * 40 + [5300, 6000], np.int64)
+    n = 6000
+    tv = (rng.random(n) ** 3).astype(np.float32)
+    tv[[301, 302]] = 1e-38, 3e38  # a wide range of keys: most rows in one bin
+    C = (rng.random(n) < 0.3).astype(np.uint8)
+    say(f"select overlapping ranges mode={mode}")
+    sel = torch.full((n + 4096,), 77, dtype=torch.uint8, device=DEV)
+    ws = torch.full((8 * n + 256 + 65536,), 77, dtype=torch.uint8, device=DEV)
+    need = saki_lib.workspace_bytes(saki_lib.binding.SAKI_OP_SELECT, n, 0)
+    for _ in range(5):
+        saki_lib.saki_select_positions(mode, torch.as_tensor(off, device=DEV), torch.as_tensor(tv, device=DEV),
+                                       torch.as_tensor(C, device=DEV), sel[:n], 99, None, 1000, ws[:need])
+    torch.cuda.synchronize()
+    assert (sel[n:] == 77).all() and (ws[need:] == 77).all()
+    got = sel[:n].cpu().numpy()
+    ends = np.array([0, 300, 5300, 6000])
+    v = np.ones(n, np.uint8)
+    ref = got.copy()
+    alone = saki_lib.select_positions(mode, torch.as_tensor(ends, device=DEV), torch.as_tensor(tv, device=DEV),
+                                      torch.as_tensor(C, device=DEV), 99, torch.as_tensor(v, device=DEV), 1000)
+    ref[:300], ref[5300:] = alone[:300].cpu().numpy(), alone[5300:].cpu().numpy()
+    assert np.array_equal(got, ref)
