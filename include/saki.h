@@ -225,7 +225,9 @@ saki_status saki_route_loss(const void *student, int32_t dtype, int64_t n_rows, 
  *   per_pos      optional per-position outputs ([n_rows], fields may be NULL):
  *                positions after the end of the committed prefix get NaN / -1
  *                and row_status SAKI_ROW_SKIPPED; proposal = the draft, token =
- *                the committed token.
+ *                the committed token.  One of its int32 fields may be the
+ *                draft's own buffer; accepted_len and correction, which hold
+ *                the blocks' state during the call, may overlap no other array.
  *   ws           required: ws_bytes >= saki_workspace_bytes(SAKI_OP_VERIFY, n_rows,
  *                vocab) (256 bytes), 4-byte aligned; it holds the counter from
  *                which workgroups take blocks, cleared by the call on `stream`.

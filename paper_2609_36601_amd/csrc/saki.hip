@@ -28,14 +28,19 @@ __global__ void clear_counter_kernel(unsigned int* c) {
   if (threadIdx.x < 4) c[threadIdx.x] = 0u;
 }
 
-// Verification, before: no block has stopped or is predicted to, no item is taken.
+// Verification, before: no block has stopped or is known to reject, no item is
+// taken.  The proposals are copied here, before any output is written, so that
+// `token` or `proposal` may share the draft's buffer.
 __global__ __launch_bounds__(256) void verify_begin_kernel(unsigned long long* next_item, int64_t n_blocks, int k,
-                                                           int32_t* accepted_len, int32_t* correction) {
+                                                           int32_t* accepted_len, int32_t* correction,
+                                                           const int32_t* draft, int32_t* proposal) {
   const int64_t b = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (b == 0) *next_item = 0ull;
   if (b < n_blocks) {
     accepted_len[b] = stop_word(k, false, -1);
     correction[b] = k;
+    if (proposal)
+      for (int j = 0; j < k; ++j) proposal[b * k + j] = draft[b * k + j];
   }
 }
 
@@ -52,7 +57,7 @@ __global__ __launch_bounds__(256) void verify_end_kernel(VerifyParams P) {
   if (P.has_pp) {
     for (int jj = j + 1; jj < P.k; ++jj) {
       const int64_t r = b * P.k + jj;
-      write_skipped(&P.pp, r, P.draft[r], SAKI_ROW_SKIPPED);
+      write_skipped(&P.pp, r, SAKI_ROW_SKIPPED);
     }
   }
 }
@@ -555,7 +560,7 @@ saki_status saki_spec_verify(const saki_rows* in, int32_t k, const int32_t* draf
   hipStream_t hs = static_cast<hipStream_t>(stream);
   const dim3 per_block(static_cast<unsigned>((P.n_blocks + 255) / 256));
   hipLaunchKernelGGL(saki::verify_begin_kernel, per_block, dim3(256), 0, hs, P.next_item, P.n_blocks, P.k,
-                     P.accepted_len, P.correction);
+                     P.accepted_len, P.correction, P.draft, P.has_pp ? P.pp.proposal : nullptr);
   st = launched("verify_begin_kernel");
   if (st != SAKI_OK) return st;
   const bool bf16 = in->dtype == SAKI_BF16;

@@ -78,9 +78,10 @@ __device__ __forceinline__ double log_ratio_bound(const RowStats& R, double eps,
   return b < 0.0 ? b : 0.0;  // (NaN: no bound)
 }
 
-// o: the per-position outputs, in the argument segment or elsewhere
+// o: the per-position outputs, in the argument segment or elsewhere (the
+// proposals are written by verify_begin_kernel)
 template <typename O>
-__device__ __forceinline__ void write_skipped(const O* o, int64_t r, int32_t draft, uint8_t status) {
+__device__ __forceinline__ void write_skipped(const O* o, int64_t r, uint8_t status) {
   if (o->lambda) o->lambda[r] = nanf_();
   if (o->kl) o->kl[r] = nanf_();
   if (o->tv) o->tv[r] = nanf_();
@@ -89,7 +90,6 @@ __device__ __forceinline__ void write_skipped(const O* o, int64_t r, int32_t dra
   if (o->logp_token) o->logp_token[r] = nanf_();
   if (o->logt_token) o->logt_token[r] = nanf_();
   if (o->logq_token) o->logq_token[r] = nanf_();
-  if (o->proposal) o->proposal[r] = draft;
   if (o->token) o->token[r] = -1;
   if (o->teacher_argmax) o->teacher_argmax[r] = -1;
   if (o->target) o->target[r] = -1;
@@ -161,7 +161,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       const int z = P->draft[r];
       if (uniform(z < 0 || z >= V)) {
         if (B.tid == 0) {
-          if (P->has_pp) write_skipped(&P->pp, r, z, SAKI_ROW_BAD_DRAFT);
+          if (P->has_pp) write_skipped(&P->pp, r, SAKI_ROW_BAD_DRAFT);
           atomicMin(P->accepted_len + b, stop_word(j, false, -1));
         }
         break;
@@ -174,7 +174,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       P = kernel_args<VerifyParams>();
       if (uniform(!R.finite)) {
         if (B.tid == 0) {
-          if (P->has_pp) write_skipped(&P->pp, r, z, SAKI_ROW_NONFINITE);
+          if (P->has_pp) write_skipped(&P->pp, r, SAKI_ROW_NONFINITE);
           atomicMin(P->accepted_len + b, stop_word(j, false, -1));
         }
         break;
@@ -223,7 +223,6 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
           if (P->has_pp && B.tid == 0) {
             if (P->pp.logp_token) P->pp.logp_token[r] = static_cast<float>(static_cast<double>(sz) - R.lse_s);
             if (P->pp.logt_token) P->pp.logt_token[r] = static_cast<float>(static_cast<double>(tz) - R.lse_t);
-            if (P->pp.proposal) P->pp.proposal[r] = z;
             if (P->pp.token) P->pp.token[r] = z;
             if (P->pp.teacher_argmax) P->pp.teacher_argmax[r] = R.vstar;
             if (P->pp.target) P->pp.target[r] = z;
@@ -427,7 +426,6 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         if (P->pp.logp_token) P->pp.logp_token[r] = static_cast<float>(logp_y);
         if (P->pp.logt_token) P->pp.logt_token[r] = static_cast<float>(logt_y);
         if (P->pp.logq_token) P->pp.logq_token[r] = static_cast<float>(logp_y + L.log_ratio(sy, ty));
-        if (P->pp.proposal) P->pp.proposal[r] = z;
         if (P->pp.token) P->pp.token[r] = y;
         if (P->pp.teacher_argmax) P->pp.teacher_argmax[r] = R.vstar;
         if (P->pp.target) P->pp.target[r] = accept ? z : R.vstar;

@@ -325,6 +325,34 @@ def test_verify_positions_evaluated_ahead(saki_lib, nb, k):
     assert np.array_equal(pp["proposal"], draft.cpu().numpy()) and np.all(pp["corrected"][skipped] == 0)
 
 
+@pytest.mark.parametrize("nb, k", [(3, 1), (40, 8), (300, 5)])
+@pytest.mark.parametrize("field", ["token", "proposal", "teacher_argmax"])
+def test_verify_with_an_output_in_the_drafts_buffer(saki_lib, nb, k, field):
+    """A per-position int32 output may be written over the draft: every other
+    output, the proposals of skipped positions among them, is as with buffers of
+    their own."""
+    V, n = 700, nb * k
+    g = torch.Generator(device=DEV).manual_seed(nb)
+    s = padded(torch.randn(n, V, generator=g, device=DEV))
+    t = padded(s + torch.randn(n, V, generator=g, device=DEV))
+    draft, _ = saki_lib.sample(s, 6)
+    draft[torch.rand(n, generator=g, device=DEV) < 0.02] = V + 3
+    s[torch.rand(n, generator=g, device=DEV) < 0.02, 5] = float("nan")
+    say(f"verify {field} in the draft's buffer nb={nb} k={k}")
+    ref = saki_lib.spec_verify(s, t, k, draft, 0.1, 21)
+    pp = saki_lib.alloc_couple_out(n, DEV)
+    pp[field] = draft.clone()
+    acc, corr = (torch.empty(nb, dtype=torch.int32, device=DEV) for _ in range(2))
+    ws = torch.empty(256, dtype=torch.uint8, device=DEV)
+    saki_lib.saki_spec_verify(s, t, k, pp[field], 0.1, 21, 0, -1, acc, corr, pp, ws)
+    torch.cuda.synchronize()
+    assert torch.equal(acc, ref["accepted_len"]) and torch.equal(corr, ref["correction"])
+    assert torch.equal(pp["proposal"], draft)
+    for key in pp:
+        x, y = pp[key].contiguous(), ref["per_pos"][key].contiguous()
+        assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), key
+
+
 @pytest.mark.parametrize("nb", [64, 256])
 def test_verify_of_blocks_that_stop_at_once(saki_lib, nb):
     """Blocks of eight whose first draft the teacher all but excludes: the
