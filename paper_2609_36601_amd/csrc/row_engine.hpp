@@ -1499,6 +1499,10 @@ constexpr double FUSED_REACH = 0.02;
 // largest bound on TV's error accepted from the fused sums (relative; the
 // bound is a worst case, the error itself is far below it)
 constexpr double FUSED_TV_TOL = 3e-6;
+// Rounding of sum_P r as half the sums of r and of |r| over every entry, of
+// sum |r|: chains of 16 float additions, then double (1.3e-7 at most over rows
+// of 1,024 to 5,120 entries; sum |r| is about twice sum_P r).
+constexpr double FUSED_SUM_ROUND = 1.5e-7;
 
 struct FusedConst {
   float msL, cL;  // as in the final sweep
@@ -1693,7 +1697,8 @@ struct FusedFinal {
 
 // acc: the sweep took the expm1 form, where each r carries ~1e-7 of itself as
 // rounding; in the plain form each carries ~6e-8 of p~ e instead, which over
-// P sums to as much as 1e-7 U0.
+// P sums to as much as 1e-7 U0.  (The entries outside P drop out of W + sum |r|
+// exactly, but not out of the sums' own rounding, FUSED_SUM_ROUND.)
 __device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResult& L, const FinalConst& F,
                                       const FusedConst& C, const FusedSums& S, bool acc) {
   FusedFinal out;
@@ -1726,7 +1731,8 @@ __device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResul
   // sum_P p~ e y^2 <= S2 (every entry)
   const double h2 = hmax * LN2_D;
   const double sq = 2.0 * (rho * rho * fabs(S.v[2]) + H0 * H0 * S.U0);
-  const double err = flip + 0.5 * LN2_D * LN2_D * sq * (1.0 + h2) + 1e-7 * ((acc ? S.T0 : S.U0) + S.U0 * h2);
+  const double err = flip + 0.5 * LN2_D * LN2_D * sq * (1.0 + h2) + 1e-7 * ((acc ? S.T0 : S.U0) + S.U0 * h2) +
+                     FUSED_SUM_ROUND * (2.0 * S.T0 - S.v[0]);
   if (!(tvu > 0.0) || !(err <= FUSED_TV_TOL * tvu)) return out;
   out.ok = true;
   out.why = 0;
