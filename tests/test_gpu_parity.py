@@ -800,16 +800,11 @@ def test_endpoint_small_kl(saki_lib, sigma):
     assert np.all(o["kl"] < 0.01)
 
 
-@pytest.mark.parametrize("D", [60.0, 70.0])
-def test_rows_resolved_again_in_the_expm1_forms(saki_lib, D):
+def _redo_rows(n, V, D, seed):
     """Rows whose TV is too small for the plain forms' rounding: five entries
-    share max p ~ 0.2, and one entry with p ~ 1e-23 carries the whole KL of
-    0.2 (t - s = D there), so TV ~ 0.0044 lies below 0.02 sqrt(max p): the
-    first launch lists these rows and the second resolves them with every
-    sweep in the expm1 form.  Every row against the oracle, with the gradient;
-    the oracle confirms that the rows meet that condition."""
-    rng = np.random.default_rng(int(D))
-    n, V = 16, 3000
+    share max p ~ 0.2, and one entry with p ~ 1e-23 carries the whole KL of 0.2
+    (t - s = D there), so TV ~ 0.0044 lies below 0.02 sqrt(max p)."""
+    rng = np.random.default_rng(seed)
     s = np.full((n, V), -10.0) + rng.normal(0, 0.01, (n, V))
     s[:, :5] = rng.normal(0, 0.01, (n, 5))
     j = rng.integers(5, V, n)
@@ -818,12 +813,87 @@ def test_rows_resolved_again_in_the_expm1_forms(saki_lib, D):
     t[np.arange(n), j] += D
     S = torch.as_tensor(s, dtype=torch.float32, device=DEV)
     T = torch.as_tensor(t, dtype=torch.float32, device=DEV)
-    S, T = padded(S), padded(T)
-    b = bridge.bridge_rows(f64(S), f64(T), 0.2)
+    return padded(S), padded(T)
+
+
+def _check_redo_rows(s, t):
+    """The oracle confirms that the rows meet the condition of a second pass."""
+    b = bridge.bridge_rows(f64(s), f64(t), 0.2)
     pmax = np.exp(b["logp"]).max(axis=1)
     assert np.all(b["kl"] >= 0.1) and np.all(pmax < 0.25) and np.all(b["tv"] < 0.02 * np.sqrt(pmax))
+
+
+@pytest.mark.parametrize("D", [60.0, 70.0])
+def test_rows_resolved_again_in_the_expm1_forms(saki_lib, D):
+    """Rows that a workgroup resolves again, in place, with every sweep in the
+    expm1 form.  Every row against the oracle, with the gradient."""
+    S, T = _redo_rows(16, 3000, D, int(D))
+    _check_redo_rows(S, T)
     out, o, R = run_and_compare(saki_lib, S, T, 0.2, 8080, row_offset=7)
     _row_properties(o, 0.2)
+
+
+def _mixed_redo_rows(n, V, every, seed):
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    s = padded(2.0 * torch.randn(n, V, generator=g, device=DEV))
+    t = padded(0.8 * s + torch.randn(n, V, generator=g, device=DEV))
+    rows = np.unique(np.r_[0, 1, np.arange(0, n, every), n - 2, n - 1])
+    ii = torch.as_tensor(rows, device=DEV)
+    s[ii], t[ii] = _redo_rows(rows.size, V, 60.0, seed)
+    _check_redo_rows(s[ii], t[ii])
+    return s, t, rows
+
+
+@pytest.mark.parametrize("n, every", [(1600, 7), (1600, 1), (600, 3)])
+def test_rows_resolved_again_among_rows_from_the_counter(saki_lib, n, every):
+    """The same rows spread over a batch of more rows than workgroups: a row is
+    resolved again while the workgroup's next row has been taken already, and
+    among the last two rows per workgroup, where none is taken ahead.  Every row
+    is written, equals the row of a call of 100 rows (one per workgroup) bit for
+    bit, and the resolved rows match the oracle."""
+    V = 3000
+    s, t, rows = _mixed_redo_rows(n, V, every, 3)
+    say(f"couple rows resolved again n={n} every={every}")
+    kw = dict(route=True, grad_dtype=torch.float32, grad_scale=0.5)
+    out = saki_lib.alloc_couple_out(n, DEV)
+    for v in out.values():
+        v.fill_(77)
+    grad = saki_lib.alloc_rows(n, V, torch.float32, DEV)
+    grad.fill_(77)
+    route = dict(grad_scale=0.5, grad=grad, row_loss=torch.full((n,), 77.0, device=DEV),
+                 loss_sum=torch.zeros(1, dtype=torch.float64, device=DEV))
+    ws = torch.empty(saki_lib.workspace_bytes(saki_lib.SAKI_OP_COUPLE, n, V), dtype=torch.uint8, device=DEV)
+    saki_lib.saki_couple(s, t, 0.2, 9, 40, out, route, ws)
+    torch.cuda.synchronize()
+    got = dict(out, grad=grad, row_loss=route["row_loss"])
+    for a in range(0, n, 100):
+        part = saki_lib.couple(s[a:a + 100], t[a:a + 100], 0.2, 9, 40 + a, **kw)
+        for key in part:
+            if key != "loss_sum":
+                x, y = got[key][a:a + 100].contiguous(), part[key].contiguous()
+                assert torch.equal(x.view(torch.uint8), y.view(torch.uint8)), (key, a)
+    pick = rows if rows.size <= 64 else np.unique(np.r_[rows[:8], rows[-8:], rows[::rows.size // 40]])
+    ii = torch.as_tensor(pick, device=DEV)
+    R = parity.compare_couple(np_out(got), f64(s[ii]), f64(t[ii]), 0.2, 9, 40, pick, grad=f64(grad[ii]) * 2.0)
+    say(R.summary())
+    R.check()
+
+
+@pytest.mark.parametrize("nb, k", [(16, 4), (120, 5), (400, 3)])
+def test_positions_resolved_again(saki_lib, nb, k):
+    """Verification's own second pass, at most one position per CU, at most one
+    block per CU, and more: every evaluated position against the oracle."""
+    s, t, rows = _mixed_redo_rows(nb * k, 3000, 2, 4)
+    draft, _ = saki_lib.sample(s, 8)
+    say(f"verify positions resolved again nb={nb} k={k}")
+    out = saki_lib.spec_verify(s, t, k, draft, 0.2, 17)
+    torch.cuda.synchronize()
+    gpu = dict(accepted_len=out["accepted_len"].cpu().numpy(), correction=out["correction"].cpu().numpy(),
+               per_pos=np_out(out["per_pos"]))
+    R = parity.compare_verify(gpu, f64(s), f64(t), k, draft.cpu().numpy(), 0.2, 17, 0, np.arange(nb))
+    say(R.summary())
+    R.check()
+    assert (gpu["per_pos"]["row_status"][rows] == 0).sum() > rows.size // 2
 
 
 def _min_ms(run, reps=7):
