@@ -100,7 +100,7 @@ __global__ __launch_bounds__(NT, WG_PER_CU) void couple_kernel(CoupleParams) {
         sh.u = philox_uniform(P->seed, ACCEPT, g, 0);
       }
     };
-    const RowStats& R = stats_sweep<T, NT, true, K34>(B, srow, trow, V, P->lam_mid, true, sample_target, idle);
+    const RowStats& R = stats_sweep<T, NT, K34>(B, srow, trow, V, P->lam_mid, true, sample_target, idle);
     if (ahead) ru = static_cast<unsigned int>(__builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)));
     P = kernel_args<CoupleParams>();
     if (uniform(!R.finite)) {

@@ -303,13 +303,6 @@ __device__ __forceinline__ float wave_sum_last(float v) {
   v += dpp_or_0<DPP_ROW_BCAST31>(v);
   return v;
 }
-__device__ __forceinline__ double wave_sum(double v) {
-  v += dpp_d<DPP_XOR1>(v);
-  v += dpp_d<DPP_XOR2>(v);
-  v += dpp_d<DPP_HALF_MIRROR>(v);
-  v += dpp_d<DPP_MIRROR>(v);
-  return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
 __device__ __forceinline__ int wave_min(int v) {
   v = min(v, dpp_i<DPP_XOR1>(v));
   v = min(v, dpp_i<DPP_XOR2>(v));
@@ -322,7 +315,7 @@ __device__ __forceinline__ int wave_min(int v) {
 // a multiple of 4 entries): at each of the first two levels a pair of values
 // swaps halves (rows) and adds, so half as many registers go on, each with a
 // value per half (row); then one reduction inside the rows of 16 serves four
-// values.  About six instructions a value, against 25 for wave_sum each.
+// values.  About six instructions a value, against 25 for one reduced alone.
 template <bool ROWS>  // swap odd rows of a with even rows of b, or the upper half of a with the lower of b
 __device__ __forceinline__ double swap_add(double a, double b) {
   const uint64_t ua = __builtin_bit_cast(uint64_t, a), ub = __builtin_bit_cast(uint64_t, b);

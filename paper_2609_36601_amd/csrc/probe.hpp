@@ -58,13 +58,14 @@ constexpr int PROBE_SEL_CAP = NT;
 static_assert(PROBE_SEL_CAP >= SAKI_MAX_PROBE_K, "the gathered set holds the Top-k");
 // Rows of up to PROBE_MAXC chunks keep each chunk's largest teacher logit.
 constexpr int PROBE_MAXC = 512;
-// Workgroups per CU: four (128 VGPRs, no spills for bf16), so that while some are
-// in a row's serial steps (reductions, the threshold, the gathering) the others
-// stream, and 1,000 rows are one round.  The sweep is bound by VALU issue and
+// Workgroups per CU: four (128 VGPRs; bf16 fits, f32 spills four of them), so that
+// while some are in a row's serial steps (reductions, the threshold, the
+// gathering) the others stream, and 1,000 rows are one round.  The sweep is bound by VALU issue and
 // HBM together: its maxima and the finiteness of its entries take one
 // instruction an entry and array instead of three.  V = 151,936 bf16, k = 16,
-// rows 256 / 1,000 / 4,096: 64 / 155 / 502 us with three and isfinite per entry,
-// 55 / 134 / 484 us now.
+// rows 256 / 1,000 / 4,096: 63 / 155 / 500 us with three and isfinite per entry,
+// three workgroups per CU, 53 / 134 / 486 us now; f32 71 / 231 / 885 us and 70 /
+// 234 / 880 us (1,000 rows of 32,000: 70 and 61 us).
 constexpr int PROBE_WG_PER_CU = 4;
 
 struct ProbeShared {
@@ -80,8 +81,8 @@ struct ProbeShared {
 };
 
 // Pivots counted per sweep in the Top-k searches (one block sum of that many
-// doubles).  Four keep the kernel free of register spills at three workgroups
-// per CU; the searches run only when more than PROBE_SEL_CAP entries reach L.
+// doubles): four fit the registers of PROBE_WG_PER_CU workgroups per CU; the
+// searches run only when more than PROBE_SEL_CAP entries reach L.
 constexpr int PROBE_PIVOTS = 4;
 
 struct Pivots {

@@ -164,8 +164,6 @@ struct Block {
     return m;
   }
 
-  __device__ __forceinline__ float min(float v) { return -max(-v); }
-
   template <typename K>
   __device__ __forceinline__ void argmin(K& key, int& idx) {
     wave_argmin(key, idx);
@@ -434,10 +432,8 @@ struct StatsAcc {
 // to the maximum of s alone they cost one instruction an entry less, but reach
 // 2^(lm (mt - ms) log2 e): the rounding of A(lm) grows with the offset, and with
 // maxima 60 / lm log2 units apart the row would have to go without the node).
-// MID: also the middle node's sums (else the row carries no middle node and
-// the lambda search starts from the ends alone); K34: the third and fourth
-// p-moments of d.
-template <bool TAIL, bool MID, bool K34, typename SH>
+// K34: the third and fourth p-moments of d.
+template <bool TAIL, bool K34, typename SH>
 __device__ __forceinline__ void stats_math(const float* s, const float* t, uint32_t vm, int c,
                                            int lane, bool keep_chunks, bool keep_teacher, float lm, SH& sh,
                                            StatsAcc& a) {
@@ -524,7 +520,7 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     const float d = t[e] - s[e];
     // the middle node's weight p~^(1 - lm) pi~^lm: its exponent is at most 0
     // (as, at <= 0), so it cannot overflow
-    float em = MID ? fexp2(fmaf(lm, at - as, as)) : 0.0f;
+    float em = fexp2(fmaf(lm, at - as, as));
     if (TAIL && !SAKI_VALID(e)) { es = 0.f; et = 0.f; em = 0.f; }
     const float d2 = d * d;
     p1 = fmaf(es, d, p1);
@@ -536,11 +532,9 @@ __device__ __forceinline__ void stats_math(const float* s, const float* t, uint3
     }
     t1 = fmaf(et, d, t1);
     t2 = fmaf(et, d2, t2);
-    if (MID) {
-      q1 = fmaf(em, d, q1);
-      q2 = fmaf(em, d2, q2);
-      gm += em;
-    }
+    q1 = fmaf(em, d, q1);
+    q2 = fmaf(em, d2, q2);
+    gm += em;
     gs += es;
     gt += et;
     if ((e & 7) == 7) {
@@ -707,7 +701,7 @@ __device__ __forceinline__ RowStats stats_combine(Block<NT, SH>& B, float lm, bo
 // whole record in registers across the later sweeps.  idle() runs on
 // the other waves while wave 0 combines the sums; the chunk masses are complete
 // then, the row statistics are not.
-template <typename T, int NT, bool MID = true, bool K34 = true, typename SH, typename Idle>
+template <typename T, int NT, bool K34, typename SH, typename Idle>
 __device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, float lm,
                                        bool keep_chunks, bool keep_teacher, Idle&& idle) {
   constexpr int NW = NT / WAVE;
@@ -716,12 +710,12 @@ __device__ __forceinline__ const RowStats& stats_sweep(Block<NT, SH>& B, const T
   for_chunks<T, NW, false, fill_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      stats_math<TAIL, MID, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, lm, B.sh, a);
+                      stats_math<TAIL, K34>(s, t, vm, c, B.lane, keep_chunks, keep_teacher, lm, B.sh, a);
                     }, row_cache<T>(B.sh));
   stats_post(B, a);
   __syncthreads();
   if (B.wave == 0) {
-    const RowStats R = stats_combine(B, MID ? lm : 0.0f, K34);
+    const RowStats R = stats_combine(B, lm, K34);
     if (B.lane == 0) B.sh.rs.r = R;
   } else {
     idle();
@@ -1692,7 +1686,6 @@ struct FusedFinal {
   bool ok;
   double TV;
   double hmax, flip;
-  int why;  // 0: ok; 1: lambda* or the form not from the node; 2: lambda moved too far; 3: TV bound
 };
 
 // acc: the sweep took the expm1 form, where each r carries ~1e-7 of itself as
@@ -1705,9 +1698,7 @@ __device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResul
   out.ok = false;
   out.TV = 0.0;
   out.hmax = out.flip = 0.0;
-  out.why = 1;
   if (L.sweeps != 0 || L.qp || F.wide || F.cL != C.cL || F.msL != C.msL) return out;
-  out.why = 2;
   const double dl = static_cast<double>(F.lam) - C.lam_e;
   const double dA = static_cast<double>(F.AL) - C.AL_e;
   // |X| over the row (X = d log2 e - cL), with a margin for its rounding
@@ -1722,7 +1713,6 @@ __device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResul
   if (!(fabs(rho) < 0.5)) return out;
   const double Hf = fabs(H0) * (1.0 + 2.0 * fabs(rho)) + 1e-7;
   if (!(Hf < static_cast<double>(FUSED_BAND)) || !(hmax < 0.01)) return out;
-  out.why = 3;
   // such an entry's residual at lambda* is below p~ e (2^Hf - 1) on either side
   const double flip = S.Bd * Hf * LN2_D * 1.02;
   const double tvu = S.T0 + LN2_D * (rho * S.U1 + H0 * S.U0);
@@ -1735,7 +1725,6 @@ __device__ __forceinline__ FusedFinal fused_tv(const RowStats& R, const LamResul
                      FUSED_SUM_ROUND * (2.0 * S.T0 - S.v[0]);
   if (!(tvu > 0.0) || !(err <= FUSED_TV_TOL * tvu)) return out;
   out.ok = true;
-  out.why = 0;
   out.TV = tvu * (R.shift * R.inv_s);
   out.hmax = hmax;
   out.flip = flip;

@@ -170,7 +170,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
       auto idle = [&]() {
         if (B.tid == VNT - WAVE) sh.u = philox_uniform(P->seed, ACCEPT, g, 0);
       };
-      const RowStats& R = stats_sweep<T, VNT, true, K34>(B, srow, trow, V, P->lam_mid, false, false, idle);
+      const RowStats& R = stats_sweep<T, VNT, K34>(B, srow, trow, V, P->lam_mid, false, false, idle);
       P = kernel_args<VerifyParams>();
       if (uniform(!R.finite)) {
         if (B.tid == 0) {
@@ -266,8 +266,9 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         }
       }
       __syncthreads();
-      const int fused = __builtin_amdgcn_readfirstlane(plan.fused);
-      if (fused < 0) break;
+      const int way = __builtin_amdgcn_readfirstlane(plan.fused);
+      if (way < 0) break;
+      const bool fused = VNT == 256 && way != 0;
       // once said, a rejection stands (the positions behind may have been skipped)
       const bool rejected = uniform(plan.C != 0);
       LamResult L;
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         __syncthreads();
         return __builtin_amdgcn_readfirstlane(static_cast<int>(sh.next)) != 0;
       };
-      if (fused != 0) {
+      if (fused) {
         // the decision at the start point (in float, as in the coupling kernel)
         const float lam_g = static_cast<float>(plan.S0.lam);
         const float A_g = static_cast<float>(plan.S0.A * static_cast<double>(LOG2E));
@@ -365,7 +366,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
         }
       }
       if (search) {
-        const LamEval E0 = fused != 0 ? plan.E0 : LamEval{};
+        const LamEval E0 = fused ? plan.E0 : LamEval{};
         L = lambda_search_with(R, P->eps, [&](float lam, bool acc) {
           ++swept;
           if (B.tid == 0) {
@@ -373,7 +374,7 @@ __global__ __launch_bounds__(VNT, VNT == 256 ? 2 : 1) void verify_kernel(VerifyP
             rj = look(P->correction + b);
           }
           return lam_sweep<T, VNT>(B, srow, trow, V, R, lam, acc);
-        }, [&] { return swept > 0 && gone(); }, force_acc, static_cast<float>(plan.S0.lam), fused != 0, E0, tv_acc);
+        }, [&] { return swept > 0 && gone(); }, force_acc, static_cast<float>(plan.S0.lam), fused, E0, tv_acc);
         if (L.sweeps < 0) break;
         F = final_const(R, L, force_acc);
       }
