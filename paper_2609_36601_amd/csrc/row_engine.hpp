@@ -743,8 +743,8 @@ __device__ __forceinline__ int entry_owner(int v) {
 //   FAST : w = 2^{a + lam X}.
 //   ACC  : w - p~ = p~ expm1(lam x), with expm1 accurate for small arguments
 //          (rows whose KL is small).
-//   SHIFT: where lam (dmax - c) could overflow float, w' = 2^{a + lam X - sigl}
-//          with a shift sigl (log2 units); W = sum w' (plain form), or in the
+//   SHIFT: where 2^{lam X} could overflow float, w' = 2^{a + lam X - sigl}
+//          with a shift sigl (log2 units, or 0); W = sum w' (plain form), or in the
 //          expm1 form sum (w' - p~') with w' - p~' = p~' expm1(lam x) where
 //          |lam x| < 1/16 (p~' = 2^{a - sigl}), so the sums keep their
 //          relative precision and do not overflow.  Rows need it rarely, so
@@ -898,14 +898,20 @@ __device__ __forceinline__ LamEval lam_sweep_mode(Block<NT, SH>& B, const T* sro
 
 // Evaluates A and its derivatives at lam over the whole row; acc selects the
 // expm1 form.  Where lam x can exceed 60 (natural units) for some entry, the
-// exponents are shifted by sigl so that lam x - sig <= 60 for every entry.
-// Every thread gets the same result.
+// weights are taken as one exponential of a + lam X, whose largest value over
+// the row is at most lam (mt - ms - c), a being at most 0 (far below lam x at
+// an entry that the student all but excludes), and shifted by sigl where that
+// too exceeds 60.  Every thread gets the same result.
 template <typename T, int NT, typename SH>
 __device__ __forceinline__ LamEval lam_sweep(Block<NT, SH>& B, const T* srow, const T* trow, int V, const RowStats& R,
                              float lam, bool acc) {
   const double top = static_cast<double>(lam) * (static_cast<double>(R.dmax) - R.c);  // largest lam x
-  const float sigl = top <= 60.0 ? 0.0f : static_cast<float>((top - 60.0) * static_cast<double>(LOG2E));
-  if (sigl != 0.0f) return lam_sweep_mode<T, NT, LAM_SHIFT>(B, srow, trow, V, R, lam, sigl, acc);
+  if (top > 60.0) {
+    const double w_top = fmin(top, static_cast<double>(lam) * (static_cast<double>(R.mt) - R.ms - R.c));
+    const float sigl = w_top <= 60.0 ? 0.0f : static_cast<float>((w_top - 60.0) * static_cast<double>(LOG2E));
+    // without a shift the sums are those of w - p~, as in the other forms
+    return lam_sweep_mode<T, NT, LAM_SHIFT>(B, srow, trow, V, R, lam, sigl, acc || sigl == 0.0f);
+  }
   if (acc) return lam_sweep_mode<T, NT, LAM_ACC>(B, srow, trow, V, R, lam, 0.0f, true);
   return lam_sweep_mode<T, NT, LAM_FAST>(B, srow, trow, V, R, lam, 0.0f, false);
 }
