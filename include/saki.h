@@ -160,7 +160,8 @@ size_t saki_workspace_bytes(int op, int64_t n_rows, int64_t vocab);
  *   route  NULL for coupling only
  *   ws     required when n_rows > 0: ws_bytes >= saki_workspace_bytes(SAKI_OP_COUPLE,
  *          n_rows, vocab), 8-byte aligned.  Its first 256 bytes hold the counter
- *          from which workgroups take rows (cleared by the call on `stream`); the
+ *          from which workgroups take rows (cleared on `stream` by a call of more
+ *          rows than workgroups run at once; smaller ones do not use it); the
  *          scaled row losses follow (with route->loss_sum).  Calls that may run
  *          at the same time need separate workspaces.
  * More than 2^31 - 1 rows in one call is SAKI_E_SHAPE (split the rows into calls
@@ -178,14 +179,14 @@ saki_status saki_couple(const saki_rows *in, double eps, uint64_t seed, const sa
  * work counter and the scaled row losses live in a static device array of the
  * library (256 + 12 * SAKI_STATIC_MAX_ROWS bytes = 3 MiB + 256 B, the size of a
  * workspace for that many rows), which each GPU the library runs on holds
- * until the process ends.  Its device
- * address is looked up once per device, on the first call made with that
- * device current.  The call allocates and frees nothing.
+ * until the process ends.  Its device address is looked up once per device, on
+ * the first call made with that device current.  The call allocates and frees
+ * nothing.
  *   n_rows > SAKI_STATIC_MAX_ROWS  SAKI_E_SHAPE, nothing enqueued (split the
  *                                  rows into calls with row_offset)
- * The array keeps the last call's contents; each call clears the counters
- * itself (a kernel on `stream`), writes every scaled row loss before summing
- * them.  All calls on one GPU share the array: calls whose work can
+ * The array keeps the last call's contents; a call that uses the counter clears
+ * it first (a kernel on `stream`), and one that sums the scaled row losses has
+ * written them all.  All calls on one GPU share the array: calls whose work can
  * overlap in time on one GPU (other streams, concurrent graph replays) race
  * and give wrong results; serialise them, or use saki_couple with separate
  * workspaces. */
@@ -213,9 +214,10 @@ saki_status saki_route_loss(const void *student, int32_t dtype, int64_t n_rows, 
 
 /* Speculative block verification (Sec. 3.5, App. F, App. I).  Rows are
  * block-major: row b*k + j holds position j of block b, whose student draft is
- * draft[b*k + j].  Positions are examined in order; position j is accepted iff
- * u_j < alpha_j(draft_j) with u_j the ACCEPT uniform of its global row; the
- * block commits the accepted prefix of length n and, if n < k, the correction
+ * draft[b*k + j].  Position j is accepted iff u_j < alpha_j(draft_j) with u_j
+ * the ACCEPT uniform of its global row, and a block stops at its first position
+ * that is not (positions behind it may be read and evaluated, and leave no
+ * trace in the outputs); the block commits the accepted prefix of length n and, if n < k, the correction
  * drawn from [q_n - p_n]_+ at position n.  With eos_id >= 0 an accepted draft
  * equal to eos_id at position j ends the block: n = j + 1, no correction.  A
  * position with bad data (non-finite logits, draft outside the vocabulary) ends
@@ -230,7 +232,7 @@ saki_status saki_route_loss(const void *student, int32_t dtype, int64_t n_rows, 
  *                the blocks' state during the call, may overlap no other array.
  *   ws           required: ws_bytes >= saki_workspace_bytes(SAKI_OP_VERIFY, n_rows,
  *                vocab) (256 bytes), 4-byte aligned; it holds the counter from
- *                which workgroups take blocks, cleared by the call on `stream`.
+ *                which workgroups take positions, cleared by the call on `stream`.
  *                Calls that may run at the same time need separate workspaces.
  * More than 2^31 - 1 blocks is SAKI_E_SHAPE. */
 saki_status saki_spec_verify(const saki_rows *in, int32_t k, const int32_t *draft, double eps,

@@ -1481,9 +1481,10 @@ __device__ __forceinline__ double final_sweep_any(Block<NT, SH>& B, const T* sro
 //           those of X, i.e. A', A'' and A''' (the model's step is accepted
 //           only within FUSED_REACH lam_g of the node, against a bound on
 //           A'''');
-//   final : over P = {y > 0}: T0 = sum r, U0 = sum p~ e, U1 = sum p~ e y, and
-//           the mass Bd = sum p~ e over the band |y| < FUSED_BAND; per chunk
-//           (keep_res) the masses sum_P r and sum_P p~ e;
+//   final : over P = {r > 0}: T0 = sum r, U0 = sum p~ e, U1 = sum p~ e y (each
+//           as half of a sum over every entry plus half of one of absolute
+//           values or signs), and the mass Bd = sum p~ e over the band |y| <
+//           FUSED_BAND; per chunk (keep_res) the masses sum_P r and sum_P p~ e;
 //   grad  : coef p_v under the accept decision taken at the start point.
 // At lambda* (node and model) each exponent moves by h = dl X - dA = rho y +
 // H0 (dl, dA the changes of lambda and of A log2 e; rho = dl / lam_g,
@@ -1652,9 +1653,10 @@ __device__ __forceinline__ double dominant_fix_fused(float s, float t, const Fus
 // The lambda node of the fused sums: sum_v p~ 2^{lam X} = 2^AL (sum p~ + W).
 // A'''' is not summed: A4 holds the bound max_v (x_v - A')^2 A'' on its size
 // (a fourth central moment is at most the squared range times the variance),
-// which the model's acceptance test needs and whose term in the model itself
-// is negligible within the node's reach (FUSED_REACH; none at the teacher end,
-// whose node only settles lambda* = 1).
+// which the model's acceptance test needs.  As a term of the model it is too
+// large: at the edge of the node's reach (FUSED_REACH; none at the teacher end,
+// whose node only settles lambda* = 1) lambda* can be off by 4e-6, elsewhere far
+// less (1e-7 over a workload's rows).
 // acc: the sweep took the expm1 form (else the dominant entry's term of W is
 // taken exactly).
 __device__ __forceinline__ LamEval fused_node(const RowStats& R, FusedSums& S, const FusedConst& C, bool end_first,
