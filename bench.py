@@ -42,16 +42,16 @@ KERNEL_SOURCES["stream"] = KERNEL_SOURCES["couple"]
 # FETCH_SIZE is scaled by 2.0 and WRITE_SIZE by 1.0.  Keyed by the SHA-256 of
 # the kernel's sources: a changed kernel reports traffic = null until re-measured.
 MEASURED_TRAFFIC = {
-    "couple": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1":
-               dict(fetch_kib=38032057.5, write_kib=40658839.2, fetch_scale=2.0, write_scale=1.0)},
-    "verify": {"3245bc13811329aa826ac93fd332e32affc9623fff5af17fa3cbf0a5b3667232":
-               dict(fetch_kib=13034843.4, write_kib=4339.4, fetch_scale=2.0, write_scale=1.0)},
-    "stream": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1":
-               dict(fetch_kib=2623863.2, write_kib=2845783.1, fetch_scale=2.0, write_scale=1.0)},
-    "route": {"b052037693f473bf4a315548335b8981897d705cc1be078d74890b3d181353de":
-               dict(fetch_kib=17097070.8, write_kib=41516477.4, fetch_scale=2.0, write_scale=1.0)},
-    "probe": {"fbdb1a7eacd3ac26c99e68125dcce42615ebf2df3103139a0eb00301c7bf3d9a":
-               dict(fetch_kib=1285172.5, write_kib=978.1, fetch_scale=2.0, write_scale=1.0)},
+    "couple": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465":
+               dict(fetch_kib=38054345.8, write_kib=40724070.0, fetch_scale=2.0, write_scale=1.0)},
+    "verify": {"4942b7b152a40bb5cb25bde7305fd2b53e27ce1616a2791182e61566878c29d7":
+               dict(fetch_kib=13048099.8, write_kib=6189.4, fetch_scale=2.0, write_scale=1.0)},
+    "stream": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465":
+               dict(fetch_kib=2628880.2, write_kib=2843952.0, fetch_scale=2.0, write_scale=1.0)},
+    "route": {"178781ca16b3aa29d7d6ba38622e67e0cb6504cf4bfd266de313fe494b20f18d":
+               dict(fetch_kib=17097154.5, write_kib=41859311.4, fetch_scale=2.0, write_scale=1.0)},
+    "probe": {"796730dcd6067475acfd869347f5b9fad31050ebda1d8899c083bd76f204eac3":
+               dict(fetch_kib=1285452.9, write_kib=967.5, fetch_scale=2.0, write_scale=1.0)},
 }
 
 
@@ -63,8 +63,8 @@ MEASURED_TRAFFIC = {
 # four cycles each), 256 CUs x 2.4 GHz = 6.14e11 per second.
 VALU_ISSUE_PEAK = 256 * 2.4e9
 MEASURED_VALU = {
-    "couple": {"de3e977737a1d797fdf6f7ce402b088115587b6c9865a72e52276e4a7a2a51f1": 8.719e9},
-    "verify": {"3245bc13811329aa826ac93fd332e32affc9623fff5af17fa3cbf0a5b3667232": 2.892e9},
+    "couple": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465": 8.886e9},
+    "verify": {"4942b7b152a40bb5cb25bde7305fd2b53e27ce1616a2791182e61566878c29d7": 2.972e9},
 }
 
 
