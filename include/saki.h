@@ -313,7 +313,8 @@ saki_status saki_commit(const saki_traj *traj, int32_t k, int32_t eos_id,
  * U is the Philox uniform of stream 7, index 0, of the global row row_offset + r.
  * Selected rows take the teacher-mode loss and the others keep RKL: pass
  * `selected` as `corrected` to saki_route_loss.  tv, corrected (uint8) and
- * selected are [n_rows] device arrays; ws holds one double per row
+ * selected are [n_rows] device arrays; selected may be the buffer of corrected or
+ * of valid_mask.  ws holds one double per row
  * (saki_workspace_bytes(SAKI_OP_SELECT, n_rows, 0)), 8-byte aligned. */
 #define SAKI_SELECT_RANDOM 0
 #define SAKI_SELECT_TV_WEIGHTED 1

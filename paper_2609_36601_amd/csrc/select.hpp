@@ -68,7 +68,9 @@ __device__ __forceinline__ int sel_bin(double key, double base, double scale) {
 // Any set of keys (ties, infinities, more rows in one bin than LDS holds, more
 // than 2^31 rows): bisection over the keys' order-preserving 64-bit images for
 // the k-th smallest, ties to the lower row by a scan in row order.  The rows of
-// `tier` for which in(key) holds are marked 1 or 0; others are left.
+// `tier` for which in(key) holds are marked SEL_TAKEN or SEL_LEFT; others keep
+// their tier.
+constexpr uint8_t SEL_TAKEN = 3, SEL_LEFT = 4;
 template <int SNT, typename In>
 __device__ void select_bisect(Block<SNT, SelShared<SNT>>& B, const SelectParams& P, int64_t lo_r, int64_t hi_r,
                               int tier, double k, In in) {
@@ -99,7 +101,7 @@ __device__ void select_bisect(Block<SNT, SelShared<SNT>>& B, const SelectParams&
       mine = P.sel[r] == tier && in(key);
       const uint64_t o = order_bits(key);
       eq = mine && o == T;
-      if (mine && !eq) P.sel[r] = o < T ? 1 : 0;
+      if (mine && !eq) P.sel[r] = o < T ? SEL_TAKEN : SEL_LEFT;
     }
     const uint64_t m = __ballot(eq);
     if (B.lane == 0) B.sh.wave_tot[B.wave] = static_cast<unsigned int>(__popcll(m));
@@ -109,7 +111,7 @@ __device__ void select_bisect(Block<SNT, SelShared<SNT>>& B, const SelectParams&
       before += w < B.wave ? B.sh.wave_tot[w] : 0u;
       all += B.sh.wave_tot[w];
     }
-    if (eq) P.sel[r] = static_cast<double>(before) < need ? 1 : 0;
+    if (eq) P.sel[r] = static_cast<double>(before) < need ? SEL_TAKEN : SEL_LEFT;
     need -= static_cast<double>(all);
     __syncthreads();
   }
@@ -309,19 +311,10 @@ __global__ __launch_bounds__(SNT) void select_kernel(SelectParams P) {
       __syncthreads();
     } else {
       select_bisect<SNT>(B, P, lo, hi, tier, k - static_cast<double>(below), [&](double key) { return side(key) == 0; });
+      // from `sel` and the keys alone: the inputs may be the buffer `sel` itself
       for (int64_t r = lo + B.tid; r < hi; r += SNT) {
-        // the bisection has marked the window's rows (0 or 1)
-        const double key = P.keys[r];
-        const bool M = P.valid ? (P.valid[r] != 0) : true;
-        if (!M) {
-          P.sel[r] = 0;
-          continue;
-        }
-        const bool t0 = P.mode == SAKI_SELECT_RANDOM || static_cast<double>(P.tv[r]) > 0.0;
-        if ((t0 ? 0 : 1) != tier)
-          P.sel[r] = outside(t0 ? 0 : 1);
-        else if (side(key) != 0)
-          P.sel[r] = side(key) < 0 ? 1 : 0;
+        const uint8_t t = P.sel[r];
+        P.sel[r] = t == SEL_TAKEN ? 1 : t == SEL_LEFT ? 0 : t != tier ? outside(t) : side(P.keys[r]) < 0 ? 1 : 0;
       }
       __syncthreads();
     }

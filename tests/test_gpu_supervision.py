@@ -143,6 +143,31 @@ def test_selection_sizes_and_key_ranges(saki_lib, lengths, special, mode):
         _compare_selection(sel.cpu().numpy(), tv.astype(np.float64), C, valid, off, 99, 1000, mode)
 
 
+@pytest.mark.parametrize("special", ["none", "inf"])
+@pytest.mark.parametrize("buffer", ["corrected", "valid"])
+def test_selection_in_place(saki_lib, special, buffer):
+    """The selection may be written over the corrections or the validity it is
+    computed from, whichever way a trajectory is resolved (infinite keys: all in
+    one bin, the bisection)."""
+    rng = np.random.default_rng(12)
+    off = np.array([0, 5000, 5900, 9900])
+    n = int(off[-1])
+    tv = (rng.random(n) ** 3).astype(np.float32)
+    if special == "inf":
+        tv[rng.random(n) < 0.6] = np.inf
+    C = (rng.random(n) < 0.3).astype(np.uint8)
+    valid = (rng.random(n) < 0.9).astype(np.uint8)
+    say(f"select in place special={special} buffer={buffer}")
+    c, v = torch.as_tensor(C, device=DEV), torch.as_tensor(valid, device=DEV)
+    ws = torch.empty(saki_lib.workspace_bytes(saki_lib.binding.SAKI_OP_SELECT, n, 0), dtype=torch.uint8, device=DEV)
+    sel = c if buffer == "corrected" else v
+    saki_lib.saki_select_positions(1, torch.as_tensor(off, device=DEV), torch.as_tensor(tv, device=DEV), c, sel, 99, v,
+                                   1000, ws)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore"):
+        _compare_selection(sel.cpu().numpy(), tv.astype(np.float64), C, valid, off, 99, 1000, 1)
+
+
 @pytest.mark.parametrize("mode", [0, 1])
 def test_selection_with_overlapping_ranges(saki_lib, mode):
     """Offsets that do not increase: the malformed range is skipped, its
