@@ -1500,9 +1500,11 @@ constexpr double FUSED_REACH = 0.02;
 // largest bound on TV's error accepted from the fused sums (relative; the
 // bound is a worst case, the error itself is far below it)
 constexpr double FUSED_TV_TOL = 3e-6;
-// Rounding of sum_P r as half the sums of r and of |r| over every entry, of
-// sum |r|: chains of 16 float additions, then double (1.3e-7 at most over rows
-// of 1,024 to 5,120 entries; sum |r| is about twice sum_P r).
+// Rounding of sum_P r as half the sums of r and of |r| over every entry, as a
+// share of sum |r| (about twice sum_P r): chains of eight float additions, then
+// double, 1.0e-7 at most over rows of 1,024 to 5,120 entries.  (In chains of
+// sixteen 1.3e-7, and TV's error against 64 bits 4 to 6% larger than with sum_P r
+// itself, which costs an instruction an entry; in chains of eight it is the same.)
 constexpr double FUSED_SUM_ROUND = 1.5e-7;
 
 struct FusedConst {
@@ -1543,7 +1545,8 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
   for_chunks<T, NW, true, use_mode<T, SH>()>(srow, trow, V, B.wave, B.lane,
                     [&](auto tail, const float* s, const float* t, uint32_t vm, int c) {
                       constexpr bool TAIL = decltype(tail)::value;
-                      float w = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f, r0 = 0.f, d0 = 0.f, a1 = 0.f;
+                      float w[2] = {0.f, 0.f}, r0[2] = {0.f, 0.f};  // chains of eight (FUSED_SUM_ROUND)
+                      float s1 = 0.f, s2 = 0.f, s3 = 0.f, d0 = 0.f, a1 = 0.f;
                       float g[EPL], ys[EPL], pes[EPL], rs[EPL];
 #pragma unroll
                       for (int e = 0; e < EPL; ++e) {
@@ -1555,7 +1558,7 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                         float r = (MODE == FIN_ACC) ? pt * expm1_sel(y * LN2, ee) : fmaf(pt, ee, -pt);
                         float pe = pt + r;
                         if (TAIL && !SAKI_VALID(e)) { r = 0.f; pe = 0.f; }
-                        w += r;
+                        w[e >> 3] += r;
                         const float y2 = y * y;
                         s1 = fmaf(pe, y, s1);
                         s2 = fmaf(pe, y2, s2);
@@ -1563,7 +1566,7 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                         // the sums over P = {r > 0} as halves of sums and sums of
                         // absolute values (the absolute value and the sign cost
                         // nothing or one instruction; a selected sum costs two more)
-                        r0 += fabsf(r);
+                        r0[e >> 3] += fabsf(r);
                         d0 += copysignf(pe, r);
                         a1 = fmaf(pe, fabsf(y), a1);
                         ys[e] = y;
@@ -1598,11 +1601,11 @@ __device__ __forceinline__ FusedSums fused_sweep(Block<NT, SH>& B, const T* srow
                           B.sh.chunk_b[c] = q;
                         }
                       }
-                      acc[0] += static_cast<double>(w);
+                      acc[0] += static_cast<double>(w[0]) + static_cast<double>(w[1]);
                       acc[1] += static_cast<double>(s1);
                       acc[2] += static_cast<double>(s2);
                       acc[3] += static_cast<double>(s3);
-                      acc[4] += static_cast<double>(r0);
+                      acc[4] += static_cast<double>(r0[0]) + static_cast<double>(r0[1]);
                       D0 += d0;
                       A1 += a1;
                       if (GRAD) store_lane<G, TAIL>(grow, c, B.lane, V, g);

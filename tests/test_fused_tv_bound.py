@@ -1,5 +1,5 @@
 """The rounding term of the fused sweep's TV bound, on the CPU: sum_P r is taken
-as half of sum r plus half of sum |r| over every entry, in chains of sixteen
+as half of sum r plus half of sum |r| over every entry, in chains of eight
 float additions that go on in double, so its rounding is a share of sum |r|,
 not of sum_P r."""
 import os
@@ -12,10 +12,10 @@ HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))
 
 
 def _chains(x):
-    """Sums over groups of 16 in float, of the groups in double."""
-    acc = np.zeros(x.size // 16, np.float32)
-    for k in range(16):
-        acc = (acc + x.reshape(-1, 16)[:, k]).astype(np.float32)
+    """Sums over groups of 8 in float, of the groups in double."""
+    acc = np.zeros(x.size // 8, np.float32)
+    for k in range(8):
+        acc = (acc + x.reshape(-1, 8)[:, k]).astype(np.float32)
     return acc.astype(np.float64).sum()
 
 
