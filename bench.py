@@ -42,16 +42,16 @@ KERNEL_SOURCES["stream"] = KERNEL_SOURCES["couple"]
 # FETCH_SIZE is scaled by 2.0 and WRITE_SIZE by 1.0.  Keyed by the SHA-256 of
 # the kernel's sources: a changed kernel reports traffic = null until re-measured.
 MEASURED_TRAFFIC = {
-    "couple": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465":
-               dict(fetch_kib=38054345.8, write_kib=40724070.0, fetch_scale=2.0, write_scale=1.0)},
-    "verify": {"4942b7b152a40bb5cb25bde7305fd2b53e27ce1616a2791182e61566878c29d7":
-               dict(fetch_kib=13048099.8, write_kib=6189.4, fetch_scale=2.0, write_scale=1.0)},
-    "stream": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465":
-               dict(fetch_kib=2628880.2, write_kib=2843952.0, fetch_scale=2.0, write_scale=1.0)},
-    "route": {"178781ca16b3aa29d7d6ba38622e67e0cb6504cf4bfd266de313fe494b20f18d":
-               dict(fetch_kib=17097154.5, write_kib=41859311.4, fetch_scale=2.0, write_scale=1.0)},
-    "probe": {"796730dcd6067475acfd869347f5b9fad31050ebda1d8899c083bd76f204eac3":
-               dict(fetch_kib=1285452.9, write_kib=967.5, fetch_scale=2.0, write_scale=1.0)},
+    "couple": {"00d65faa91eaf0f80742922469398c4c9f569e617eee4fdf2719db3235af0969":
+               dict(fetch_kib=38047288.8, write_kib=40718215.0, fetch_scale=2.0, write_scale=1.0)},
+    "verify": {"17be2578ccb9247a1ba10972fbb1ae586ce45e1066bccf6e395071a279bdb386":
+               dict(fetch_kib=13043150.1, write_kib=6189.4, fetch_scale=2.0, write_scale=1.0)},
+    "stream": {"00d65faa91eaf0f80742922469398c4c9f569e617eee4fdf2719db3235af0969":
+               dict(fetch_kib=2629986.2, write_kib=2850790.9, fetch_scale=2.0, write_scale=1.0)},
+    "route": {"af8737b4ad1a8ab44931f40886983b160244436e1bd2f6ce7088195b44814fc3":
+               dict(fetch_kib=17097049.1, write_kib=41663778.2, fetch_scale=2.0, write_scale=1.0)},
+    "probe": {"3a270d9228d1c9e89c5db6d7d1e7f5a0f929e3f9f2aca46c77c7c72a5e3c31df":
+               dict(fetch_kib=1285231.1, write_kib=976.0, fetch_scale=2.0, write_scale=1.0)},
 }
 
 
@@ -63,8 +63,8 @@ MEASURED_TRAFFIC = {
 # four cycles each), 256 CUs x 2.4 GHz = 6.14e11 per second.
 VALU_ISSUE_PEAK = 256 * 2.4e9
 MEASURED_VALU = {
-    "couple": {"a0a6ed89f5f8861d19a210f56909a8d03ea2fb3439c54dc5ddb2ecec290a5465": 8.886e9},
-    "verify": {"4942b7b152a40bb5cb25bde7305fd2b53e27ce1616a2791182e61566878c29d7": 2.972e9},
+    "couple": {"00d65faa91eaf0f80742922469398c4c9f569e617eee4fdf2719db3235af0969": 8.915e9},
+    "verify": {"17be2578ccb9247a1ba10972fbb1ae586ce45e1066bccf6e395071a279bdb386": 2.978e9},
 }
 
 
